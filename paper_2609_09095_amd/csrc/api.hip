@@ -92,10 +92,11 @@ bool fused_a(int64_t m, int64_t n, ozaki25_moduli_set set) {
 }
 
 // The plane layout between the stages of one ozaki25_dgemm* call: the
-// published set's mixed slots (21 bytes per element in place of the stored
-// planes' 30, and cheaper products), the all-byte set's stored planes.
+// published set's mixed slots (24 bytes per element in place of the stored
+// planes' 30, and five sixths of their products' matrix time), the all-byte
+// set's stored planes.
 int inner_layout(ozaki25_moduli_set set) { return bytes_set(set) ? (int)set : oz::kLayoutMixed; }
-static_assert(oz::kMixedBytes <= oz::kPlanes * oz::kKAlign, "mixed slots fit the room of the stored planes");
+static_assert(oz::kMixedSlots <= oz::kPlanes, "mixed slots fit the room of the stored planes");
 
 // planes of A and B (room for the stored planes of the set), exponents, and
 // the residue products: int16 for the published set (|c| <= 0.51 m <= 556), int8 for the all-byte set (|c| <= 128)
@@ -156,8 +157,8 @@ hipError_t scan_and_deconstruct(int planes_layout, ozaki25_quantiser quant, int 
       e = oz::launch_scan_cols(nv, k, Xr, ldx, exps + v0, s);
     }
     if (e == hipSuccess)
-      e = oz::launch_deconstruct(planes_layout, (int)quant, side, nv, v0, vecs, k, kp, t, Xr, ldx, exps + v0,
-                                 side == 1, planes, s);
+      e = oz::launch_deconstruct(planes_layout, (int)quant, side, nv, vecs, k, kp, t, Xr, ldx, exps + v0,
+                                 side == 1, planes + v0 * oz::kKAlign, s);
   }
   if (side == 1 && e == hipSuccess) e = oz::launch_keys_to_sigma(vecs, t, exps, s);
   return e;
@@ -549,10 +550,10 @@ ozaki25_status ozaki25_dgemm_accurate(int64_t m, int64_t n, int64_t k, const dou
   if (e == hipSuccess) e = accurate_exponents(set, m, n, k, A, lda, B, ldb, ea, eb, base + w.total, aw, s);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[1], s);
   if (e == hipSuccess && !fused)
-    e = oz::launch_deconstruct(inner_layout(set), (int)quant, 0, m, 0, m, k, kp, kAccurateT, A, lda, ea, false, pa, s);
+    e = oz::launch_deconstruct(inner_layout(set), (int)quant, 0, m, m, k, kp, kAccurateT, A, lda, ea, false, pa, s);
   // (the published set's fused product makes B's digit planes itself)
   if (e == hipSuccess && (bytes || !fused))
-    e = oz::launch_deconstruct(inner_layout(set), (int)quant, 1, n, 0, n, k, kp, kAccurateT, B, ldb, eb, false, pb, s);
+    e = oz::launch_deconstruct(inner_layout(set), (int)quant, 1, n, n, k, kp, kAccurateT, B, ldb, eb, false, pb, s);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[2], s);
   if (e == hipSuccess) {
     if (fused && bytes)

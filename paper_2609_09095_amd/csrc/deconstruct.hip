@@ -202,79 +202,29 @@ __device__ __forceinline__ void emit_modulus(const double (&y)[kElems], const ui
   }
 }
 
-// Mixed slots (moduli.hpp): a square's two digit planes as FP6, a nonsquare's
-// centred residue (|x| <= 255, exact) as fp16.
+// Mixed slots (kMixedSlots): a square's two digit planes as above, a
+// nonsquare's centred residue (|x| <= 255, exact) as fp16, the thread's first
+// eight k in slot 2 I and its last eight in slot 2 I + 1, so that each
+// 16-byte store of a wavefront fills 1 KiB of contiguous bytes.
 typedef __fp16 h2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_f16(int a, int b) {
   return __builtin_bit_cast(uint32_t, (h2)__builtin_amdgcn_cvt_pkrtz((float)a, (float)b));
 }
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x6 __attribute__((ext_vector_type(6)));
-
-// the value of the lane eight further round its row of 16: the other group of
-// the same vector's fragment
-__device__ __forceinline__ uint32_t other_group(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, true);  // row_ror:8
-}
-
-// Where a thread's bytes go: the operand's base at its k block, the vector,
-// its fragment (two groups of 16 k) and chunk (one group).
-struct MixedAt {
-  int8_t* base;
-  int64_t vstride, v;
-  int group;  // 0-7 within the k block
-};
 
 template <int I, int RM>
 __device__ __forceinline__ void emit_mixed(const double (&y)[kElems], const uint32_t (&ylo)[kElems],
-                                           const MixedAt& at) {
+                                           int8_t* planes, int64_t plane_stride, int64_t off) {
   constexpr int M = kModulus[I];
-  const int v5 = (int)(at.v & 31);
   if constexpr (!mixed_half(I)) {
-    // one conversion gives both digits' 16 codes: it takes its two sources'
-    // values in turn, so the halves of d0 make the low 96 bits and those of
-    // d1 the high ones (the k order within a fragment is free: it is the
-    // same for every slot and operand)
-    v16f s0, s1;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      float lo0, hi0, lo1, hi1;
-      split_square<root_of(I)>((float)centred_residue<M, RM>(y[c], ylo[c]), lo0, hi0);
-      split_square<root_of(I)>((float)centred_residue<M, RM>(y[8 + c], ylo[8 + c]), lo1, hi1);
-      s0[c] = lo0;
-      s0[8 + c] = hi0;
-      s1[c] = lo1;
-      s1[8 + c] = hi1;
-    }
-    const u32x6 w = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(s0, s1, 8.0f);
-    // a fragment holds two groups: the even group's lane takes d0's, the odd
-    // one's d1's
-    const bool odd = at.group & 1;
-    uint32_t f[6];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const uint32_t got = other_group(odd ? w[c] : w[3 + c]);
-      f[c] = odd ? got : w[c];
-      f[3 + c] = odd ? w[3 + c] : got;
-    }
-    const int area = at.group >> 2, half = (at.group >> 1) & 1;
-    int8_t* slot =
-        at.base + (int64_t)(mixed_slot_offset(2 * I) + (odd ? kMixedDigitBytes : 0) + area * kMixedLo) * at.vstride;
-    put16(slot + at.v * kMixedLo + mixed_half_lo(v5, half) * 16, uint4{f[0], f[1], f[2], f[3]});
-    __builtin_nontemporal_store(
-        u32x2{f[4], f[5]},
-        reinterpret_cast<u32x2*>(slot + (2 * kMixedLo - area * (kMixedLo - kMixedHi)) * at.vstride +
-                                 at.v * kMixedHi + mixed_half_hi(v5, half) * 8));
+    emit_modulus<I, RM>(y, ylo, planes, plane_stride, off, nullptr);
   } else {
-    int8_t* slot = at.base + (int64_t)(mixed_slot_offset(2 * I) + (at.group >> 1) * kMixedLo) * at.vstride +
-                   at.v * kMixedLo + mixed_half_lo(v5, at.group & 1) * 16;
+    int8_t* base = planes + (int64_t)(2 * I) * plane_stride + off;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       int x[8];
 #pragma unroll
       for (int c = 0; c < 8; ++c) x[c] = centred_residue<M, RM>(y[8 * h + c], ylo[8 * h + c]);
-      put16(slot + h * at.vstride * kMixedHalfBytes,
+      put16(base + h * plane_stride,
             uint4{pack_f16(x[0], x[1]), pack_f16(x[2], x[3]), pack_f16(x[4], x[5]), pack_f16(x[6], x[7])});
     }
   }
@@ -282,8 +232,9 @@ __device__ __forceinline__ void emit_mixed(const double (&y)[kElems], const uint
 
 template <int RM, int... I>
 __device__ __forceinline__ void emit_all_mixed(std::integer_sequence<int, I...>, const double (&y)[kElems],
-                                               const uint32_t (&ylo)[kElems], const MixedAt& at) {
-  (emit_mixed<I, RM>(y, ylo, at), ...);
+                                               const uint32_t (&ylo)[kElems], int8_t* planes,
+                                               int64_t plane_stride, int64_t off) {
+  (emit_mixed<I, RM>(y, ylo, planes, plane_stride, off), ...);
 }
 
 template <int RM, int... I>
@@ -397,25 +348,24 @@ __global__ __launch_bounds__(256) void deconstruct_kernel(int64_t vecs, int64_t 
                   plane_offset(vstride, kPlanes, v, g), lut);
 }
 
-// The same for the mixed slots: no split table, 21 bytes written per element.
-// v0: the first vector's place in the layout.
+// The same for the mixed slots: no split table, 24 bytes written per element.
 template <int SIDE, int RM, bool TZ>
-__global__ __launch_bounds__(256) void deconstruct_mixed_kernel(int64_t vecs, int64_t v0, int64_t vstride,
-                                                                int64_t k, int64_t kp,
-                                                                const double* __restrict__ X, int64_t ldx,
+__global__ __launch_bounds__(256) void deconstruct_mixed_kernel(int64_t vecs, int64_t vstride, int64_t k,
+                                                                int64_t kp, const double* __restrict__ X,
+                                                                int64_t ldx,
                                                                 const int32_t* __restrict__ exps,
                                                                 bool keys_in, int t,
                                                                 int8_t* __restrict__ planes) {
   int64_t v, g;
   group_of(vecs, v, g);
-  const bool active = v < vecs && g < kp / kElems;  // the same for every group of a vector
+  const bool active = v < vecs && g < kp / kElems;
   if (!active) return;
   double x[kElems], y[kElems];
   uint32_t ylo[kElems];
   const int sigma = load_group<SIDE>(vecs, k, X, ldx, exps, keys_in, t, v, g * kElems, true, x);
   scale_round<TZ, RM>(x, sigma, y, ylo);
-  emit_all_mixed<RM>(std::make_integer_sequence<int, kR>{}, y, ylo,
-                     MixedAt{planes + (g >> 3) * kMixedBytes * vstride, vstride, v0 + v, (int)(g & 7)});
+  emit_all_mixed<RM>(std::make_integer_sequence<int, kR>{}, y, ylo, planes, vstride * 128,
+                     plane_offset(vstride, kMixedSlots, v, g));
 }
 
 // ---- all-byte set (Sec. 5.1, candidate A) on the int8 route: the centred
@@ -511,7 +461,7 @@ __global__ __launch_bounds__(256) void digits_kernel(int64_t vecs, int64_t k, in
 }
 
 struct DecArgs {
-  int64_t blocks, vecs, v0, vstride, k, kp;
+  int64_t blocks, vecs, vstride, k, kp;
   const double* X;
   int64_t ldx;
   const int32_t* exps;
@@ -524,16 +474,14 @@ template <int SIDE, int LAYOUT, int RM, bool TZ>
 void launch_one(const DecArgs& a, hipStream_t stream) {
   if constexpr (LAYOUT == kSetBytes)
     hipLaunchKernelGGL((deconstruct_bytes_kernel<SIDE, RM, TZ>), dim3((unsigned)a.blocks), dim3(256), 0,
-                       stream, a.vecs, a.vstride, a.k, a.kp, a.X, a.ldx, a.exps, a.keys_in, a.t,
-                       a.planes + a.v0 * 128);
+                       stream, a.vecs, a.vstride, a.k, a.kp, a.X, a.ldx, a.exps, a.keys_in, a.t, a.planes);
   else if constexpr (RM != 2) {  // the nearest-quotient bound of RM 2 holds for byte moduli only
     if constexpr (LAYOUT == kLayoutMixed)
       hipLaunchKernelGGL((deconstruct_mixed_kernel<SIDE, RM, TZ>), dim3((unsigned)a.blocks), dim3(256), 0,
-                         stream, a.vecs, a.v0, a.vstride, a.k, a.kp, a.X, a.ldx, a.exps, a.keys_in, a.t, a.planes);
+                         stream, a.vecs, a.vstride, a.k, a.kp, a.X, a.ldx, a.exps, a.keys_in, a.t, a.planes);
     else
       hipLaunchKernelGGL((deconstruct_kernel<SIDE, RM, TZ>), dim3((unsigned)a.blocks), dim3(256), 0, stream,
-                         a.vecs, a.vstride, a.k, a.kp, a.X, a.ldx, a.exps, a.keys_in, a.t,
-                         a.planes + a.v0 * 128);
+                         a.vecs, a.vstride, a.k, a.kp, a.X, a.ldx, a.exps, a.keys_in, a.t, a.planes);
   }
 }
 
@@ -573,17 +521,17 @@ hipError_t launch_digits(int side, int64_t vecs, int64_t k, int64_t kp, const do
   return hipGetLastError();
 }
 
-hipError_t launch_deconstruct(int layout, int quant, int side, int64_t vecs, int64_t v0, int64_t vstride,
-                              int64_t k, int64_t kp, int t, const double* X, int64_t ldx, const int32_t* exps,
+hipError_t launch_deconstruct(int layout, int quant, int side, int64_t vecs, int64_t vstride, int64_t k,
+                              int64_t kp, int t, const double* X, int64_t ldx, const int32_t* exps,
                               bool keys_in, int8_t* planes, hipStream_t stream) {
-  if (v0 < 0 || vstride < v0 + vecs || t > kMaxScaleBits) return hipErrorInvalidValue;
+  if (vstride < vecs || t > kMaxScaleBits) return hipErrorInvalidValue;
   if (vecs <= 0 || kp <= 0) return hipSuccess;
   const bool bytes = layout == kSetBytes;
   const bool tz = quant == kQuantTZ;
   // |y| <= 2^t: the nearest quotient with ylo from kMagic, then (the byte
   // moduli at t = 52) with ylo split off, else one correction
   const int mode = t <= (bytes ? 51 : 50) ? 1 : (bytes && t == 52 ? 2 : 3);
-  const DecArgs a{((vecs + 31) / 32) * (kp / 128), vecs, v0, vstride, k, kp, X, ldx, exps, keys_in, t, planes};
+  const DecArgs a{((vecs + 31) / 32) * (kp / 128), vecs, vstride, k, kp, X, ldx, exps, keys_in, t, planes};
   if (bytes) launch_layout<kSetBytes>(side, mode, tz, a, stream);
   else if (layout == kLayoutMixed) launch_layout<kLayoutMixed>(side, mode, tz, a, stream);
   else launch_layout<kSetPublished>(side, mode, tz, a, stream);

@@ -13,7 +13,7 @@ constexpr int kSetPublished = 0;  // Eq. (moduli), FP8 limb route
 constexpr int kSetBytes = 1;      // Sec. 5.1 candidate A, int8 route
 // Plane layouts, as launch_deconstruct takes them: the two sets' stored
 // planes under their own numbers, and the published set's mixed slots
-// (moduli.hpp), which stay inside ozaki25_dgemm*.
+// (kMixedSlots in moduli.hpp), which stay inside ozaki25_dgemm*.
 constexpr int kLayoutMixed = 2;
 // Quantisers, as numbered by ozaki25_quantiser.
 constexpr int kQuantRN = 0;  // round to nearest, ties to even
@@ -47,11 +47,12 @@ constexpr int kMaxScaleBits = 58;
 // (sigma, or with keys_in the column scan's exponent keys, turned into sigma
 // on load) and the scale bits t: e4m3 limb planes (published set), int8
 // residue planes (all-byte set) or the published set's mixed slots.  vecs
-// vectors of X, written as vectors v0 .. of a plane layout of vstride >=
-// v0 + vecs vectors, so that a run of vectors can fill its part of a larger
-// operand's planes.
-hipError_t launch_deconstruct(int layout, int quant, int side, int64_t vecs, int64_t v0, int64_t vstride,
-                              int64_t k, int64_t kp, int t, const double* X, int64_t ldx, const int32_t* exps,
+// vectors of X, written into a plane
+// layout of vstride >= vecs vectors (planes points at the first one's
+// bytes), so that a run of vectors can fill its part of a larger operand's
+// planes.
+hipError_t launch_deconstruct(int layout, int quant, int side, int64_t vecs, int64_t vstride, int64_t k,
+                              int64_t kp, int t, const double* X, int64_t ldx, const int32_t* exps,
                               bool keys_in, int8_t* planes, hipStream_t stream);
 
 // Eq. (residueprod): r centred per-modulus products [r][m][n], on FP8 MFMA

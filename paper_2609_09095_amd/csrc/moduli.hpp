@@ -77,33 +77,12 @@ constexpr int compact_scale(int i) { return root_of(i) ? 1 : 16; }
 
 static_assert(plane_base(kR) == kPlanes, "30 stored planes for the published set");
 
-// The layout that ozaki25_dgemm* uses between its own stages: two slots per
-// modulus and 128-wide k block, [k_pad/128][24 slots][vectors].
-//  - Squares (slots 2 i, 2 i + 1): the digit planes d0 and d1 as FP6 E2M3 (d / 8),
-//    96 bytes per vector in four areas, [2][vectors][32] then [2][vectors][16]:
-//    fragment f of four (32 k, 24 bytes) has its first 16 bytes in area f / 2
-//    and its last 8 in area 2 + f / 2, at half f % 2 of the vector's row.
-//  - Nonsquares: the centred residue as fp16, 128 bytes per vector and slot
-//    in four areas [4][vectors][32]: slot 2 i holds the first eight and slot
-//    2 i + 1 the last eight of every sixteen k; the c-th sixteen are 16 bytes in
-//    area c / 2, at half c % 2.
-// The two halves of a row swap places so that the matrix kernel's LDS reads,
-// which take the same half of 16 (16-byte halves) or 32 (8-byte halves)
-// consecutive vectors at a time, fall on distinct banks.
+// The layout that ozaki25_dgemm* uses between its own stages: two 128-byte
+// slots per modulus and k block, [k_pad/128][24][vectors][128].  Squares keep
+// their two limb planes; a nonsquare holds its centred residue as fp16, slot
+// 0 the first eight and slot 1 the last eight of every sixteen k.
 constexpr int kMixedSlots = 2 * kR;
-constexpr int kMixedDigitSlots = 12;  // the squares'
-constexpr int kMixedLo = 32, kMixedHi = 16;  // bytes of an area's row
-constexpr int kMixedDigitBytes = 2 * (kMixedLo + kMixedHi), kMixedHalfBytes = 4 * kMixedLo;
-constexpr bool mixed_half(int i) { return 2 * i >= kMixedDigitSlots; }
-// bytes before slot q per vector and k block, and of a whole k block
-constexpr int mixed_slot_offset(int q) {
-  return q < kMixedDigitSlots
-             ? q * kMixedDigitBytes
-             : kMixedDigitSlots * kMixedDigitBytes + (q - kMixedDigitSlots) * kMixedHalfBytes;
-}
-constexpr int kMixedBytes = mixed_slot_offset(kMixedSlots);
-constexpr int mixed_half_lo(int v, int h) { return h ^ ((v >> 3) & 1); }
-constexpr int mixed_half_hi(int v, int h) { return h ^ ((v >> 4) & 1); }
+constexpr bool mixed_half(int i) { return i >= 6; }
 
 // ---- all-byte set (Sec. 5.1, candidate A): 256 first, then fourteen odd
 // moduli; log2 of the product 117.8

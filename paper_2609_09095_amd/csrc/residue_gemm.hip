@@ -331,6 +331,94 @@ static_assert((int64_t)(kModulus[0] / 2 + kModulus[0] / 50 + 1) * (kModulus[0] -
               "carry bound");
 static_assert(kModulus[0] >= kModulus[kR - 1] && kModulus[0] >= kModulus[1], "largest modulus first");
 
+// ---- mixed operands: fp16 residues for the nonsquare moduli ---------------
+// Inside ozaki25_dgemm* the published set's planes take kMixedSlots slots
+// instead of the stage API's 30 limb planes: a square keeps its two base-s
+// digit planes (three FP8 products, as above), a nonsquare (m <= 511) holds
+// its centred residue itself, |x| <= 255, as fp16 in two slots of 64 k each
+// (the k order within the pair is the deconstruction's, the same for A and
+// B).  Its product is ONE fp16 MFMA product: at half the FP8 rate that is two
+// FP8 products' matrix time and operand bytes in place of three, 30 instead
+// of 36 over the set, and 24 plane bytes per element instead of 30.
+// Per k the fp16 products reach 255^2, so an accumulator holds at most
+// kWindow = 4 stages (256 k) between reductions to stay an exact integer
+// below 2^24; the four 32 x 32 blocks of a wavefront take turns, one reduced
+// per stage, so that its 48 VALU instructions run under the other blocks'
+// MFMAs (all four together would hold every wavefront's MFMAs up).
+constexpr int kWindow = 4;
+constexpr int kHalfK = BK / 2;  // k per fp16 stage
+static_assert((int64_t)kWindow * kHalfK * 255 * 255 + 261 < (1LL << 24), "fp16 sums exact between reductions");
+constexpr bool mixed_moduli_fit() {
+  for (int i = 0; i < kR; ++i)
+    if (mixed_half(i) ? kModulus[i] > 511 : (!root_of(i) || plane_base(i) != 2 * i)) return false;
+  return true;
+}
+static_assert(mixed_moduli_fit(), "fp16 moduli below 512; the squares' slots are their limb planes");
+
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+
+// fp16 fragment of one 32-row block for one 16-k step: lane half fh takes
+// 16-byte chunk 2 ks + fh of its row
+__device__ __forceinline__ v8h frag_f16(const int8_t* base, int r, int ks, int fh) {
+  return *reinterpret_cast<const v8h*>(base + r * BK + (((2 * ks + fh) ^ swz(r)) << 4));
+}
+
+// One stage: four 16-k steps of 2 x 2 MFMAs; block RED (row block RED / 2,
+// column block RED % 2) is reduced mod m first, under the other blocks'
+// MFMAs of step 0.
+template <int S, int RED>
+__device__ __forceinline__ void stage_mma_dma_f16(const int8_t* la, const int8_t* lb, int ra0, int rb0,
+                                                  int fh, v16f (&acc)[2][2], float fm, float finv,
+                                                  __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb,
+                                                  int8_t* na, int8_t* nb, const int* voffa,
+                                                  const int* voffb, int wave) {
+  constexpr int ND = Tile<S>::DMA;
+  static_assert(Tile<S>::BB == 2, "2 x 2 blocks per wavefront");
+  v8h af[4][2], bf[4][2];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x) af[ks][x] = frag_f16(la, ra0 + 32 * x, ks, fh);
+#pragma unroll
+    for (int x = 0; x < 2; ++x) bf[ks][x] = frag_f16(lb, rb0 + 32 * x, ks, fh);
+  }
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int q = (RED + 1 + i) & 3, a = q >> 1, b = q & 1;  // block RED last
+      const int j = ks * 4 + i;                               // MFMA number in issue order
+      if (j < ND) stage_dma<S>(j, ra, rb, na, nb, voffa, voffb, wave);
+      if (ks == 0 && i == 3) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[a][b][v] = reduce_f(acc[a][b][v], fm, finv);
+      }
+      acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[ks][a], bf[ks][b], acc[a][b], 0, 0, 0);
+    }
+  // step 0: its fragments, then per MFMA one fragment of step 1, one DMA load
+  // and a third of the reduction; the later steps' fragments among the MFMAs
+  __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
+  }
+#pragma unroll
+  for (int i = 3; i < ND; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < 12 - ND; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+}
+
 // Output stores through a global (not generic) pointer; NT marks them
 // streaming (measured: the FP8 kernel gains with it, the int8 one without).
 template <bool NT, typename OT>
@@ -389,7 +477,7 @@ __device__ __forceinline__ void store_tile(OT* out, int nn, int rows_left, int c
 // splits > 1 (split-k): consecutive blocks take the same tile's stage ranges,
 // and block (tile, split) writes its centred partial product to the split's
 // own [r][m][n] slice of cres; reduce_splits_kernel sums them mod m.
-template <typename OT, int S>
+template <typename OT, int S, bool MIXED>
 __global__ __launch_bounds__(1024, 1) void residue_gemm_kernel(int64_t m, int64_t n, int64_t kp,
                                                               const int8_t* __restrict__ pa,
                                                               const int8_t* __restrict__ pb,
@@ -397,6 +485,8 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_kernel(int64_t m, int64_
                                                               int group) {
   // two LDS stages, each an A tile (BM rows x 128 bytes) and a B tile
   constexpr int BM = Tile<S>::BM, BN = Tile<S>::BN, NB = Tile<S>::BB, WC = Tile<S>::WC;
+  constexpr int NPL = MIXED ? kMixedSlots : kPlanes;  // planes (or slots) in the layout
+  static_assert(!MIXED || sizeof(OT) == 2, "mixed operands: the compact int16 output");
   __shared__ __attribute__((aligned(1024))) int8_t lds_a0[BM * BK];
   __shared__ __attribute__((aligned(1024))) int8_t lds_b0[BN * BK];
   __shared__ __attribute__((aligned(1024))) int8_t lds_a1[BM * BK];
@@ -456,12 +546,12 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_kernel(int64_t m, int64_
   // plane layout and jumping to the next product's first stage at a product
   // boundary (it stays on the last stage, whose look-ahead load repeats
   // it); the carry cursor (cp, cs) follows the stage just computed.
-  const int64_t step_a = (int64_t)kPlanes * m * BK, step_b = (int64_t)kPlanes * n * BK;
+  const int64_t step_a = (int64_t)NPL * m * BK, step_b = (int64_t)NPL * n * BK;
   auto first_a = [&](int p) {
-    return pa + (((int64_t)sbeg * kPlanes + kSched[mod].plane_a[p]) * m + tm * BM) * BK;
+    return pa + (((int64_t)sbeg * NPL + kSched[mod].plane_a[p]) * m + tm * BM) * BK;
   };
   auto first_b = [&](int p) {
-    return pb + (((int64_t)sbeg * kPlanes + kSched[mod].plane_b[p]) * n + tn * BN) * BK;
+    return pb + (((int64_t)sbeg * NPL + kSched[mod].plane_b[p]) * n + tn * BN) * BK;
   };
   int lp = 0, ls = 0, cp = 0, cs = 0;
   const int8_t* la = first_a(0);
@@ -489,22 +579,68 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_kernel(int64_t m, int64_
       ++cp;
     }
   };
-  if (total > 0) stage_load<S>(rsrc(la, na), rsrc(lb, nb), lds_a0, lds_b0, voffa, voffb, wave);
-  advance();
-  for (int G = 0; G < total; G += 2) {
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    stage_mma_dma<S>(lds_a0, lds_b0, ra0, rb0, fh, acc, rsrc(la, na), rsrc(lb, nb), lds_a1, lds_b1,
-                      voffa, voffb, wave);
+  if (MIXED && mixed_half(mod)) {
+    // fp16 modulus: 2 nstage stages of 64 k, slots 2 mod and 2 mod + 1 of
+    // each k block in turn; the look-ahead stays on the last stage
+    const int8_t* ha = pa + (((int64_t)sbeg * NPL + 2 * mod) * m + tm * BM) * BK;
+    const int8_t* hb = pb + (((int64_t)sbeg * NPL + 2 * mod) * n + tn * BN) * BK;
+    const int64_t odd_a = m * BK, odd_b = n * BK;
+    const int halves = 2 * nstage;
+    int lj = 0;
+    auto next = [&]() {
+      if (lj + 1 < halves) {
+        ha += (lj & 1) ? step_a - odd_a : odd_a;
+        hb += (lj & 1) ? step_b - odd_b : odd_b;
+        ++lj;
+      }
+    };
+    auto stage = [&]<int RED>(std::integral_constant<int, RED>, const int8_t* a, const int8_t* b, int8_t* an,
+                              int8_t* bn) __attribute__((always_inline)) {
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      stage_mma_dma_f16<S, RED>(a, b, ra0, rb0, fh, acc, fm, finv, rsrc(ha, na), rsrc(hb, nb), an, bn,
+                                 voffa, voffb, wave);
+      __builtin_amdgcn_sched_barrier(0);
+      next();
+    };
+    stage_load<S>(rsrc(ha, na), rsrc(hb, nb), lds_a0, lds_b0, voffa, voffb, wave);
+    next();
+    // an odd k block first, so that the loop needs no exit half way (its
+    // join costs registers)
+    if (halves & 2) {
+      stage(std::integral_constant<int, 2>{}, lds_a0, lds_b0, lds_a1, lds_b1);
+      stage(std::integral_constant<int, 3>{}, lds_a1, lds_b1, lds_a0, lds_b0);
+    }
+    for (int G = halves & 2; G < halves; G += 4) {
+      stage(std::integral_constant<int, 0>{}, lds_a0, lds_b0, lds_a1, lds_b1);
+      stage(std::integral_constant<int, 1>{}, lds_a1, lds_b1, lds_a0, lds_b0);
+      stage(std::integral_constant<int, 2>{}, lds_a0, lds_b0, lds_a1, lds_b1);
+      stage(std::integral_constant<int, 3>{}, lds_a1, lds_b1, lds_a0, lds_b0);
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[a][b][v] = reduce_f(acc[a][b][v], fm, finv);
+  } else {
+    if (total > 0) stage_load<S>(rsrc(la, na), rsrc(lb, nb), lds_a0, lds_b0, voffa, voffb, wave);
     advance();
-    carry_step();
-    if (G + 1 >= total) break;
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    stage_mma_dma<S>(lds_a1, lds_b1, ra0, rb0, fh, acc, rsrc(la, na), rsrc(lb, nb), lds_a0, lds_b0,
-                      voffa, voffb, wave);
-    advance();
-    carry_step();
+    for (int G = 0; G < total; G += 2) {
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      stage_mma_dma<S>(lds_a0, lds_b0, ra0, rb0, fh, acc, rsrc(la, na), rsrc(lb, nb), lds_a1, lds_b1,
+                        voffa, voffb, wave);
+      advance();
+      carry_step();
+      if (G + 1 >= total) break;
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      stage_mma_dma<S>(lds_a1, lds_b1, ra0, rb0, fh, acc, rsrc(la, na), rsrc(lb, nb), lds_a0, lds_b0,
+                        voffa, voffb, wave);
+      advance();
+      carry_step();
+    }
   }
   __builtin_amdgcn_s_waitcnt(0);  // the repeated look-ahead load lands before the epilogue
 
@@ -538,11 +674,12 @@ __device__ __forceinline__ int lane_id_now() {
 // The next tile's first barrier waits for every load and store (loads and
 // stores share one counter, and their relative completion order is not
 // relied on).  Only the compact int16 output takes this form.
-template <typename OT, int S>
+template <typename OT, int S, bool MIXED>
 __global__ __launch_bounds__(1024, 1) void residue_gemm_persistent_kernel(
     int64_t m, int64_t n, int64_t kp, const int8_t* __restrict__ pa, const int8_t* __restrict__ pb,
     OT* __restrict__ cres, int group, uint32_t nvirt) {
   constexpr int BM = Tile<S>::BM, BN = Tile<S>::BN, NB = Tile<S>::BB, WC = Tile<S>::WC;
+  constexpr int NPL = MIXED ? kMixedSlots : kPlanes;
   static_assert(sizeof(OT) == 2, "the compact int16 residue output");
   __shared__ __attribute__((aligned(1024))) int8_t lds_a0[BM * BK];
   __shared__ __attribute__((aligned(1024))) int8_t lds_b0[BN * BK];
@@ -561,7 +698,7 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_persistent_kernel(
   const int nstage = (int)(kp / BK);
   const int nseg = (nstage + kSeg - 1) / kSeg;
   const int total = 3 * nstage;  // even (the host checks)
-  const int64_t step_a = (int64_t)kPlanes * m * BK, step_b = (int64_t)kPlanes * n * BK;
+  const int64_t step_a = (int64_t)NPL * m * BK, step_b = (int64_t)NPL * n * BK;
   auto rsrc = [](const int8_t* p, int nrec) __attribute__((always_inline)) {
     return __builtin_amdgcn_make_buffer_rsrc((void*)uniform_ptr(p), (short)0, nrec, 0x00020000);
   };
@@ -582,10 +719,12 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_persistent_kernel(
     return t;
   };
   auto first_a = [&](const TileAt& t, int p) __attribute__((always_inline)) {
-    return pa + ((int64_t)kSched[t.mod].plane_a[p] * m + t.tm * BM) * BK;
+    const int q = MIXED && mixed_half(t.mod) ? 2 * t.mod : kSched[t.mod].plane_a[p];
+    return pa + ((int64_t)q * m + t.tm * BM) * BK;
   };
   auto first_b = [&](const TileAt& t, int p) __attribute__((always_inline)) {
-    return pb + ((int64_t)kSched[t.mod].plane_b[p] * n + t.tn * BN) * BK;
+    const int q = MIXED && mixed_half(t.mod) ? 2 * t.mod : kSched[t.mod].plane_b[p];
+    return pb + ((int64_t)q * n + t.tn * BN) * BK;
   };
 
   uint32_t v = blockIdx.x;
@@ -597,13 +736,19 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_persistent_kernel(
   int lp = 0, ls = 0, lna = cur.na, lnb = cur.nb;
   const int8_t* la = first_a(cur, 0);
   const int8_t* lb = first_b(cur, 0);
+  // an fp16 tile's stages: the two slots of each k block in turn, lp the slot
   auto advance = [&]() __attribute__((always_inline)) {
     if (ahead) return;
-    if (ls + 1 < nstage) {
+    if (MIXED && mixed_half(cur.mod) && (lp == 0 || ls + 1 < nstage)) {
+      la += lp ? step_a - m * BK : m * BK;
+      lb += lp ? step_b - n * BK : n * BK;
+      ls += lp;
+      lp ^= 1;
+    } else if (!(MIXED && mixed_half(cur.mod)) && ls + 1 < nstage) {
       ++ls;
       la += step_a;
       lb += step_b;
-    } else if (lp < 2) {
+    } else if (!(MIXED && mixed_half(cur.mod)) && lp < 2) {
       ++lp;
       ls = 0;
       la = first_a(cur, lp);
@@ -639,19 +784,36 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_persistent_kernel(
         ++cp;
       }
     };
-    for (int G = 0; G < total; G += 2) {
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      stage_mma_dma<S>(lds_a0, lds_b0, ra0, rb0, fh, acc, rsrc(la, lna), rsrc(lb, lnb), lds_a1, lds_b1,
-                        voffa, voffb, wave);
-      advance();
-      carry_step();
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      stage_mma_dma<S>(lds_a1, lds_b1, ra0, rb0, fh, acc, rsrc(la, lna), rsrc(lb, lnb), lds_a0, lds_b0,
-                        voffa, voffb, wave);
-      advance();
-      carry_step();
+    if (MIXED && mixed_half(cur.mod)) {
+      auto stage = [&]<int RED>(std::integral_constant<int, RED>, const int8_t* a, const int8_t* b, int8_t* an,
+                                int8_t* bn) __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        stage_mma_dma_f16<S, RED>(a, b, ra0, rb0, fh, acc, fm, finv, rsrc(la, lna), rsrc(lb, lnb), an, bn,
+                                   voffa, voffb, wave);
+        advance();
+      };
+      for (int G = 0; G < 2 * nstage; G += 4) {  // nstage is even
+        stage(std::integral_constant<int, 0>{}, lds_a0, lds_b0, lds_a1, lds_b1);
+        stage(std::integral_constant<int, 1>{}, lds_a1, lds_b1, lds_a0, lds_b0);
+        stage(std::integral_constant<int, 2>{}, lds_a0, lds_b0, lds_a1, lds_b1);
+        stage(std::integral_constant<int, 3>{}, lds_a1, lds_b1, lds_a0, lds_b0);
+      }
+    } else {
+      for (int G = 0; G < total; G += 2) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        stage_mma_dma<S>(lds_a0, lds_b0, ra0, rb0, fh, acc, rsrc(la, lna), rsrc(lb, lnb), lds_a1, lds_b1,
+                          voffa, voffb, wave);
+        advance();
+        carry_step();
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        stage_mma_dma<S>(lds_a1, lds_b1, ra0, rb0, fh, acc, rsrc(la, lna), rsrc(lb, lnb), lds_a0, lds_b0,
+                          voffa, voffb, wave);
+        advance();
+        carry_step();
+      }
     }
     OT* out = (OT*)uniform_ptr((const int8_t*)(cres + (int64_t)cur.mod * m * n + cur.tm * BM * n +
                                                cur.tn * BN));
@@ -666,513 +828,6 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_persistent_kernel(
     cur = nxt;
     lp = 0;
     ls = 0;
-    ahead = false;
-  }
-  __builtin_amdgcn_s_waitcnt(0);  // the last look-ahead (a repeat) lands before the block ends
-}
-
-// ---- mixed slots: FP6 digits and fp16 residues (inside ozaki25_dgemm*) -----
-// Between the stages of one ozaki25_dgemm* call the published set's planes
-// are kMixedSlots slots (moduli.hpp) instead of the 30 limb planes:
-//  - a square m = s^2 keeps its balanced base-s digits (d0, d1), |d| <= 16, as
-//    FP6 (E2M3): d / 8 is exact there (subnormals and the first binade step by
-//    1/8, and 16 / 8 = 2), and the FP6 product runs at twice the FP8 rate on
-//    three quarters of the bytes.  The same three products through one
-//    accumulator as above, in units of 1/64 (m / 64 in place of m in every
-//    reduction; scaling by a power of two changes no rounding).
-//  - a nonsquare m <= 511 holds its centred residue, |x| <= 255, as fp16: ONE
-//    fp16 product, at half the FP8 rate two FP8 products' time and operand
-//    bytes in place of three.  Per k it reaches 255^2, so an accumulator holds
-//    at most kWindow = 4 stages of 64 k between reductions to stay an exact
-//    integer below 2^24; the four 32 x 32 blocks of a wavefront take turns,
-//    one reduced per stage, so that its 48 VALU instructions run under the
-//    other blocks' MFMAs.
-// The slots hold each 256-row tile's bytes in the order LDS wants them (the
-// bank swizzle is applied by the deconstruction), so every LDS-DMA load is a
-// linear copy, and the K step is an immediate offset from a lane's one address.
-constexpr int kWindow = 4;
-constexpr int kHalfK = BK / 2;  // k per fp16 stage
-static_assert((int64_t)kWindow * kHalfK * 255 * 255 + 261 < (1LL << 24), "fp16 sums exact between reductions");
-constexpr bool mixed_moduli_fit() {
-  for (int i = 0; i < kR; ++i)
-    if (mixed_half(i) ? kModulus[i] > 511 : (!root_of(i) || root_of(i) > 33 || plane_base(i) != 2 * i))
-      return false;
-  return true;
-}
-static_assert(mixed_moduli_fit(), "fp16 moduli below 512; squares of at most 33 in slots 2 i, 2 i + 1");
-
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-
-constexpr int MT = 256;                // output rows and columns per block
-constexpr int kBuf = 2 * MT * BK;      // bytes of an LDS stage buffer
-// In it an fp16 stage: A's four areas (one per 16-k step), then B's; an FP6
-// stage: the 32-byte areas (one per 64-k step) of A, of B, then the 16-byte
-// areas of A, of B.
-constexpr int kLo = MT * kMixedLo, kHi = MT * kMixedHi;  // an area's bytes of a tile
-constexpr int kB16 = 4 * kLo, kB6 = 2 * kLo, kAh6 = 4 * kLo, kBh6 = 4 * kLo + 2 * kHi;
-static_assert(2 * kB16 == kBuf && kBh6 + 2 * kHi <= kBuf, "both stages fit the buffer");
-static_assert(kLo == 8 * 1024 && kHi == 4 * 1024, "the wavefronts' shares of the loads below");
-
-// One tile's operands: its rows of A and columns of B (those past the matrix
-// edge fall outside the buffer range and read as zero).
-struct MixedTile {
-  int mod;
-  int64_t tm, tn;
-  int ra, rb;
-};
-
-__device__ __forceinline__ MixedTile mixed_tile(uint32_t id, int64_t m, int64_t n, uint32_t group) {
-  MixedTile t;
-  block_coords(id, (uint32_t)((m + MT - 1) / MT), (uint32_t)((n + MT - 1) / MT), group, t.mod, t.tm, t.tn);
-  t.ra = __builtin_amdgcn_readfirstlane((int)(m - t.tm * MT < MT ? m - t.tm * MT : MT));
-  t.rb = __builtin_amdgcn_readfirstlane((int)(n - t.tn * MT < MT ? n - t.tn * MT : MT));
-  return t;
-}
-
-// the first area of slot q of k block kb of an operand of `rows` vectors, at
-// the tile's first row
-__device__ __forceinline__ const int8_t* mixed_piece(const int8_t* p, int64_t kb, int q, int64_t rows,
-                                                     int64_t tile) {
-  return p + (kb * kMixedBytes + mixed_slot_offset(q)) * rows + tile * kLo;
-}
-
-// A stage's loads are linear copies of 1 KiB.  d-th load of an fp16 stage
-// (0, 1: A; 2, 3: B): areas 2 (d & 1) and 2 (d & 1) + 1, eight wavefronts
-// each.  FP6 (0: A, 1: B): areas 0 and 1, eight wavefronts each; 2: the
-// 16-byte areas of A and B, four wavefronts each.  vlo: (wave & 7) * 1024 +
-// lane * 16.
-__device__ __forceinline__ void load_areas(const int8_t* p, int64_t rows, int tile_rows, int area, int8_t* dst,
-                                           int vlo, int wave) {
-  const int8_t* src = uniform_ptr(p + (area + (wave >> 3)) * kMixedLo * rows);
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(
-      __builtin_amdgcn_make_buffer_rsrc((void*)src, (short)0, tile_rows * kMixedLo, 0x00020000),
-      (lds_ptr)(dst + area * kLo + wave * 1024), 16, vlo, 0, 0, 0);
-}
-__device__ __forceinline__ void dma16(int d, const int8_t* a, const int8_t* b, const MixedTile& t, int64_t m,
-                                      int64_t n, int8_t* buf, int vlo, int wave) {
-  if (d < 2)
-    load_areas(a, m, t.ra, 2 * (d & 1), buf, vlo, wave);
-  else
-    load_areas(b, n, t.rb, 2 * (d & 1), buf + kB16, vlo, wave);
-}
-__device__ __forceinline__ void dma6(int d, const int8_t* a, const int8_t* b, const MixedTile& t, int64_t m,
-                                     int64_t n, int8_t* buf, int vlo, int wave) {
-  if (d == 0) {
-    load_areas(a, m, t.ra, 0, buf, vlo, wave);
-  } else if (d == 1) {
-    load_areas(b, n, t.rb, 0, buf + kB6, vlo, wave);
-  } else {
-    const bool of_a = wave < 8;
-    const int64_t rows = of_a ? m : n;
-    const int8_t* src = (of_a ? a - t.tm * (kLo - kHi) : b - t.tn * (kLo - kHi)) +
-                        (2 * kMixedLo + ((wave >> 2) & 1) * kMixedHi) * rows;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        __builtin_amdgcn_make_buffer_rsrc((void*)uniform_ptr(src), (short)0, (of_a ? t.ra : t.rb) * kMixedHi,
-                                          0x00020000),
-        (lds_ptr)(buf + kAh6 + wave * 1024), 16, vlo & (kHi - 1), 0, 0, 0);
-  }
-}
-
-// FP6 fragment of row r for the 64-k step ks: lane half fh takes one of the
-// step's two runs of 32 k, 24 bytes, the same on both operands.  hi: the byte
-// offset of its last 8, from tail6.
-__device__ __forceinline__ v8i frag6(const int8_t* lo, const int8_t* buf, int hi, int r, int ks, int fh) {
-  const v4i l = *reinterpret_cast<const v4i*>(lo + ks * kLo + r * kMixedLo + mixed_half_lo(r, fh) * 16);
-  const v2i h = *reinterpret_cast<const v2i*>(buf + hi);
-  const v4i h4 = __builtin_shufflevector(h, h, 0, 1, -1, -1);
-  return __builtin_shufflevector(l, h4, 0, 1, 2, 3, 4, 5, -1, -1);
-}
-// Each 8-byte read gets an address of its own: merged into two-address reads
-// their results would need moves into the fragments' registers.
-__device__ __forceinline__ int tail6(int area, int r, int ks, int fh) {
-  int at = area + ks * kHi + r * kMixedHi + mixed_half_hi(r, fh) * 8;
-  asm volatile("" : "+v"(at));
-  return at;
-}
-// fp16 fragment of row r for the 16-k step ks: lane half fh takes 8 of its k
-__device__ __forceinline__ v8h frag16(const int8_t* base, int r, int ks, int fh) {
-  return *reinterpret_cast<const v8h*>(base + ks * kLo + r * kMixedLo + mixed_half_lo(r, fh) * 16);
-}
-
-// One FP6 stage (128 k): two 64-k steps of 2 x 2 MFMAs; the next stage's DMA
-// loads go among the first MFMAs.
-__device__ __forceinline__ void stage6(const int8_t* buf, int ra0, int rb0, int fh, v16f (&acc)[2][2],
-                                       const int8_t* a, const int8_t* b, const MixedTile& t, int64_t m,
-                                       int64_t n, int8_t* next, int vlo, int wave) {
-  v8i af[2][2], bf[2][2];
-  int ta[2][2], tb[2][2];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-    for (int x = 0; x < 2; ++x) {
-      ta[ks][x] = tail6(kAh6, ra0 + 32 * x, ks, fh);
-      tb[ks][x] = tail6(kBh6, rb0 + 32 * x, ks, fh);
-    }
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-#pragma unroll
-    for (int x = 0; x < 2; ++x) af[ks][x] = frag6(buf, buf, ta[ks][x], ra0 + 32 * x, ks, fh);
-#pragma unroll
-    for (int x = 0; x < 2; ++x) bf[ks][x] = frag6(buf + kB6, buf, tb[ks][x], rb0 + 32 * x, ks, fh);
-  }
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int ks = j >> 2, x = (j >> 1) & 1, y = j & 1;
-    if (j < 3) dma6(j, a, b, t, m, n, next, vlo, wave);
-    // formats 2, 2: FP6 E2M3 on both sides
-    acc[x][y] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[ks][x], bf[ks][y], acc[x][y], 2, 2, 0, 0, 0,
-                                                                0);
-  }
-  __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-  }
-  __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-  __builtin_amdgcn_sched_group_barrier(0x008, 5, 0);
-}
-
-// One fp16 stage (64 k): four 16-k steps of 2 x 2 MFMAs; block RED (row block
-// RED / 2, column block RED % 2) is reduced mod m first, under the other
-// blocks' MFMAs of step 0.
-template <int RED>
-__device__ __forceinline__ void stage16(const int8_t* buf, int ra0, int rb0, int fh, v16f (&acc)[2][2],
-                                        float fm, float finv, const int8_t* a, const int8_t* b,
-                                        const MixedTile& t, int64_t m, int64_t n, int8_t* next, int vlo,
-                                        int wave) {
-  v8h af[4][2], bf[4][2];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-#pragma unroll
-    for (int x = 0; x < 2; ++x) af[ks][x] = frag16(buf, ra0 + 32 * x, ks, fh);
-#pragma unroll
-    for (int x = 0; x < 2; ++x) bf[ks][x] = frag16(buf + kB16, rb0 + 32 * x, ks, fh);
-  }
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int q = (RED + 1 + i) & 3, x = q >> 1, y = q & 1;  // block RED last
-      const int j = ks * 4 + i;                               // MFMA number in issue order
-      if (j < 4) dma16(j, a, b, t, m, n, next, vlo, wave);
-      if (ks == 0 && i == 3) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[x][y][v] = reduce_f(acc[x][y][v], fm, finv);
-      }
-      acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[ks][x], bf[ks][y], acc[x][y], 0, 0, 0);
-    }
-  // step 0: its fragments, then per MFMA one fragment of step 1, one DMA load
-  // and a third of the reduction; the later steps' fragments among the MFMAs
-  __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
-  }
-  __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-  __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-  __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-  }
-  __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-}
-
-// The four reduction turns in order, as compile-time values for stage16.
-template <int R>
-using Turn = std::integral_constant<int, R>;
-
-// One tile per block; splits as residue_gemm_kernel.  The outputs are the
-// residues reduced to |c| <= 0.51 m, int16.
-__global__ __launch_bounds__(1024, 1) void mixed_gemm_kernel(int64_t m, int64_t n, int64_t kp,
-                                                            const int8_t* __restrict__ pa,
-                                                            const int8_t* __restrict__ pb,
-                                                            int16_t* __restrict__ cres, int splits, int group) {
-  // two stage buffers, each its own object: the compiler then tells the one
-  // the DMA fills from the one being read
-  __shared__ __attribute__((aligned(1024))) int8_t lds0[kBuf];
-  __shared__ __attribute__((aligned(1024))) int8_t lds1[kBuf];
-  const int split = (int)(blockIdx.x % (unsigned)splits);
-  const MixedTile t = mixed_tile(blockIdx.x / (unsigned)splits, m, n, (uint32_t)group);
-  const bool half = mixed_half(t.mod);
-  cres += (int64_t)split * kR * m * n;
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wr = wave >> 2, wc = wave & 3;   // 4 x 4 wavefronts of 64 x 64
-  const int fr = lane & 31, fh = lane >> 5;  // fragment row, k half
-  const int ra0 = wr * 64 + fr, rb0 = wc * 64 + fr;
-  const int vlo = (wave & 7) * 1024 + lane * 16;
-
-  v16f acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = v16f{};
-
-  // this block's k blocks [sbeg, sbeg + nstage), at least one
-  const int nstage_all = (int)(kp / BK);
-  const int sbeg = (int)((uint32_t)nstage_all * (uint32_t)split / (uint32_t)splits);
-  const int nstage = (int)((uint32_t)nstage_all * (uint32_t)(split + 1) / (uint32_t)splits) - sbeg;
-  const int64_t step_a = (int64_t)kMixedBytes * m, step_b = (int64_t)kMixedBytes * n;
-  const ModSched sc = kSched[t.mod];
-  // FP6 sums are in units of 1/64
-  const float unit = half ? 1.0f : 64.0f;
-  const float fm = (float)sc.m / unit, finv = sc.inv * unit;
-
-  if (half) {
-    // slots 2 mod and 2 mod + 1 of each k block in turn; the look-ahead stays
-    // on the last stage
-    const int8_t* la = mixed_piece(pa, sbeg, 2 * t.mod, m, t.tm);
-    const int8_t* lb = mixed_piece(pb, sbeg, 2 * t.mod, n, t.tn);
-    const int64_t odd_a = m * BK, odd_b = n * BK;
-    const int halves = 2 * nstage;
-    int lj = 0;
-    auto advance = [&]() {
-      if (lj + 1 < halves) {
-        la += (lj & 1) ? step_a - odd_a : odd_a;
-        lb += (lj & 1) ? step_b - odd_b : odd_b;
-        ++lj;
-      }
-    };
-    auto stage = [&]<int R>(Turn<R>, const int8_t* buf, int8_t* next) __attribute__((always_inline)) {
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      stage16<R>(buf, ra0, rb0, fh, acc, fm, finv, la, lb, t, m, n, next, vlo, wave);
-      __builtin_amdgcn_sched_barrier(0);
-      advance();
-    };
-#pragma unroll
-    for (int d = 0; d < 4; ++d) dma16(d, la, lb, t, m, n, lds0, vlo, wave);
-    advance();
-    // an odd k block first, so that the loop needs no exit half way (its join
-    // costs registers)
-    if (halves & 2) {
-      stage(Turn<2>{}, lds0, lds1);
-      stage(Turn<3>{}, lds1, lds0);
-    }
-    for (int G = halves & 2; G < halves; G += 4) {
-      stage(Turn<0>{}, lds0, lds1);
-      stage(Turn<1>{}, lds1, lds0);
-      stage(Turn<2>{}, lds0, lds1);
-      stage(Turn<3>{}, lds1, lds0);
-    }
-  } else {
-    // the three products as one pipeline over 3 nstage stages, as in
-    // residue_gemm_kernel
-    const int nseg = (nstage + kSeg - 1) / kSeg;
-    const int total = 3 * nstage;
-    int lp = 0, ls = 0, cp = 0, cs = 0;
-    const int8_t* la = mixed_piece(pa, sbeg, sc.plane_a[0], m, t.tm);
-    const int8_t* lb = mixed_piece(pb, sbeg, sc.plane_b[0], n, t.tn);
-    auto advance = [&]() {
-      if (ls + 1 < nstage) {
-        ++ls;
-        la += step_a;
-        lb += step_b;
-      } else if (lp < 2) {
-        ++lp;
-        ls = 0;
-        la = mixed_piece(pa, sbeg, kSched[t.mod].plane_a[lp], m, t.tm);
-        lb = mixed_piece(pb, sbeg, kSched[t.mod].plane_b[lp], n, t.tn);
-      }
-    };
-    auto carry_step = [&]() {
-      // the tile's last carry is the epilogue's reduction
-      if (cp < 2 || cs + 1 < nstage) carry<2, false>(acc, cp, cs, nstage, nseg, t.mod, fm, finv);
-      if (++cs == nstage) {
-        cs = 0;
-        ++cp;
-      }
-    };
-#pragma unroll
-    for (int d = 0; d < 3; ++d) dma6(d, la, lb, t, m, n, lds0, vlo, wave);
-    advance();
-    for (int G = 0; G < total; G += 2) {
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      stage6(lds0, ra0, rb0, fh, acc, la, lb, t, m, n, lds1, vlo, wave);
-      advance();
-      carry_step();
-      if (G + 1 >= total) break;
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      stage6(lds1, ra0, rb0, fh, acc, la, lb, t, m, n, lds0, vlo, wave);
-      advance();
-      carry_step();
-    }
-  }
-  __builtin_amdgcn_s_waitcnt(0);  // the repeated look-ahead load lands before the epilogue
-
-  int16_t* out = (int16_t*)uniform_ptr((const int8_t*)(cres + (int64_t)t.mod * m * n + t.tm * MT * n + t.tn * MT));
-  store_tile<true, int16_t, 2>(out, (int)n, (int)(m - t.tm * MT), (int)(n - t.tn * MT), wr, wc, fr, fh,
-                               [&](int a, int b, int v) {
-                                 return (int)(reduce_f(acc[a][b][v], fm, finv) * unit);
-                               });
-}
-
-// Persistent form for short k, as residue_gemm_persistent_kernel: an even
-// number of k blocks, a block per CU walking tiles, the next tile's first
-// stage loading under the current one's stores.  Across the one change from
-// FP6 to fp16 tiles a block walks (moduli are outermost) that load waits for
-// the stores instead, so that a stage loads one kind of slot only.
-__global__ __launch_bounds__(1024, 1) void mixed_gemm_persistent_kernel(
-    int64_t m, int64_t n, int64_t kp, const int8_t* __restrict__ pa, const int8_t* __restrict__ pb,
-    int16_t* __restrict__ cres, int group, uint32_t nvirt) {
-  __shared__ __attribute__((aligned(1024))) int8_t lds0[kBuf];
-  __shared__ __attribute__((aligned(1024))) int8_t lds1[kBuf];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wr = wave >> 2, wc = wave & 3;
-  const int fr = lane & 31, fh = lane >> 5;
-  const int ra0 = wr * 64 + fr, rb0 = wc * 64 + fr;
-  const int vlo = (wave & 7) * 1024 + lane * 16;
-  const int nstage = (int)(kp / BK);  // even, at most 16 (the host checks): one segment
-  const int64_t step_a = (int64_t)kMixedBytes * m, step_b = (int64_t)kMixedBytes * n;
-
-  uint32_t v = blockIdx.x;
-  if (v >= nvirt) return;
-  MixedTile cur = mixed_tile(v, m, n, (uint32_t)group), nxt = cur;
-  // look-ahead cursor: product (FP6) or half (fp16) lp of k block ls of the
-  // current tile, or, once ahead, the next tile's first stage
-  bool have_next = false, ahead = false, same = false;
-  int lp = 0, ls = 0;
-  const int8_t *la, *lb;
-  MixedTile lt = cur;  // the tile whose stage is loaded next
-  auto first = [&](const MixedTile& t, int p) __attribute__((always_inline)) {
-    const int qa = mixed_half(t.mod) ? 2 * t.mod : kSched[t.mod].plane_a[p];
-    const int qb = mixed_half(t.mod) ? 2 * t.mod : kSched[t.mod].plane_b[p];
-    la = mixed_piece(pa, 0, qa, m, t.tm);
-    lb = mixed_piece(pb, 0, qb, n, t.tn);
-  };
-  auto cross = [&]() __attribute__((always_inline)) {
-    if (same) {
-      ahead = true;
-      first(nxt, 0);
-      lt = nxt;
-    }
-  };
-  auto advance6 = [&]() __attribute__((always_inline)) {
-    if (ahead) return;
-    if (ls + 1 < nstage) {
-      ++ls;
-      la += step_a;
-      lb += step_b;
-    } else if (lp < 2) {
-      ++lp;
-      ls = 0;
-      first(cur, lp);
-    } else {
-      cross();
-    }
-  };
-  auto advance16 = [&]() __attribute__((always_inline)) {
-    if (ahead) return;
-    if (lp == 0) {
-      lp = 1;
-      la += m * BK;
-      lb += n * BK;
-    } else if (ls + 1 < nstage) {
-      ++ls;
-      lp = 0;
-      la += step_a - m * BK;
-      lb += step_b - n * BK;
-    } else {
-      cross();
-    }
-  };
-  first(cur, 0);
-  auto load_first = [&]() __attribute__((always_inline)) {
-    if (mixed_half(cur.mod)) {
-#pragma unroll
-      for (int d = 0; d < 4; ++d) dma16(d, la, lb, cur, m, n, lds0, vlo, wave);
-    } else {
-#pragma unroll
-      for (int d = 0; d < 3; ++d) dma6(d, la, lb, cur, m, n, lds0, vlo, wave);
-    }
-  };
-  load_first();
-  for (;;) {
-    const uint32_t vn = v + gridDim.x;
-    have_next = vn < nvirt;
-    if (have_next) nxt = mixed_tile(vn, m, n, (uint32_t)group);
-    const bool half = mixed_half(cur.mod);
-    same = have_next && mixed_half(nxt.mod) == half;
-    const float unit = half ? 1.0f : 64.0f;
-    const float fm = (float)kSched[cur.mod].m / unit, finv = kSched[cur.mod].inv * unit;
-    v16f acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) acc[a][b] = v16f{};
-    if (half) {
-      advance16();
-      auto stage = [&]<int R>(Turn<R>, const int8_t* buf, int8_t* next) __attribute__((always_inline)) {
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        stage16<R>(buf, ra0, rb0, fh, acc, fm, finv, la, lb, lt, m, n, next, vlo, wave);
-        __builtin_amdgcn_sched_barrier(0);
-        advance16();
-      };
-      for (int G = 0; G < 2 * nstage; G += 4) {
-        stage(Turn<0>{}, lds0, lds1);
-        stage(Turn<1>{}, lds1, lds0);
-        stage(Turn<2>{}, lds0, lds1);
-        stage(Turn<3>{}, lds1, lds0);
-      }
-    } else {
-      advance6();
-      int cp = 0, cs = 0;
-      auto carry_step = [&]() __attribute__((always_inline)) {
-        if (cp < 2 || cs + 1 < nstage) carry<2, false>(acc, cp, cs, nstage, 1, cur.mod, fm, finv);
-        if (++cs == nstage) {
-          cs = 0;
-          ++cp;
-        }
-      };
-      for (int G = 0; G < 3 * nstage; G += 2) {
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        stage6(lds0, ra0, rb0, fh, acc, la, lb, lt, m, n, lds1, vlo, wave);
-        advance6();
-        carry_step();
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        stage6(lds1, ra0, rb0, fh, acc, la, lb, lt, m, n, lds0, vlo, wave);
-        advance6();
-        carry_step();
-      }
-    }
-    int16_t* out =
-        (int16_t*)uniform_ptr((const int8_t*)(cres + (int64_t)cur.mod * m * n + cur.tm * MT * n + cur.tn * MT));
-    // the store offsets from a lane index read here, as in
-    // residue_gemm_persistent_kernel
-    const int el = lane_id_now() & 63;
-    store_tile<true, int16_t, 2>(out, (int)n, (int)(m - cur.tm * MT), (int)(n - cur.tn * MT), wr, wc, el & 31,
-                                 el >> 5, [&](int a, int b, int vv) {
-                                   return (int)(reduce_f(acc[a][b][vv], fm, finv) * unit);
-                                 });
-    if (!have_next) break;
-    v = vn;
-    cur = nxt;
-    lt = nxt;
-    lp = 0;
-    ls = 0;
-    if (!same) {
-      // the repeated last stage lands and every wavefront is done with both
-      // buffers before the first stage of the other kind goes out
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      first(cur, 0);
-      load_first();
-    }
     ahead = false;
   }
   __builtin_amdgcn_s_waitcnt(0);  // the last look-ahead (a repeat) lands before the block ends
@@ -1592,7 +1247,7 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_bytes_persistent_kernel(
   __builtin_amdgcn_s_waitcnt(0);  // the last look-ahead (a repeat) lands before the block ends
 }
 
-template <bool BYTES, typename OT>
+template <bool BYTES, typename OT, bool MIXED = false>
 hipError_t launch_gemm(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const int8_t* pb,
                        OT* cres, OT* part, int splits, hipStream_t stream) {
   if (m <= 0 || n <= 0) return hipSuccess;
@@ -1635,10 +1290,10 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const
                              n, kp, pa, pb, dst, group, (uint32_t)blocks);
       } else {
         if (shape == 3)
-          hipLaunchKernelGGL((residue_gemm_persistent_kernel<OT, 3>), pgrid, dim3(1024), 0, stream, m, n,
+          hipLaunchKernelGGL((residue_gemm_persistent_kernel<OT, 3, MIXED>), pgrid, dim3(1024), 0, stream, m, n,
                              kp, pa, pb, dst, group, (uint32_t)blocks);
         else
-          hipLaunchKernelGGL((residue_gemm_persistent_kernel<OT, 2>), pgrid, dim3(1024), 0, stream, m, n,
+          hipLaunchKernelGGL((residue_gemm_persistent_kernel<OT, 2, MIXED>), pgrid, dim3(1024), 0, stream, m, n,
                              kp, pa, pb, dst, group, (uint32_t)blocks);
       }
       return hipGetLastError();
@@ -1653,10 +1308,10 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const
                          pb, dst, splits, group);
   } else {
     if (shape == 3)
-      hipLaunchKernelGGL((residue_gemm_kernel<OT, 3>), grid, dim3(1024), 0, stream, m, n, kp, pa, pb,
+      hipLaunchKernelGGL((residue_gemm_kernel<OT, 3, MIXED>), grid, dim3(1024), 0, stream, m, n, kp, pa, pb,
                          dst, splits, group);
     else
-      hipLaunchKernelGGL((residue_gemm_kernel<OT, 2>), grid, dim3(1024), 0, stream, m, n, kp, pa, pb,
+      hipLaunchKernelGGL((residue_gemm_kernel<OT, 2, MIXED>), grid, dim3(1024), 0, stream, m, n, kp, pa, pb,
                          dst, splits, group);
   }
   if (splits > 1) {
@@ -1664,34 +1319,6 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const
     hipLaunchKernelGGL((reduce_splits_kernel<BYTES, OT>),
                        dim3((unsigned)((mn + 255) / 256), (unsigned)(BYTES ? kRA : kR)), dim3(256), 0,
                        stream, mn, splits, part, cres);
-  }
-  return hipGetLastError();
-}
-
-// The mixed slots' products: one persistent or one-tile launch, as launch_gemm.
-hipError_t launch_mixed(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const int8_t* pb, int16_t* cres,
-                        int16_t* part, int splits, hipStream_t stream) {
-  if (m <= 0 || n <= 0) return hipSuccess;
-  if (n > kMaxResidueCols) return hipErrorInvalidValue;
-  const int nstage = (int)(kp / BK);
-  if (nstage < 1 || splits < 1 || splits > nstage || (splits > 1 && !part)) return hipErrorInvalidValue;
-  const int group = kp <= 16 * BK ? 1 : 2;
-  const int64_t blocks = kR * ((m + MT - 1) / MT) * ((n + MT - 1) / MT);
-  if (blocks * splits > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
-  int dev = 0, cus = 0;
-  if (splits == 1 && nstage >= 2 && nstage <= 16 && nstage % 2 == 0 && hipGetDevice(&dev) == hipSuccess &&
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus >= 8 &&
-      blocks >= 2 * (int64_t)(cus / 8 * 8) && blocks <= (int64_t)UINT32_MAX - cus) {
-    hipLaunchKernelGGL(mixed_gemm_persistent_kernel, dim3((unsigned)(cus / 8 * 8)), dim3(1024), 0, stream, m, n,
-                       kp, pa, pb, cres, group, (uint32_t)blocks);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(mixed_gemm_kernel, dim3((unsigned)(blocks * splits)), dim3(1024), 0, stream, m, n, kp, pa,
-                     pb, splits > 1 ? part : cres, splits, group);
-  if (splits > 1) {
-    const int64_t mn = m * n;
-    hipLaunchKernelGGL((reduce_splits_kernel<false, int16_t>), dim3((unsigned)((mn + 255) / 256), (unsigned)kR),
-                       dim3(256), 0, stream, mn, splits, part, cres);
   }
   return hipGetLastError();
 }
@@ -1784,7 +1411,7 @@ hipError_t launch_residue_gemm_i16(int64_t m, int64_t n, int64_t kp, const int8_
 
 hipError_t launch_residue_gemm_mixed(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const int8_t* pb,
                                      int16_t* cres, int16_t* part, int splits, hipStream_t stream) {
-  return launch_mixed(m, n, kp, pa, pb, cres, part, splits, stream);
+  return launch_gemm<false, int16_t, true>(m, n, kp, pa, pb, cres, part, splits, stream);
 }
 
 hipError_t launch_residue_gemm_bytes_i32(int64_t m, int64_t n, int64_t kp, const int8_t* pa,
