@@ -91,15 +91,8 @@ bool fused_a(int64_t m, int64_t n, ozaki25_moduli_set set) {
   return known_set(set) && n <= 128 && m >= kFusedMinRows;
 }
 
-// The plane layout between the stages of one ozaki25_dgemm* call: the
-// published set's mixed slots (24 bytes per element in place of the stored
-// planes' 30, and five sixths of their products' matrix time), the all-byte
-// set's stored planes.
-int inner_layout(ozaki25_moduli_set set) { return bytes_set(set) ? (int)set : oz::kLayoutMixed; }
-static_assert(oz::kMixedSlots <= oz::kPlanes, "mixed slots fit the room of the stored planes");
-
-// planes of A and B (room for the stored planes of the set), exponents, and
-// the residue products: int16 for the published set (|c| <= 0.51 m <= 556), int8 for the all-byte set (|c| <= 128)
+// planes of A and B, exponents, and the residue products: int16 for the
+// published set (|c| <= 0.51 m <= 556), int8 for the all-byte set (|c| <= 128)
 Workspace layout(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set) {
   Workspace w;
   const int64_t kp = k_pad(k);
@@ -133,7 +126,7 @@ Workspace layout(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set) {
 // keys_cleared, were cleared by A's scan on the side), each run's
 // deconstruction reads the keys directly, and one launch turns all of them
 // into tau at the end.  zero / nzero (side 0): keys to clear on the side.
-hipError_t scan_and_deconstruct(int planes_layout, ozaki25_quantiser quant, int side, int64_t vecs,
+hipError_t scan_and_deconstruct(ozaki25_moduli_set set, ozaki25_quantiser quant, int side, int64_t vecs,
                                 int64_t k, const double* X, int64_t ldx, int t, int32_t* exps,
                                 int8_t* planes, hipStream_t s, int32_t* zero = nullptr,
                                 int64_t nzero = 0, bool keys_cleared = false) {
@@ -157,7 +150,7 @@ hipError_t scan_and_deconstruct(int planes_layout, ozaki25_quantiser quant, int 
       e = oz::launch_scan_cols(nv, k, Xr, ldx, exps + v0, s);
     }
     if (e == hipSuccess)
-      e = oz::launch_deconstruct(planes_layout, (int)quant, side, nv, vecs, k, kp, t, Xr, ldx, exps + v0,
+      e = oz::launch_deconstruct((int)set, (int)quant, side, nv, vecs, k, kp, t, Xr, ldx, exps + v0,
                                  side == 1, planes + v0 * oz::kKAlign, s);
   }
   if (side == 1 && e == hipSuccess) e = oz::launch_keys_to_sigma(vecs, t, exps, s);
@@ -316,7 +309,7 @@ ozaki25_status ozaki25_deconstruct(int side, int64_t vecs, int64_t k, const doub
   if (!X || !planes || !exps) return OZAKI25_ERR_INVALID_VALUE;
   if (((uintptr_t)planes & 15) || ((uintptr_t)exps & 3) || ((uintptr_t)X & 7))
     return OZAKI25_ERR_INVALID_VALUE;
-  return hip_status(scan_and_deconstruct((int)set, quant, side, vecs, k, X, ldx, scale_bits(k, set), exps,
+  return hip_status(scan_and_deconstruct(set, quant, side, vecs, k, X, ldx, scale_bits(k, set), exps,
                                           (int8_t*)planes, (hipStream_t)stream));
 }
 
@@ -411,7 +404,7 @@ ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A
     if (e == hipSuccess) e = oz::launch_scan_rows(m, k, A, lda, t, ea, eb, n, s);
     if (ev && e == hipSuccess) e = hipEventRecord(ev[1], s);
     if (bytes) {
-      if (e == hipSuccess) e = scan_and_deconstruct((int)set, quant, 1, n, k, B, ldb, t, eb, pb, s, nullptr, 0, true);
+      if (e == hipSuccess) e = scan_and_deconstruct(set, quant, 1, n, k, B, ldb, t, eb, pb, s, nullptr, 0, true);
     } else {
       if (e == hipSuccess) e = oz::launch_scan_cols(n, k, B, ldb, eb, s);
       if (e == hipSuccess) e = oz::launch_keys_to_sigma(n, t, eb, s);
@@ -424,7 +417,7 @@ ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A
     const oz::NativeOperands nat{A, lda, B, ldb, k};
     if (e == hipSuccess)
       e = bytes ? oz::launch_reconstruct_bytes_i8(m, n, (const int8_t*)cres, ea, eb, C, ldc, subtract ? 1 : 0, nat, s)
-                : oz::launch_reconstruct_i16(false, m, n, (const int16_t*)cres, ea, eb, C, ldc, subtract ? 1 : 0, nat, s);
+                : oz::launch_reconstruct_i16(m, n, (const int16_t*)cres, ea, eb, C, ldc, subtract ? 1 : 0, nat, s);
     if (ev && e == hipSuccess) e = hipEventRecord(ev[4], s);
     if (owned) {
       const hipError_t f = hipFreeAsync(ws, s);
@@ -435,23 +428,22 @@ ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A
   // the scans run interleaved with the deconstruction (scan_and_deconstruct),
   // so the scan stage is empty and the deconstruct stage holds both
   if (ev && e == hipSuccess) e = hipEventRecord(ev[1], s);
-  const int pl = inner_layout(set);
   // A's row scan clears B's column keys on the side
-  if (e == hipSuccess) e = scan_and_deconstruct(pl, quant, 0, m, k, A, lda, t, ea, pa, s, eb, n);
-  if (e == hipSuccess) e = scan_and_deconstruct(pl, quant, 1, n, k, B, ldb, t, eb, pb, s, nullptr, 0, true);
+  if (e == hipSuccess) e = scan_and_deconstruct(set, quant, 0, m, k, A, lda, t, ea, pa, s, eb, n);
+  if (e == hipSuccess) e = scan_and_deconstruct(set, quant, 1, n, k, B, ldb, t, eb, pb, s, nullptr, 0, true);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[2], s);
   if (e == hipSuccess)
     e = bytes ? oz::launch_residue_gemm_bytes_i8(m, n, kp, pa, pb, (int8_t*)cres, (int8_t*)part,
                                                  w.splits, s)
-              : oz::launch_residue_gemm_mixed(m, n, kp, pa, pb, (int16_t*)cres, (int16_t*)part,
-                                              w.splits, s);
+              : oz::launch_residue_gemm_i16(m, n, kp, pa, pb, (int16_t*)cres, (int16_t*)part,
+                                            w.splits, s);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[3], s);
   const int sub = subtract ? 1 : 0;
   // outputs on rows / columns flagged non-finite are re-issued natively
   const oz::NativeOperands nat{A, lda, B, ldb, k};
   if (e == hipSuccess)
     e = bytes ? oz::launch_reconstruct_bytes_i8(m, n, (const int8_t*)cres, ea, eb, C, ldc, sub, nat, s)
-              : oz::launch_reconstruct_i16(false, m, n, (const int16_t*)cres, ea, eb, C, ldc, sub, nat, s);
+              : oz::launch_reconstruct_i16(m, n, (const int16_t*)cres, ea, eb, C, ldc, sub, nat, s);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[4], s);
   if (owned) {
     const hipError_t f = hipFreeAsync(ws, s);
@@ -550,10 +542,10 @@ ozaki25_status ozaki25_dgemm_accurate(int64_t m, int64_t n, int64_t k, const dou
   if (e == hipSuccess) e = accurate_exponents(set, m, n, k, A, lda, B, ldb, ea, eb, base + w.total, aw, s);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[1], s);
   if (e == hipSuccess && !fused)
-    e = oz::launch_deconstruct(inner_layout(set), (int)quant, 0, m, m, k, kp, kAccurateT, A, lda, ea, false, pa, s);
+    e = oz::launch_deconstruct((int)set, (int)quant, 0, m, m, k, kp, kAccurateT, A, lda, ea, false, pa, s);
   // (the published set's fused product makes B's digit planes itself)
   if (e == hipSuccess && (bytes || !fused))
-    e = oz::launch_deconstruct(inner_layout(set), (int)quant, 1, n, n, k, kp, kAccurateT, B, ldb, eb, false, pb, s);
+    e = oz::launch_deconstruct((int)set, (int)quant, 1, n, n, k, kp, kAccurateT, B, ldb, eb, false, pb, s);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[2], s);
   if (e == hipSuccess) {
     if (fused && bytes)
@@ -563,12 +555,12 @@ ozaki25_status ozaki25_dgemm_accurate(int64_t m, int64_t n, int64_t k, const dou
     else if (bytes)
       e = oz::launch_residue_gemm_bytes_i8(m, n, kp, pa, pb, (int8_t*)cres, (int8_t*)part, w.splits, s);
     else
-      e = oz::launch_residue_gemm_mixed(m, n, kp, pa, pb, (int16_t*)cres, (int16_t*)part, w.splits, s);
+      e = oz::launch_residue_gemm_i16(m, n, kp, pa, pb, (int16_t*)cres, (int16_t*)part, w.splits, s);
   }
   if (ev && e == hipSuccess) e = hipEventRecord(ev[3], s);
   if (e == hipSuccess)
     e = bytes ? oz::launch_reconstruct_bytes_i8(m, n, (const int8_t*)cres, ea, eb, C, ldc, sub, nat, s)
-              : oz::launch_reconstruct_i16(false, m, n, (const int16_t*)cres, ea, eb, C, ldc, sub, nat, s);
+              : oz::launch_reconstruct_i16(m, n, (const int16_t*)cres, ea, eb, C, ldc, sub, nat, s);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[4], s);
   if (owned) {
     const hipError_t f = hipFreeAsync(ws, s);
@@ -622,7 +614,7 @@ ozaki25_status ozaki25_dgemm_planes(int64_t m, int64_t n, int64_t k, const uint8
     int16_t* cres = (int16_t*)ws;
     e = oz::launch_residue_gemm_i16(m, n, kp, pa, pb, cres, (int16_t*)part, splits, s);
     if (e == hipSuccess)
-      e = oz::launch_reconstruct_i16(true, m, n, cres, expsA, expsB, C, ldc, sub, oz::NativeOperands{}, s);
+      e = oz::launch_reconstruct_i16(m, n, cres, expsA, expsB, C, ldc, sub, oz::NativeOperands{}, s);
   }
   if (owned) {
     const hipError_t f = hipFreeAsync(ws, s);

@@ -202,41 +202,6 @@ __device__ __forceinline__ void emit_modulus(const double (&y)[kElems], const ui
   }
 }
 
-// Mixed slots (kMixedSlots): a square's two digit planes as above, a
-// nonsquare's centred residue (|x| <= 255, exact) as fp16, the thread's first
-// eight k in slot 2 I and its last eight in slot 2 I + 1, so that each
-// 16-byte store of a wavefront fills 1 KiB of contiguous bytes.
-typedef __fp16 h2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_f16(int a, int b) {
-  return __builtin_bit_cast(uint32_t, (h2)__builtin_amdgcn_cvt_pkrtz((float)a, (float)b));
-}
-
-template <int I, int RM>
-__device__ __forceinline__ void emit_mixed(const double (&y)[kElems], const uint32_t (&ylo)[kElems],
-                                           int8_t* planes, int64_t plane_stride, int64_t off) {
-  constexpr int M = kModulus[I];
-  if constexpr (!mixed_half(I)) {
-    emit_modulus<I, RM>(y, ylo, planes, plane_stride, off, nullptr);
-  } else {
-    int8_t* base = planes + (int64_t)(2 * I) * plane_stride + off;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      int x[8];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) x[c] = centred_residue<M, RM>(y[8 * h + c], ylo[8 * h + c]);
-      put16(base + h * plane_stride,
-            uint4{pack_f16(x[0], x[1]), pack_f16(x[2], x[3]), pack_f16(x[4], x[5]), pack_f16(x[6], x[7])});
-    }
-  }
-}
-
-template <int RM, int... I>
-__device__ __forceinline__ void emit_all_mixed(std::integer_sequence<int, I...>, const double (&y)[kElems],
-                                               const uint32_t (&ylo)[kElems], int8_t* planes,
-                                               int64_t plane_stride, int64_t off) {
-  (emit_mixed<I, RM>(y, ylo, planes, plane_stride, off), ...);
-}
-
 template <int RM, int... I>
 __device__ __forceinline__ void emit_all(std::integer_sequence<int, I...>, const double (&y)[kElems],
                                          const uint32_t (&ylo)[kElems], int8_t* planes,
@@ -348,26 +313,6 @@ __global__ __launch_bounds__(256) void deconstruct_kernel(int64_t vecs, int64_t 
                   plane_offset(vstride, kPlanes, v, g), lut);
 }
 
-// The same for the mixed slots: no split table, 24 bytes written per element.
-template <int SIDE, int RM, bool TZ>
-__global__ __launch_bounds__(256) void deconstruct_mixed_kernel(int64_t vecs, int64_t vstride, int64_t k,
-                                                                int64_t kp, const double* __restrict__ X,
-                                                                int64_t ldx,
-                                                                const int32_t* __restrict__ exps,
-                                                                bool keys_in, int t,
-                                                                int8_t* __restrict__ planes) {
-  int64_t v, g;
-  group_of(vecs, v, g);
-  const bool active = v < vecs && g < kp / kElems;
-  if (!active) return;
-  double x[kElems], y[kElems];
-  uint32_t ylo[kElems];
-  const int sigma = load_group<SIDE>(vecs, k, X, ldx, exps, keys_in, t, v, g * kElems, true, x);
-  scale_round<TZ, RM>(x, sigma, y, ylo);
-  emit_all_mixed<RM>(std::make_integer_sequence<int, kR>{}, y, ylo, planes, vstride * 128,
-                     plane_offset(vstride, kMixedSlots, v, g));
-}
-
 // ---- all-byte set (Sec. 5.1, candidate A) on the int8 route: the centred
 // residue of a byte modulus lies in [-128, 127] and is stored as it stands,
 // one int8 plane per modulus (8 bytes read, 15 written per element).
@@ -470,39 +415,28 @@ struct DecArgs {
   int8_t* planes;
 };
 
-template <int SIDE, int LAYOUT, int RM, bool TZ>
+template <int SIDE, bool BYTES, int RM, bool TZ>
 void launch_one(const DecArgs& a, hipStream_t stream) {
-  if constexpr (LAYOUT == kSetBytes)
+  if constexpr (BYTES)
     hipLaunchKernelGGL((deconstruct_bytes_kernel<SIDE, RM, TZ>), dim3((unsigned)a.blocks), dim3(256), 0,
                        stream, a.vecs, a.vstride, a.k, a.kp, a.X, a.ldx, a.exps, a.keys_in, a.t, a.planes);
-  else if constexpr (RM != 2) {  // the nearest-quotient bound of RM 2 holds for byte moduli only
-    if constexpr (LAYOUT == kLayoutMixed)
-      hipLaunchKernelGGL((deconstruct_mixed_kernel<SIDE, RM, TZ>), dim3((unsigned)a.blocks), dim3(256), 0,
-                         stream, a.vecs, a.vstride, a.k, a.kp, a.X, a.ldx, a.exps, a.keys_in, a.t, a.planes);
-    else
-      hipLaunchKernelGGL((deconstruct_kernel<SIDE, RM, TZ>), dim3((unsigned)a.blocks), dim3(256), 0, stream,
-                         a.vecs, a.vstride, a.k, a.kp, a.X, a.ldx, a.exps, a.keys_in, a.t, a.planes);
-  }
+  else if constexpr (RM != 2)  // the nearest-quotient bound of RM 2 holds for byte moduli only
+    hipLaunchKernelGGL((deconstruct_kernel<SIDE, RM, TZ>), dim3((unsigned)a.blocks), dim3(256), 0, stream,
+                       a.vecs, a.vstride, a.k, a.kp, a.X, a.ldx, a.exps, a.keys_in, a.t, a.planes);
 }
 
-template <int SIDE, int LAYOUT>
+template <int SIDE, bool BYTES>
 void launch_side(int rm, bool tz, const DecArgs& a, hipStream_t stream) {
   if (rm == 1) {
-    if (tz) launch_one<SIDE, LAYOUT, 1, true>(a, stream);
-    else launch_one<SIDE, LAYOUT, 1, false>(a, stream);
+    if (tz) launch_one<SIDE, BYTES, 1, true>(a, stream);
+    else launch_one<SIDE, BYTES, 1, false>(a, stream);
   } else if (rm == 2) {
-    if (tz) launch_one<SIDE, LAYOUT, 2, true>(a, stream);
-    else launch_one<SIDE, LAYOUT, 2, false>(a, stream);
+    if (tz) launch_one<SIDE, BYTES, 2, true>(a, stream);
+    else launch_one<SIDE, BYTES, 2, false>(a, stream);
   } else {
-    if (tz) launch_one<SIDE, LAYOUT, 3, true>(a, stream);
-    else launch_one<SIDE, LAYOUT, 3, false>(a, stream);
+    if (tz) launch_one<SIDE, BYTES, 3, true>(a, stream);
+    else launch_one<SIDE, BYTES, 3, false>(a, stream);
   }
-}
-
-template <int LAYOUT>
-void launch_layout(int side, int rm, bool tz, const DecArgs& a, hipStream_t stream) {
-  if (side == 0) launch_side<0, LAYOUT>(rm, tz, a, stream);
-  else launch_side<1, LAYOUT>(rm, tz, a, stream);
 }
 
 }  // namespace
@@ -521,20 +455,24 @@ hipError_t launch_digits(int side, int64_t vecs, int64_t k, int64_t kp, const do
   return hipGetLastError();
 }
 
-hipError_t launch_deconstruct(int layout, int quant, int side, int64_t vecs, int64_t vstride, int64_t k,
+hipError_t launch_deconstruct(int set, int quant, int side, int64_t vecs, int64_t vstride, int64_t k,
                               int64_t kp, int t, const double* X, int64_t ldx, const int32_t* exps,
                               bool keys_in, int8_t* planes, hipStream_t stream) {
   if (vstride < vecs || t > kMaxScaleBits) return hipErrorInvalidValue;
   if (vecs <= 0 || kp <= 0) return hipSuccess;
-  const bool bytes = layout == kSetBytes;
+  const bool bytes = set == kSetBytes;
   const bool tz = quant == kQuantTZ;
   // |y| <= 2^t: the nearest quotient with ylo from kMagic, then (the byte
   // moduli at t = 52) with ylo split off, else one correction
   const int mode = t <= (bytes ? 51 : 50) ? 1 : (bytes && t == 52 ? 2 : 3);
   const DecArgs a{((vecs + 31) / 32) * (kp / 128), vecs, vstride, k, kp, X, ldx, exps, keys_in, t, planes};
-  if (bytes) launch_layout<kSetBytes>(side, mode, tz, a, stream);
-  else if (layout == kLayoutMixed) launch_layout<kLayoutMixed>(side, mode, tz, a, stream);
-  else launch_layout<kSetPublished>(side, mode, tz, a, stream);
+  if (side == 0) {
+    if (bytes) launch_side<0, true>(mode, tz, a, stream);
+    else launch_side<0, false>(mode, tz, a, stream);
+  } else {
+    if (bytes) launch_side<1, true>(mode, tz, a, stream);
+    else launch_side<1, false>(mode, tz, a, stream);
+  }
   return hipGetLastError();
 }
 

@@ -400,7 +400,8 @@ hipError_t launch_fused_g(int64_t m, int64_t n, int64_t k, int64_t kp, const dou
 // products reach 255^2, so that set is reduced every kSegN = 4 stages (256
 // k: 16 646 400, plus at most 256 left by the last reduction); the square
 // sets (at most 256 and 512 per k) every kSegS stages.  The outputs are the
-// residues of the product path (|c| <= 0.51 m_i), so its reconstruction takes
+// compact residues of the published set's product path (the true ones times
+// compact_scale(i)^-1 mod m_i, |c| <= 0.51 m_i), so its reconstruction takes
 // them as they stand.  B's operands come from fused_b_digits_kernel in
 // [kp/128][24][n][128] bytes: planes 2 g, 2 g + 1 hold square g's digits
 // (the 128 k of the block, one byte each); planes 12 + 2 g + h hold
@@ -425,6 +426,7 @@ struct PairConst {
   int ms, s, mn;         // square modulus, its root, nonsquare modulus
   double qs, qn;         // RN(1/m) for the quotient route
   float is, ims, imn;    // RN(1/s), RN(1/ms), RN(1/mn)
+  float inv16;           // 16^-1 mod mn
 };
 constexpr PairConst make_pair(int g) {
   return PairConst{kModulus[g],
@@ -434,7 +436,8 @@ constexpr PairConst make_pair(int g) {
                    1.0 / kModulus[kPairs + g],
                    1.0f / (float)root_of(g),
                    1.0f / (float)kModulus[g],
-                   1.0f / (float)kModulus[kPairs + g]};
+                   1.0f / (float)kModulus[kPairs + g],
+                   (float)inverse_mod(16, kModulus[kPairs + g])};
 }
 constexpr bool pairs_are_square_nonsquare() {
   for (int g = 0; g < kPairs; ++g)
@@ -443,6 +446,7 @@ constexpr bool pairs_are_square_nonsquare() {
 }
 static_assert(kR == 2 * kPairs && pairs_are_square_nonsquare(),
               "six squares (s <= 33) first, then six nonsquares below 512");
+static_assert(compact_scale(0) == 1 && compact_scale(kPairs) == 16, "compact scales of the product path");
 __constant__ PairConst kPair[kPairs] = {make_pair(0), make_pair(1), make_pair(2),
                                         make_pair(3), make_pair(4), make_pair(5)};
 
@@ -786,8 +790,8 @@ __global__ __launch_bounds__(1024, 1) void fused_pub_kernel(
     if (s + 1 < nstage) step(s + 1, x1, x0);
   }
 
-  // epilogue: the residues -- square (acc1 + s accs) mod m; nonsquare (x y
-  // summed) mod m -- each reduced to |c| <= 0.51 m (every value
+  // epilogue: the compact residues -- square (acc1 + s accs) mod m; nonsquare
+  // (x y summed) 16^-1 mod m -- each reduced to |c| <= 0.51 m (every value
   // here is an integer below 2^24 in magnitude), as int16 in [12][m][n]
   const int64_t col = wc * 32 + fr;
   int16_t* outs = cres + (int64_t)grp * m * n;
@@ -797,7 +801,7 @@ __global__ __launch_bounds__(1024, 1) void fused_pub_kernel(
     const int64_t row = row0 + wr * 32 + 8 * (v >> 2) + 4 * fh + (v & 3);
     const float sv = reduce_pf(reduce_pf(acc1[v], fms, pc.ims) + fs * reduce_pf(accs[v], fms, pc.ims), fms,
                                pc.ims);
-    const float nv = reduce_pf(accn[v], fmn, pc.imn);
+    const float nv = reduce_pf(reduce_pf(accn[v], fmn, pc.imn) * pc.inv16, fmn, pc.imn);
     if (row < m && col < n) {
       outs[row * n + col] = (int16_t)(int)sv;
       outn[row * n + col] = (int16_t)(int)nv;

@@ -11,10 +11,6 @@ namespace oz {
 // Modulus sets, as numbered by ozaki25_moduli_set.
 constexpr int kSetPublished = 0;  // Eq. (moduli), FP8 limb route
 constexpr int kSetBytes = 1;      // Sec. 5.1 candidate A, int8 route
-// Plane layouts, as launch_deconstruct takes them: the two sets' stored
-// planes under their own numbers, and the published set's mixed slots
-// (kMixedSlots in moduli.hpp), which stay inside ozaki25_dgemm*.
-constexpr int kLayoutMixed = 2;
 // Quantisers, as numbered by ozaki25_quantiser.
 constexpr int kQuantRN = 0;  // round to nearest, ties to even
 constexpr int kQuantTZ = 1;  // toward zero
@@ -45,13 +41,12 @@ constexpr int kMaxScaleBits = 58;
 
 // Alg. 2: scale, quantise, residues and the planes of one operand, given exps
 // (sigma, or with keys_in the column scan's exponent keys, turned into sigma
-// on load) and the scale bits t: e4m3 limb planes (published set), int8
-// residue planes (all-byte set) or the published set's mixed slots.  vecs
-// vectors of X, written into a plane
+// on load) and the scale bits t: e4m3 limb planes (published set) or int8
+// residue planes (all-byte set).  vecs vectors of X, written into a plane
 // layout of vstride >= vecs vectors (planes points at the first one's
 // bytes), so that a run of vectors can fill its part of a larger operand's
 // planes.
-hipError_t launch_deconstruct(int layout, int quant, int side, int64_t vecs, int64_t vstride, int64_t k,
+hipError_t launch_deconstruct(int set, int quant, int side, int64_t vecs, int64_t vstride, int64_t k,
                               int64_t kp, int t, const double* X, int64_t ldx, const int32_t* exps,
                               bool keys_in, int8_t* planes, hipStream_t stream);
 
@@ -72,10 +67,6 @@ int residue_gemm_splits(int set, int64_t m, int64_t n, int64_t kp);
 hipError_t launch_residue_gemm_i16(int64_t m, int64_t n, int64_t kp, const int8_t* pa,
                                    const int8_t* pb, int16_t* cres, int16_t* part, int splits,
                                    hipStream_t stream);
-// The same compact products from mixed slots; the residues are the true ones,
-// reduced to |c| <= 0.51 m_i (launch_reconstruct_i16 with compact false).
-hipError_t launch_residue_gemm_mixed(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const int8_t* pb,
-                                     int16_t* cres, int16_t* part, int splits, hipStream_t stream);
 hipError_t launch_residue_gemm_bytes_i32(int64_t m, int64_t n, int64_t kp, const int8_t* pa,
                                          const int8_t* pb, int32_t* cres, hipStream_t stream);
 hipError_t launch_residue_gemm_bytes_i8(int64_t m, int64_t n, int64_t kp, const int8_t* pa,
@@ -94,7 +85,8 @@ hipError_t launch_fused_bytes(int quant, int64_t m, int64_t n, int64_t k, int64_
 // Storage mode F for A, published set (at most 128 columns): B's digit
 // planes for the fused product (24 planes [kp/128][24][n][128] into pb, from
 // B and its column exponents tau), then the per-modulus products [12][m][n]
-// as true residues reduced to |c| <= 0.51 m_i, int16, straight from FP64 A and its row exponents sigma.  k == 0 is not handled here.
+// as the compact int16 residues launch_reconstruct_i16 takes, straight from
+// FP64 A and its row exponents sigma.  k == 0 is not handled here.
 hipError_t launch_fused_pub(int quant, int64_t m, int64_t n, int64_t k, int64_t kp, int t, const double* A,
                             int64_t lda, const int32_t* sigma, const double* B, int64_t ldb,
                             const int32_t* tau, int8_t* pb, int16_t* cres, hipStream_t stream);
@@ -112,13 +104,11 @@ struct NativeOperands {
   int64_t k = 0;
 };
 
-// Alg. 3: Garner, Horner, lift, single rounding (C = or C -= ).  The int16
-// residues, |c| <= 0.51 m_i, are the true ones or (compact) the limb
-// products' compact ones, without compact_scale(i).
+// Alg. 3: Garner, Horner, lift, single rounding (C = or C -= ).
 hipError_t launch_reconstruct_i32(int64_t m, int64_t n, const int32_t* cres, const int32_t* ea,
                                   const int32_t* eb, double* C, int64_t ldc, int subtract,
                                   hipStream_t stream);
-hipError_t launch_reconstruct_i16(bool compact, int64_t m, int64_t n, const int16_t* cres, const int32_t* ea,
+hipError_t launch_reconstruct_i16(int64_t m, int64_t n, const int16_t* cres, const int32_t* ea,
                                   const int32_t* eb, double* C, int64_t ldc, int subtract,
                                   const NativeOperands& nat, hipStream_t stream);
 // the same for the fifteen residues of the all-byte set

@@ -77,13 +77,6 @@ constexpr int compact_scale(int i) { return root_of(i) ? 1 : 16; }
 
 static_assert(plane_base(kR) == kPlanes, "30 stored planes for the published set");
 
-// The layout that ozaki25_dgemm* uses between its own stages: two 128-byte
-// slots per modulus and k block, [k_pad/128][24][vectors][128].  Squares keep
-// their two limb planes; a nonsquare holds its centred residue as fp16, slot
-// 0 the first eight and slot 1 the last eight of every sixteen k.
-constexpr int kMixedSlots = 2 * kR;
-constexpr bool mixed_half(int i) { return i >= 6; }
-
 // ---- all-byte set (Sec. 5.1, candidate A): 256 first, then fourteen odd
 // moduli; log2 of the product 117.8
 constexpr int kRA = 15;

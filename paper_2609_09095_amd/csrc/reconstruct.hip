@@ -138,7 +138,7 @@ __device__ __forceinline__ int load_residue(const RT* rowbase, int n, int col) {
 // modulus-q row sits mn elements further per q.
 // fill: the value of an output on a row or column flagged non-finite (NaN,
 // or +0 when the native re-issue supplies those outputs)
-template <typename RT, bool COMPACT>
+template <typename RT>
 __device__ __forceinline__ double reconstruct_one(const RT* rowq, int64_t mn, int n, int col, int sa,
                                                   int sb, double fill) {
   if (sa == INT32_MIN || sb == INT32_MIN) return fill;
@@ -147,7 +147,7 @@ __device__ __forceinline__ double reconstruct_one(const RT* rowq, int64_t mn, in
 #pragma unroll
   for (int q = 0; q < kR; ++q) c[q] = load_residue(rowq + q * mn, n, col);
   [&]<int... J>(std::integer_sequence<int, J...>) {
-    (garner_digit<J, COMPACT>(c, v, packed), ...);
+    (garner_digit<J, sizeof(RT) == 2>(c, v, packed), ...);
   }(std::make_integer_sequence<int, kR>{});
   const int e = -sa - sb;
   double out;
@@ -232,7 +232,7 @@ __device__ __forceinline__ double reconstruct_one_a(const RT* rowq, int64_t mn, 
 }
 
 // Grid: x over 256-column strips, y over rows (strided by gridDim.y).
-template <bool BYTES, typename RT, bool COMPACT>
+template <bool BYTES, typename RT>
 __global__ __launch_bounds__(256) void reconstruct_kernel(int64_t m, int64_t n,
                                                           const RT* __restrict__ cres,
                                                           const int32_t* __restrict__ ea,
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(int64_t m, int64_t n,
   const int sb = eb[col];
   for (int64_t row = blockIdx.y; row < m; row += gridDim.y) {
     const double r = BYTES ? reconstruct_one_a(cres + row * n, mn, (int)n, (int)col, ea[row], sb, fill)
-                           : reconstruct_one<RT, COMPACT>(cres + row * n, mn, (int)n, (int)col, ea[row], sb, fill);
+                           : reconstruct_one(cres + row * n, mn, (int)n, (int)col, ea[row], sb, fill);
     // C streams through once: non-temporal load and store (with the
     // residues' nt loads, the 32768^2 update 8.14 -> 7.74 ms; the all-byte
     // set and 8192^3 unchanged)
@@ -322,7 +322,7 @@ dim3 grid_for(int64_t m, int64_t n) {
   return dim3((unsigned)((n + 255) / 256), (unsigned)(y < 65535 ? y : 65535));
 }
 
-template <bool BYTES, typename RT, bool COMPACT = false>
+template <bool BYTES, typename RT>
 hipError_t launch_rec(int64_t m, int64_t n, const RT* cres, const int32_t* ea, const int32_t* eb,
                       double* C, int64_t ldc, int subtract, const NativeOperands& nat,
                       hipStream_t stream) {
@@ -334,7 +334,7 @@ hipError_t launch_rec(int64_t m, int64_t n, const RT* cres, const int32_t* ea, c
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((reconstruct_kernel<BYTES, RT, COMPACT>), grid, dim3(256), 0, stream, m, n, cres, ea, eb, C,
+  hipLaunchKernelGGL((reconstruct_kernel<BYTES, RT>), grid, dim3(256), 0, stream, m, n, cres, ea, eb, C,
                      ldc, subtract, nat.A ? 0.0 : __builtin_nan(""));
   if (nat.A && !subtract) {
     const hipError_t e = hipGetLastError();
@@ -353,11 +353,10 @@ hipError_t launch_reconstruct_i32(int64_t m, int64_t n, const int32_t* cres, con
   return launch_rec<false, int32_t>(m, n, cres, ea, eb, C, ldc, subtract, NativeOperands{}, stream);
 }
 
-hipError_t launch_reconstruct_i16(bool compact, int64_t m, int64_t n, const int16_t* cres, const int32_t* ea,
+hipError_t launch_reconstruct_i16(int64_t m, int64_t n, const int16_t* cres, const int32_t* ea,
                                   const int32_t* eb, double* C, int64_t ldc, int subtract,
                                   const NativeOperands& nat, hipStream_t stream) {
-  return compact ? launch_rec<false, int16_t, true>(m, n, cres, ea, eb, C, ldc, subtract, nat, stream)
-                 : launch_rec<false, int16_t>(m, n, cres, ea, eb, C, ldc, subtract, nat, stream);
+  return launch_rec<false, int16_t>(m, n, cres, ea, eb, C, ldc, subtract, nat, stream);
 }
 
 hipError_t launch_reconstruct_bytes_i32(int64_t m, int64_t n, const int32_t* cres,

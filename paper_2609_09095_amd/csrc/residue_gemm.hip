@@ -48,8 +48,6 @@
 // 20-25 B/clk per CU, which bounds a stage (halving the stream cuts the time
 // by a quarter, halving the LDS fragment reads by 2 %), and the MFMA clock
 // itself drops with the switching activity of dense data.
-#include <type_traits>
-
 #include "kernels.hpp"
 #include "moduli.hpp"
 
@@ -331,94 +329,6 @@ static_assert((int64_t)(kModulus[0] / 2 + kModulus[0] / 50 + 1) * (kModulus[0] -
               "carry bound");
 static_assert(kModulus[0] >= kModulus[kR - 1] && kModulus[0] >= kModulus[1], "largest modulus first");
 
-// ---- mixed operands: fp16 residues for the nonsquare moduli ---------------
-// Inside ozaki25_dgemm* the published set's planes take kMixedSlots slots
-// instead of the stage API's 30 limb planes: a square keeps its two base-s
-// digit planes (three FP8 products, as above), a nonsquare (m <= 511) holds
-// its centred residue itself, |x| <= 255, as fp16 in two slots of 64 k each
-// (the k order within the pair is the deconstruction's, the same for A and
-// B).  Its product is ONE fp16 MFMA product: at half the FP8 rate that is two
-// FP8 products' matrix time and operand bytes in place of three, 30 instead
-// of 36 over the set, and 24 plane bytes per element instead of 30.
-// Per k the fp16 products reach 255^2, so an accumulator holds at most
-// kWindow = 4 stages (256 k) between reductions to stay an exact integer
-// below 2^24; the four 32 x 32 blocks of a wavefront take turns, one reduced
-// per stage, so that its 48 VALU instructions run under the other blocks'
-// MFMAs (all four together would hold every wavefront's MFMAs up).
-constexpr int kWindow = 4;
-constexpr int kHalfK = BK / 2;  // k per fp16 stage
-static_assert((int64_t)kWindow * kHalfK * 255 * 255 + 261 < (1LL << 24), "fp16 sums exact between reductions");
-constexpr bool mixed_moduli_fit() {
-  for (int i = 0; i < kR; ++i)
-    if (mixed_half(i) ? kModulus[i] > 511 : (!root_of(i) || plane_base(i) != 2 * i)) return false;
-  return true;
-}
-static_assert(mixed_moduli_fit(), "fp16 moduli below 512; the squares' slots are their limb planes");
-
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-
-// fp16 fragment of one 32-row block for one 16-k step: lane half fh takes
-// 16-byte chunk 2 ks + fh of its row
-__device__ __forceinline__ v8h frag_f16(const int8_t* base, int r, int ks, int fh) {
-  return *reinterpret_cast<const v8h*>(base + r * BK + (((2 * ks + fh) ^ swz(r)) << 4));
-}
-
-// One stage: four 16-k steps of 2 x 2 MFMAs; block RED (row block RED / 2,
-// column block RED % 2) is reduced mod m first, under the other blocks'
-// MFMAs of step 0.
-template <int S, int RED>
-__device__ __forceinline__ void stage_mma_dma_f16(const int8_t* la, const int8_t* lb, int ra0, int rb0,
-                                                  int fh, v16f (&acc)[2][2], float fm, float finv,
-                                                  __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb,
-                                                  int8_t* na, int8_t* nb, const int* voffa,
-                                                  const int* voffb, int wave) {
-  constexpr int ND = Tile<S>::DMA;
-  static_assert(Tile<S>::BB == 2, "2 x 2 blocks per wavefront");
-  v8h af[4][2], bf[4][2];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-#pragma unroll
-    for (int x = 0; x < 2; ++x) af[ks][x] = frag_f16(la, ra0 + 32 * x, ks, fh);
-#pragma unroll
-    for (int x = 0; x < 2; ++x) bf[ks][x] = frag_f16(lb, rb0 + 32 * x, ks, fh);
-  }
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int q = (RED + 1 + i) & 3, a = q >> 1, b = q & 1;  // block RED last
-      const int j = ks * 4 + i;                               // MFMA number in issue order
-      if (j < ND) stage_dma<S>(j, ra, rb, na, nb, voffa, voffb, wave);
-      if (ks == 0 && i == 3) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[a][b][v] = reduce_f(acc[a][b][v], fm, finv);
-      }
-      acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[ks][a], bf[ks][b], acc[a][b], 0, 0, 0);
-    }
-  // step 0: its fragments, then per MFMA one fragment of step 1, one DMA load
-  // and a third of the reduction; the later steps' fragments among the MFMAs
-  __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
-  }
-#pragma unroll
-  for (int i = 3; i < ND; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-  }
-#pragma unroll
-  for (int i = 0; i < 12 - ND; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-  }
-  __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-}
-
 // Output stores through a global (not generic) pointer; NT marks them
 // streaming (measured: the FP8 kernel gains with it, the int8 one without).
 template <bool NT, typename OT>
@@ -477,7 +387,7 @@ __device__ __forceinline__ void store_tile(OT* out, int nn, int rows_left, int c
 // splits > 1 (split-k): consecutive blocks take the same tile's stage ranges,
 // and block (tile, split) writes its centred partial product to the split's
 // own [r][m][n] slice of cres; reduce_splits_kernel sums them mod m.
-template <typename OT, int S, bool MIXED>
+template <typename OT, int S>
 __global__ __launch_bounds__(1024, 1) void residue_gemm_kernel(int64_t m, int64_t n, int64_t kp,
                                                               const int8_t* __restrict__ pa,
                                                               const int8_t* __restrict__ pb,
@@ -485,8 +395,6 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_kernel(int64_t m, int64_
                                                               int group) {
   // two LDS stages, each an A tile (BM rows x 128 bytes) and a B tile
   constexpr int BM = Tile<S>::BM, BN = Tile<S>::BN, NB = Tile<S>::BB, WC = Tile<S>::WC;
-  constexpr int NPL = MIXED ? kMixedSlots : kPlanes;  // planes (or slots) in the layout
-  static_assert(!MIXED || sizeof(OT) == 2, "mixed operands: the compact int16 output");
   __shared__ __attribute__((aligned(1024))) int8_t lds_a0[BM * BK];
   __shared__ __attribute__((aligned(1024))) int8_t lds_b0[BN * BK];
   __shared__ __attribute__((aligned(1024))) int8_t lds_a1[BM * BK];
@@ -546,12 +454,12 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_kernel(int64_t m, int64_
   // plane layout and jumping to the next product's first stage at a product
   // boundary (it stays on the last stage, whose look-ahead load repeats
   // it); the carry cursor (cp, cs) follows the stage just computed.
-  const int64_t step_a = (int64_t)NPL * m * BK, step_b = (int64_t)NPL * n * BK;
+  const int64_t step_a = (int64_t)kPlanes * m * BK, step_b = (int64_t)kPlanes * n * BK;
   auto first_a = [&](int p) {
-    return pa + (((int64_t)sbeg * NPL + kSched[mod].plane_a[p]) * m + tm * BM) * BK;
+    return pa + (((int64_t)sbeg * kPlanes + kSched[mod].plane_a[p]) * m + tm * BM) * BK;
   };
   auto first_b = [&](int p) {
-    return pb + (((int64_t)sbeg * NPL + kSched[mod].plane_b[p]) * n + tn * BN) * BK;
+    return pb + (((int64_t)sbeg * kPlanes + kSched[mod].plane_b[p]) * n + tn * BN) * BK;
   };
   int lp = 0, ls = 0, cp = 0, cs = 0;
   const int8_t* la = first_a(0);
@@ -579,68 +487,22 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_kernel(int64_t m, int64_
       ++cp;
     }
   };
-  if (MIXED && mixed_half(mod)) {
-    // fp16 modulus: 2 nstage stages of 64 k, slots 2 mod and 2 mod + 1 of
-    // each k block in turn; the look-ahead stays on the last stage
-    const int8_t* ha = pa + (((int64_t)sbeg * NPL + 2 * mod) * m + tm * BM) * BK;
-    const int8_t* hb = pb + (((int64_t)sbeg * NPL + 2 * mod) * n + tn * BN) * BK;
-    const int64_t odd_a = m * BK, odd_b = n * BK;
-    const int halves = 2 * nstage;
-    int lj = 0;
-    auto next = [&]() {
-      if (lj + 1 < halves) {
-        ha += (lj & 1) ? step_a - odd_a : odd_a;
-        hb += (lj & 1) ? step_b - odd_b : odd_b;
-        ++lj;
-      }
-    };
-    auto stage = [&]<int RED>(std::integral_constant<int, RED>, const int8_t* a, const int8_t* b, int8_t* an,
-                              int8_t* bn) __attribute__((always_inline)) {
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      stage_mma_dma_f16<S, RED>(a, b, ra0, rb0, fh, acc, fm, finv, rsrc(ha, na), rsrc(hb, nb), an, bn,
-                                 voffa, voffb, wave);
-      __builtin_amdgcn_sched_barrier(0);
-      next();
-    };
-    stage_load<S>(rsrc(ha, na), rsrc(hb, nb), lds_a0, lds_b0, voffa, voffb, wave);
-    next();
-    // an odd k block first, so that the loop needs no exit half way (its
-    // join costs registers)
-    if (halves & 2) {
-      stage(std::integral_constant<int, 2>{}, lds_a0, lds_b0, lds_a1, lds_b1);
-      stage(std::integral_constant<int, 3>{}, lds_a1, lds_b1, lds_a0, lds_b0);
-    }
-    for (int G = halves & 2; G < halves; G += 4) {
-      stage(std::integral_constant<int, 0>{}, lds_a0, lds_b0, lds_a1, lds_b1);
-      stage(std::integral_constant<int, 1>{}, lds_a1, lds_b1, lds_a0, lds_b0);
-      stage(std::integral_constant<int, 2>{}, lds_a0, lds_b0, lds_a1, lds_b1);
-      stage(std::integral_constant<int, 3>{}, lds_a1, lds_b1, lds_a0, lds_b0);
-    }
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[a][b][v] = reduce_f(acc[a][b][v], fm, finv);
-  } else {
-    if (total > 0) stage_load<S>(rsrc(la, na), rsrc(lb, nb), lds_a0, lds_b0, voffa, voffb, wave);
+  if (total > 0) stage_load<S>(rsrc(la, na), rsrc(lb, nb), lds_a0, lds_b0, voffa, voffb, wave);
+  advance();
+  for (int G = 0; G < total; G += 2) {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    stage_mma_dma<S>(lds_a0, lds_b0, ra0, rb0, fh, acc, rsrc(la, na), rsrc(lb, nb), lds_a1, lds_b1,
+                      voffa, voffb, wave);
     advance();
-    for (int G = 0; G < total; G += 2) {
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      stage_mma_dma<S>(lds_a0, lds_b0, ra0, rb0, fh, acc, rsrc(la, na), rsrc(lb, nb), lds_a1, lds_b1,
-                        voffa, voffb, wave);
-      advance();
-      carry_step();
-      if (G + 1 >= total) break;
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      stage_mma_dma<S>(lds_a1, lds_b1, ra0, rb0, fh, acc, rsrc(la, na), rsrc(lb, nb), lds_a0, lds_b0,
-                        voffa, voffb, wave);
-      advance();
-      carry_step();
-    }
+    carry_step();
+    if (G + 1 >= total) break;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    stage_mma_dma<S>(lds_a1, lds_b1, ra0, rb0, fh, acc, rsrc(la, na), rsrc(lb, nb), lds_a0, lds_b0,
+                      voffa, voffb, wave);
+    advance();
+    carry_step();
   }
   __builtin_amdgcn_s_waitcnt(0);  // the repeated look-ahead load lands before the epilogue
 
@@ -674,12 +536,11 @@ __device__ __forceinline__ int lane_id_now() {
 // The next tile's first barrier waits for every load and store (loads and
 // stores share one counter, and their relative completion order is not
 // relied on).  Only the compact int16 output takes this form.
-template <typename OT, int S, bool MIXED>
+template <typename OT, int S>
 __global__ __launch_bounds__(1024, 1) void residue_gemm_persistent_kernel(
     int64_t m, int64_t n, int64_t kp, const int8_t* __restrict__ pa, const int8_t* __restrict__ pb,
     OT* __restrict__ cres, int group, uint32_t nvirt) {
   constexpr int BM = Tile<S>::BM, BN = Tile<S>::BN, NB = Tile<S>::BB, WC = Tile<S>::WC;
-  constexpr int NPL = MIXED ? kMixedSlots : kPlanes;
   static_assert(sizeof(OT) == 2, "the compact int16 residue output");
   __shared__ __attribute__((aligned(1024))) int8_t lds_a0[BM * BK];
   __shared__ __attribute__((aligned(1024))) int8_t lds_b0[BN * BK];
@@ -698,7 +559,7 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_persistent_kernel(
   const int nstage = (int)(kp / BK);
   const int nseg = (nstage + kSeg - 1) / kSeg;
   const int total = 3 * nstage;  // even (the host checks)
-  const int64_t step_a = (int64_t)NPL * m * BK, step_b = (int64_t)NPL * n * BK;
+  const int64_t step_a = (int64_t)kPlanes * m * BK, step_b = (int64_t)kPlanes * n * BK;
   auto rsrc = [](const int8_t* p, int nrec) __attribute__((always_inline)) {
     return __builtin_amdgcn_make_buffer_rsrc((void*)uniform_ptr(p), (short)0, nrec, 0x00020000);
   };
@@ -719,12 +580,10 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_persistent_kernel(
     return t;
   };
   auto first_a = [&](const TileAt& t, int p) __attribute__((always_inline)) {
-    const int q = MIXED && mixed_half(t.mod) ? 2 * t.mod : kSched[t.mod].plane_a[p];
-    return pa + ((int64_t)q * m + t.tm * BM) * BK;
+    return pa + ((int64_t)kSched[t.mod].plane_a[p] * m + t.tm * BM) * BK;
   };
   auto first_b = [&](const TileAt& t, int p) __attribute__((always_inline)) {
-    const int q = MIXED && mixed_half(t.mod) ? 2 * t.mod : kSched[t.mod].plane_b[p];
-    return pb + ((int64_t)q * n + t.tn * BN) * BK;
+    return pb + ((int64_t)kSched[t.mod].plane_b[p] * n + t.tn * BN) * BK;
   };
 
   uint32_t v = blockIdx.x;
@@ -736,19 +595,13 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_persistent_kernel(
   int lp = 0, ls = 0, lna = cur.na, lnb = cur.nb;
   const int8_t* la = first_a(cur, 0);
   const int8_t* lb = first_b(cur, 0);
-  // an fp16 tile's stages: the two slots of each k block in turn, lp the slot
   auto advance = [&]() __attribute__((always_inline)) {
     if (ahead) return;
-    if (MIXED && mixed_half(cur.mod) && (lp == 0 || ls + 1 < nstage)) {
-      la += lp ? step_a - m * BK : m * BK;
-      lb += lp ? step_b - n * BK : n * BK;
-      ls += lp;
-      lp ^= 1;
-    } else if (!(MIXED && mixed_half(cur.mod)) && ls + 1 < nstage) {
+    if (ls + 1 < nstage) {
       ++ls;
       la += step_a;
       lb += step_b;
-    } else if (!(MIXED && mixed_half(cur.mod)) && lp < 2) {
+    } else if (lp < 2) {
       ++lp;
       ls = 0;
       la = first_a(cur, lp);
@@ -784,36 +637,19 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_persistent_kernel(
         ++cp;
       }
     };
-    if (MIXED && mixed_half(cur.mod)) {
-      auto stage = [&]<int RED>(std::integral_constant<int, RED>, const int8_t* a, const int8_t* b, int8_t* an,
-                                int8_t* bn) __attribute__((always_inline)) {
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        stage_mma_dma_f16<S, RED>(a, b, ra0, rb0, fh, acc, fm, finv, rsrc(la, lna), rsrc(lb, lnb), an, bn,
-                                   voffa, voffb, wave);
-        advance();
-      };
-      for (int G = 0; G < 2 * nstage; G += 4) {  // nstage is even
-        stage(std::integral_constant<int, 0>{}, lds_a0, lds_b0, lds_a1, lds_b1);
-        stage(std::integral_constant<int, 1>{}, lds_a1, lds_b1, lds_a0, lds_b0);
-        stage(std::integral_constant<int, 2>{}, lds_a0, lds_b0, lds_a1, lds_b1);
-        stage(std::integral_constant<int, 3>{}, lds_a1, lds_b1, lds_a0, lds_b0);
-      }
-    } else {
-      for (int G = 0; G < total; G += 2) {
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        stage_mma_dma<S>(lds_a0, lds_b0, ra0, rb0, fh, acc, rsrc(la, lna), rsrc(lb, lnb), lds_a1, lds_b1,
-                          voffa, voffb, wave);
-        advance();
-        carry_step();
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        stage_mma_dma<S>(lds_a1, lds_b1, ra0, rb0, fh, acc, rsrc(la, lna), rsrc(lb, lnb), lds_a0, lds_b0,
-                          voffa, voffb, wave);
-        advance();
-        carry_step();
-      }
+    for (int G = 0; G < total; G += 2) {
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      stage_mma_dma<S>(lds_a0, lds_b0, ra0, rb0, fh, acc, rsrc(la, lna), rsrc(lb, lnb), lds_a1, lds_b1,
+                        voffa, voffb, wave);
+      advance();
+      carry_step();
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      stage_mma_dma<S>(lds_a1, lds_b1, ra0, rb0, fh, acc, rsrc(la, lna), rsrc(lb, lnb), lds_a0, lds_b0,
+                        voffa, voffb, wave);
+      advance();
+      carry_step();
     }
     OT* out = (OT*)uniform_ptr((const int8_t*)(cres + (int64_t)cur.mod * m * n + cur.tm * BM * n +
                                                cur.tn * BN));
@@ -1247,7 +1083,7 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_bytes_persistent_kernel(
   __builtin_amdgcn_s_waitcnt(0);  // the last look-ahead (a repeat) lands before the block ends
 }
 
-template <bool BYTES, typename OT, bool MIXED = false>
+template <bool BYTES, typename OT>
 hipError_t launch_gemm(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const int8_t* pb,
                        OT* cres, OT* part, int splits, hipStream_t stream) {
   if (m <= 0 || n <= 0) return hipSuccess;
@@ -1290,10 +1126,10 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const
                              n, kp, pa, pb, dst, group, (uint32_t)blocks);
       } else {
         if (shape == 3)
-          hipLaunchKernelGGL((residue_gemm_persistent_kernel<OT, 3, MIXED>), pgrid, dim3(1024), 0, stream, m, n,
+          hipLaunchKernelGGL((residue_gemm_persistent_kernel<OT, 3>), pgrid, dim3(1024), 0, stream, m, n,
                              kp, pa, pb, dst, group, (uint32_t)blocks);
         else
-          hipLaunchKernelGGL((residue_gemm_persistent_kernel<OT, 2, MIXED>), pgrid, dim3(1024), 0, stream, m, n,
+          hipLaunchKernelGGL((residue_gemm_persistent_kernel<OT, 2>), pgrid, dim3(1024), 0, stream, m, n,
                              kp, pa, pb, dst, group, (uint32_t)blocks);
       }
       return hipGetLastError();
@@ -1308,10 +1144,10 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const
                          pb, dst, splits, group);
   } else {
     if (shape == 3)
-      hipLaunchKernelGGL((residue_gemm_kernel<OT, 3, MIXED>), grid, dim3(1024), 0, stream, m, n, kp, pa, pb,
+      hipLaunchKernelGGL((residue_gemm_kernel<OT, 3>), grid, dim3(1024), 0, stream, m, n, kp, pa, pb,
                          dst, splits, group);
     else
-      hipLaunchKernelGGL((residue_gemm_kernel<OT, 2, MIXED>), grid, dim3(1024), 0, stream, m, n, kp, pa, pb,
+      hipLaunchKernelGGL((residue_gemm_kernel<OT, 2>), grid, dim3(1024), 0, stream, m, n, kp, pa, pb,
                          dst, splits, group);
   }
   if (splits > 1) {
@@ -1407,11 +1243,6 @@ hipError_t launch_residue_gemm_i16(int64_t m, int64_t n, int64_t kp, const int8_
                                    const int8_t* pb, int16_t* cres, int16_t* part, int splits,
                                    hipStream_t stream) {
   return launch_gemm<false, int16_t>(m, n, kp, pa, pb, cres, part, splits, stream);
-}
-
-hipError_t launch_residue_gemm_mixed(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const int8_t* pb,
-                                     int16_t* cres, int16_t* part, int splits, hipStream_t stream) {
-  return launch_gemm<false, int16_t, true>(m, n, kp, pa, pb, cres, part, splits, stream);
 }
 
 hipError_t launch_residue_gemm_bytes_i32(int64_t m, int64_t n, int64_t kp, const int8_t* pa,
