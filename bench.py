@@ -5,10 +5,13 @@ MI355X, through the C ABI.
 One step = one full ozaki25_dgemm_ex call: exponent scans, deconstruction of
 both operands into planes, the per-modulus products and the CRT
 reconstruction, on synthetic seeded inputs that are already resident in HBM.
-The headline line is the published 12-modulus set (e4m3 planes, 36 FP8-MFMA
-limb products with FP32 accumulation and the modular epilogue); the same run
-also times the all-byte 15-modulus set of Sec. 5.1 (int8 planes, 15 int8-MFMA
-products) on the same inputs and reports it under "all_byte_set".
+The headline line is the published 12-modulus set: its scale t(k) and its
+results, bit for bit, with the integer product recovered modulo the fifteen
+byte moduli (int8 planes, 15 int8-MFMA products), as the library does for
+either set inside ozaki25_dgemm*.  The same run also times the all-byte
+15-modulus set of Sec. 5.1 (its own, larger t(k)) on the same inputs and
+reports it under "all_byte_set".  "stored_planes" runs each set's own planes
+(the published set: e4m3 limbs, 36 FP8-MFMA products).
 ``--moduli a15`` makes the all-byte set the headline instead; ``--quantiser
 tz`` times the truncating quantiser.  Each set also reports "stored_planes":
 the per-call time of ozaki25_dgemm_planes on planes made once (storage mode
@@ -39,23 +42,29 @@ FP8_PEAK_TOPS = 5000.0
 INT8_PEAK_TOPS = 5000.0
 FP64_PEAK_TFLOPS = 78.6
 
-# per modulus set: products per output, plane bytes per input element,
-# residue bytes per output (the fused path's internal products), peak
+# each modulus set on its own planes (the stage API and stored planes):
+# products per output, plane bytes per input element, residue bytes per
+# output (compact products), peak
 SETS = {
     "s12": dict(id=0, oracle_set=0, r=12, products=36, plane_bytes=30, cres_bytes=24,
                 peak=FP8_PEAK_TOPS, dtype="fp8", moduli="published 12-modulus set",
-                route="e4m3 MFMA, fp32 accumulate", gemm_kernel="residue_gemm_kernel<int16>",
+                gemm_kernel="residue_gemm_kernel<int16>",
                 persistent_kernel="residue_gemm_persistent_kernel<int16>",
                 dec_kernel="deconstruct_kernel<0>+<1>",
-                fused_kernel="fused_pub_kernel", fused_products=30,
                 note="fp8 ops (1 MAC = 2 ops): 36 limb products x 2mnk per launch; peak is the dense fp8 rate"),
     "a15": dict(id=1, oracle_set=1, r=15, products=15, plane_bytes=15, cres_bytes=15,
                 peak=INT8_PEAK_TOPS, dtype="int8", moduli="all-byte 15-modulus set (Sec. 5.1 candidate A)",
-                route="int8 MFMA, int32 accumulate", gemm_kernel="residue_gemm_bytes_kernel<int8>",
+                gemm_kernel="residue_gemm_bytes_kernel<int8>",
                 persistent_kernel="residue_gemm_bytes_persistent_kernel<int8>",
                 dec_kernel="deconstruct_bytes_kernel<0>+<1>",
                 fused_kernel="fused_bytes_kernel", fused_products=15,
                 note="int8 ops (1 MAC = 2 ops): 15 residue products x 2mnk per launch; peak is the dense int8 rate"),
+}
+# what ozaki25_dgemm* run for either set: the byte moduli
+DGEMM = {
+    "s12": dict(SETS["a15"], id=0, oracle_set=0, moduli=SETS["s12"]["moduli"],
+                route="int8 MFMA modulo the 15 byte moduli, int32 accumulate; the published set's t(k) and results"),
+    "a15": dict(SETS["a15"], route="int8 MFMA, int32 accumulate"),
 }
 COUNTER_FILES = {"s12": os.path.join(ROOT, "profiles", "residue_gemm_square_counters.txt"),
                  "a15": os.path.join(ROOT, "profiles", "residue_gemm_bytes_square_counters.txt")}
@@ -140,30 +149,21 @@ def cpu_baseline(A, B, w, rows, cols, cfg):
     flops = 2.0 * rows * cols * w.k
     return {"value": flops / dt / 1e12, "unit": "TFLOPS", "cores": threads, "kind": "oracle",
             "sample": f"{rows} rows of A x {cols} columns of B of the {w.name} workload, full k={w.k} "
-                      f"(exponent scan, quantise, residues, {cfg['r']} int64 residue GEMMs, Garner, "
+                      f"(exponent scan, quantise, residues, {12 if cfg['oracle_set'] == 0 else 15} int64 residue GEMMs, Garner, "
                       f"rounding, exact-product check), {dt:.1f} s on {threads} threads"}
 
 
 def vendor_lowp_gemm(torch, w, cfg, steps):
-    """The vendor library's dense low-precision GEMM on one residue product's
-    shape (m x k times k x n, limb-sized integer data): hipBLASLt e4m3 through
-    torch._scaled_mm for the published set, int8 through torch._int_mm for the
-    all-byte set.  A practical reference for the residue GEMM's rate, not part
-    of the emulated path."""
+    """The vendor library's dense int8 GEMM on one residue product's shape (m x
+    k times k x n, uniform bytes) through torch._int_mm.  A practical
+    reference for the residue GEMM's rate, not part of the emulated path."""
     dev = torch.device("cuda:0")
     g = torch.Generator(device=dev)
     g.manual_seed(7)
-    A = torch.randint(-22, 23, (w.m, w.k), dtype=torch.int8, device=dev, generator=g)
-    Bt = torch.randint(-22, 23, (w.n, w.k), dtype=torch.int8, device=dev, generator=g)
-    if cfg["dtype"] == "fp8":
-        Af = A.to(torch.float32).to(torch.float8_e4m3fn)
-        Bf = Bt.to(torch.float32).to(torch.float8_e4m3fn)
-        one = torch.tensor(1.0, device=dev)
-        fn = lambda: torch._scaled_mm(Af, Bf.t(), scale_a=one, scale_b=one, out_dtype=torch.bfloat16)  # noqa: E731
-        lib_name = "hipBLASLt e4m3 x e4m3 -> bf16 (torch._scaled_mm)"
-    else:
-        fn = lambda: torch._int_mm(A, Bt.t())  # noqa: E731
-        lib_name = "int8 x int8 -> int32 (torch._int_mm)"
+    A = torch.randint(-128, 128, (w.m, w.k), dtype=torch.int8, device=dev, generator=g)
+    Bt = torch.randint(-128, 128, (w.n, w.k), dtype=torch.int8, device=dev, generator=g)
+    fn = lambda: torch._int_mm(A, Bt.t())  # noqa: E731
+    lib_name = "int8 x int8 -> int32 (torch._int_mm)"
     try:
         fn()
         torch.cuda.synchronize()
@@ -184,7 +184,7 @@ def vendor_lowp_gemm(torch, w, cfg, steps):
     tops = 2.0 * w.m * w.n * w.k / (ms * 1e-3) / 1e12
     return {"library": lib_name, "ms_per_call": round(ms, 4), "achieved": round(tops, 3),
             "peak": cfg["peak"], "frac": round(tops / cfg["peak"], 4),
-            "unit": "TFLOP/s" if cfg["dtype"] == "fp8" else "TOP/s"}
+            "unit": "TOP/s"}
 
 
 def time_set(oz, torch, w, Ad, Bd, Cd, cfg, steps, warmup, quant):
@@ -326,7 +326,7 @@ def rates(w, cfg, ms, stages):
                 roof=cfg["peak"] / cfg["products"])
 
 
-def dec_roofline(w, cfg, rt, moduli, scan_ms, dec_ms):
+def dec_roofline(w, cfg, rt, scan_ms, dec_ms):
     if fused(w):
         return {"bound": "hbm", "kernel": None, "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": None, "bytes_per_call": None,
@@ -335,7 +335,7 @@ def dec_roofline(w, cfg, rt, moduli, scan_ms, dec_ms):
     return {"bound": "hbm", "kernel": cfg["dec_kernel"], "achieved": round(rt["dec_gbs"], 1),
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(rt["dec_gbs"] / HBM_PEAK_GBS, 4),
             "bytes_per_call": rt["dec_bytes"], "stage_with_scan_gbs": round(rt["stage_gbs"], 1),
-            **measured_deconstruction(w, moduli, scan_ms, dec_ms)}
+            **measured_deconstruction(w, "a15", scan_ms, dec_ms)}
 
 
 def gemm_kernel_name(w, cfg):
@@ -354,18 +354,15 @@ def gemm_kernel_name(w, cfg):
     return cfg["gemm_kernel"]
 
 
-def gemm_roofline(w, cfg, rt, moduli):
-    unit = "TFLOP/s" if cfg["dtype"] == "fp8" else "TOP/s"
+def gemm_roofline(w, cfg, rt):
     r = {"bound": "mfma", "kernel": cfg["fused_kernel"] if fused(w) else gemm_kernel_name(w, cfg),
-         "achieved": round(rt["gemm_tops"], 2), "peak": cfg["peak"], "unit": unit,
+         "achieved": round(rt["gemm_tops"], 2), "peak": cfg["peak"], "unit": "TOP/s",
          "frac": round(rt["gemm_tops"] / cfg["peak"], 4),
-         "traffic": None if fused(w) else measured_traffic(w, moduli), "ops_per_launch": rt["gemm_ops"],
+         "traffic": None if fused(w) else measured_traffic(w, "a15"), "ops_per_launch": rt["gemm_ops"],
          "note": cfg["note"]}
     if fused(w):
-        r["note"] = (f"storage mode F: {cfg['fused_products']} products x 2mnk per launch, in units of the "
-                     "peak's dtype (the published set: 3 e4m3 digit products per square modulus and one fp16 "
-                     "residue product per nonsquare one, counted twice as fp16 runs at half the fp8 rate); "
-                     "the kernel is bound by converting A (VALU), not by the matrix cores")
+        r["note"] = (f"storage mode F: {cfg['fused_products']} products x 2mnk per launch; the kernel is bound by "
+                     "converting A (VALU), not by the matrix cores")
     return r
 
 
@@ -422,7 +419,7 @@ def main():
         del src, dst
         log("[bench] calibration copy: 1 GiB read, 1 GiB written")
 
-    cfg = SETS[args.moduli]
+    cfg = DGEMM[args.moduli]
     quant = oz.TZ if args.quantiser == "tz" else oz.RN
     log(f"[bench] {cfg['moduli']}: warmup {args.warmup}, timing {args.steps} steps")
     ms, stages, ms_median = time_set(oz, torch, w, Ad, Bd, Cd, cfg, args.steps, args.warmup, quant)
@@ -434,7 +431,7 @@ def main():
     other = None
     if not args.only:
         name = "a15" if args.moduli == "s12" else "s12"
-        ocfg = SETS[name]
+        ocfg = DGEMM[name]
         if C0d is not None:
             Cd.copy_(C0d)
         log(f"[bench] {ocfg['moduli']}: warmup {args.warmup}, timing {args.steps} steps")
@@ -446,8 +443,8 @@ def main():
             "value": round(ort["tflops"], 3), "unit": "TFLOPS", "ms_per_step": round(oms, 4),
             "stage_ms": dict(zip(("scan", "deconstruct", "residue_gemm", "reconstruct"),
                                  [round(x, 4) for x in ostages])),
-            "roofline": gemm_roofline(w, ocfg, ort, name),
-            "roofline_deconstruct": dec_roofline(w, ocfg, ort, name, ostages[0], ostages[1]),
+            "roofline": gemm_roofline(w, ocfg, ort),
+            "roofline_deconstruct": dec_roofline(w, ocfg, ort, ostages[0], ostages[1]),
             "emulation_roof_tflops": round(ort["roof"], 2),
             "emulation_roof_frac": round(ort["tflops"] / ort["roof"], 4),
         }
@@ -518,8 +515,8 @@ def main():
                                f"entries (U-0.5)exp({w.s} N), seed {w.seed}",
                    "m": w.m, "n": w.n, "k": w.k, "moduli": cfg["moduli"], "quantiser": args.quantiser.upper(),
                    "route": cfg["route"]},
-        "roofline": gemm_roofline(w, cfg, rt, args.moduli),
-        "roofline_deconstruct": dec_roofline(w, cfg, rt, args.moduli, scan_ms, dec_ms),
+        "roofline": gemm_roofline(w, cfg, rt),
+        "roofline_deconstruct": dec_roofline(w, cfg, rt, scan_ms, dec_ms),
         "roofline_reconstruct": {"bound": "hbm", "achieved": round(rt["rec_gbs"], 1), "peak": HBM_PEAK_GBS,
                                  "unit": "GB/s", "frac": round(rt["rec_gbs"] / HBM_PEAK_GBS, 4)},
         "stage_ms": {"scan": round(scan_ms, 4), "deconstruct": round(dec_ms, 4), "residue_gemm": round(gemm_ms, 4),

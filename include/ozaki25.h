@@ -179,12 +179,18 @@ ozaki25_status ozaki25_reconstruct(int64_t m, int64_t n, const int32_t* Cres,
                                    ozaki25_moduli_set set, double* C, int64_t ldc,
                                    int subtract, void* stream);
 
-/* Device workspace that ozaki25_dgemm_ex needs for an m x n x k product. */
+/* Device workspace that ozaki25_dgemm_ex needs for an m x n x k product: the
+ * set's own planes, exponents and products. */
 size_t ozaki25_dgemm_workspace_size(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set);
 
 /* Emulated DGEMM C = A B (Alg. 1): both operands deconstructed once into
  * planes in the workspace (storage mode M), the residue products, then the
- * reconstruction.  With n <= 128 and m >= 1024 (tall and skinny: one output
+ * reconstruction.  The set fixes t(k), hence the integers A'B', and so every
+ * bit of the result.  Inside this and the other ozaki25_dgemm* entry points
+ * (ozaki25_dgemm_planes apart) those integers are recovered modulo the
+ * fifteen byte moduli of OZAKI25_MODULI_A15 for either set, whose range
+ * contains the published set's: 15 int8 products in place of 36 FP8 ones,
+ * with the same result.  With n <= 128 and m >= 1024 (tall and skinny: one output
  * tile spans all of B), either set, only B's planes are stored and A is
  * quantised and reduced inside the product kernel (storage mode F for A --
  * the hybrid of Sec. 6.2); the result is the same bit for bit.  The

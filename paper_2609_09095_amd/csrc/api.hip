@@ -81,23 +81,54 @@ size_t products_bytes(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set, i
   return align_up(one) + (sp > 1 ? align_up(one * sp) : 0);
 }
 
-// Storage mode F for A (at most 128 columns, at least kFusedMinRows rows;
-// either set): A is converted inside the product kernel, so the workspace
-// holds no planes of A and the products need no split of k.  B's planes
-// there: the all-byte set's residue planes, or for the published set the
-// 24 digit planes of its fused product (fewer bytes than its 30 planes).
+// Storage mode F for A (at most 128 columns, at least kFusedMinRows rows):
+// A is converted inside the product kernel, so the workspace holds no planes
+// of A and the products need no split of k.
 constexpr int64_t kFusedMinRows = 1024;
-bool fused_a(int64_t m, int64_t n, ozaki25_moduli_set set) {
-  return known_set(set) && n <= 128 && m >= kFusedMinRows;
+bool fused_a(int64_t m, int64_t n) { return n <= 128 && m >= kFusedMinRows; }
+
+// Bytes of the ozaki25_dgemm* workspace: the set's own planes of A (none in
+// storage mode F) and B, both exponents and the residue products.
+size_t workspace_total(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set) {
+  const int64_t kp = k_pad(k);
+  const size_t np = (size_t)num_planes(set);
+  const bool fused = fused_a(m, n);
+  const size_t prod = fused ? align_up((size_t)num_moduli(set) * m * n * cres_elem(set))
+                            : products_bytes(m, n, k, set, nullptr);
+  return (fused ? 0 : align_up(np * m * kp)) + align_up(np * n * kp) + align_up((size_t)m * sizeof(int32_t)) +
+         align_up((size_t)n * sizeof(int32_t)) + prod;
 }
 
-// planes of A and B, exponents, and the residue products: int16 for the
-// published set (|c| <= 0.51 m <= 556), int8 for the all-byte set (|c| <= 128)
+// ozaki25_dgemm* recover the integer product A'B' from its residues modulo
+// the fifteen byte moduli for either set: what a set fixes is t(k) (with the
+// accurate mode its M), which bounds |A'B'| by its M/2, and any coprime
+// moduli whose product covers that range give the same integer and so the
+// same rounded result.  The byte moduli cover the published set's range
+// (2^117.8 against 2^111.8) with 15 int8 products and 15 plane bytes per
+// element where its limb planes take 36 FP8 products and 30 bytes: 8192^3
+// 14.89 -> 7.61 ms, 32768^2 x 1024 update 39.9 -> 25.5 ms, 262144 x 128 x
+// 4096 10.3 -> 7.1 ms, 512^3 61 -> 43 us.  The stage API and stored planes keep the published moduli's own
+// planes.
+constexpr ozaki25_moduli_set kInner = OZAKI25_MODULI_A15;
+constexpr bool byte_moduli_cover_published() {
+  u128 ms = 1, ma = 1;
+  for (int i = 0; i < oz::kR; ++i) ms *= (u128)oz::kModulus[i];
+  for (int i = 0; i < oz::kRA; ++i) ma *= (u128)oz::kModulusA[i];
+  return ma > ms;
+}
+static_assert(byte_moduli_cover_published(), "A'B' of the published set inside the byte moduli's range");
+
+// Offsets inside the workspace: byte planes of A (none in storage mode F)
+// and B, exponents, int8 residue products (|c| <= 128) and, with split-k,
+// the per-split partials.  total is what the set's size function states,
+// which the byte planes of either set fit: the split is lowered where its
+// partials would not.
 Workspace layout(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set) {
   Workspace w;
   const int64_t kp = k_pad(k);
-  const size_t np = (size_t)num_planes(set);
-  const bool fused = fused_a(m, n, set);
+  const size_t np = (size_t)num_planes(kInner);
+  const bool fused = fused_a(m, n);
+  w.total = workspace_total(m, n, k, set);
   size_t off = 0;
   w.planes_a = off;
   off = fused ? off : align_up(off + np * m * kp);
@@ -108,12 +139,11 @@ Workspace layout(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set) {
   w.exps_b = off;
   off = align_up(off + (size_t)n * sizeof(int32_t));
   w.cres = off;
-  const size_t one = align_up((size_t)num_moduli(set) * m * n * cres_elem(set));
-  const size_t prod = fused ? one : products_bytes(m, n, k, set, &w.splits);
-  if (fused) w.splits = 1;
-  w.part = off + one;
-  off += prod;
-  w.total = off;
+  const size_t one = (size_t)num_moduli(kInner) * m * n * cres_elem(kInner);
+  off = align_up(off + one);
+  w.part = off;
+  w.splits = fused ? 1 : oz::residue_gemm_splits((int)kInner, m, n, kp);
+  while (w.splits > 1 && off + align_up(one * w.splits) > w.total) --w.splits;
   return w;
 }
 
@@ -345,7 +375,7 @@ ozaki25_status ozaki25_reconstruct(int64_t m, int64_t n, const int32_t* Cres, co
 
 size_t ozaki25_dgemm_workspace_size(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set) {
   if (!known_set(set) || m < 0 || n < 0 || k < 0) return 0;
-  return layout(m, n, k, set).total;
+  return workspace_total(m, n, k, set);
 }
 
 ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
@@ -389,35 +419,24 @@ ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A
   int8_t* pb = (int8_t*)(base + w.planes_b);
   int32_t* ea = (int32_t*)(base + w.exps_a);
   int32_t* eb = (int32_t*)(base + w.exps_b);
-  void* cres = base + w.cres;
-  void* part = w.splits > 1 ? base + w.part : nullptr;
-  const bool bytes = bytes_set(set);
+  int8_t* cres = (int8_t*)(base + w.cres);
+  int8_t* part = w.splits > 1 ? (int8_t*)(base + w.part) : nullptr;
   const int t = scale_bits(k, set);
   const int64_t kp = k_pad(k);
 
   if (ev) e = hipEventRecord(ev[0], s);
-  if (fused_a(m, n, set)) {
+  if (fused_a(m, n)) {
     // storage mode F for A: its exponent scan (clearing B's column keys on
-    // the side), B's scan and planes (for the published set B's scan only:
-    // its digit planes come with the product), then the products straight
-    // from FP64 A
+    // the side), B's scan and planes, then the products straight from FP64 A
     if (e == hipSuccess) e = oz::launch_scan_rows(m, k, A, lda, t, ea, eb, n, s);
     if (ev && e == hipSuccess) e = hipEventRecord(ev[1], s);
-    if (bytes) {
-      if (e == hipSuccess) e = scan_and_deconstruct(set, quant, 1, n, k, B, ldb, t, eb, pb, s, nullptr, 0, true);
-    } else {
-      if (e == hipSuccess) e = oz::launch_scan_cols(n, k, B, ldb, eb, s);
-      if (e == hipSuccess) e = oz::launch_keys_to_sigma(n, t, eb, s);
-    }
+    if (e == hipSuccess) e = scan_and_deconstruct(kInner, quant, 1, n, k, B, ldb, t, eb, pb, s, nullptr, 0, true);
     if (ev && e == hipSuccess) e = hipEventRecord(ev[2], s);
-    if (e == hipSuccess)
-      e = bytes ? oz::launch_fused_bytes((int)quant, m, n, k, kp, t, A, lda, ea, pb, (int8_t*)cres, s)
-                : oz::launch_fused_pub((int)quant, m, n, k, kp, t, A, lda, ea, B, ldb, eb, pb, (int16_t*)cres, s);
+    if (e == hipSuccess) e = oz::launch_fused_bytes((int)quant, m, n, k, kp, t, A, lda, ea, pb, cres, s);
     if (ev && e == hipSuccess) e = hipEventRecord(ev[3], s);
     const oz::NativeOperands nat{A, lda, B, ldb, k};
     if (e == hipSuccess)
-      e = bytes ? oz::launch_reconstruct_bytes_i8(m, n, (const int8_t*)cres, ea, eb, C, ldc, subtract ? 1 : 0, nat, s)
-                : oz::launch_reconstruct_i16(m, n, (const int16_t*)cres, ea, eb, C, ldc, subtract ? 1 : 0, nat, s);
+      e = oz::launch_reconstruct_bytes_i8(m, n, cres, ea, eb, C, ldc, subtract ? 1 : 0, nat, s);
     if (ev && e == hipSuccess) e = hipEventRecord(ev[4], s);
     if (owned) {
       const hipError_t f = hipFreeAsync(ws, s);
@@ -429,21 +448,15 @@ ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A
   // so the scan stage is empty and the deconstruct stage holds both
   if (ev && e == hipSuccess) e = hipEventRecord(ev[1], s);
   // A's row scan clears B's column keys on the side
-  if (e == hipSuccess) e = scan_and_deconstruct(set, quant, 0, m, k, A, lda, t, ea, pa, s, eb, n);
-  if (e == hipSuccess) e = scan_and_deconstruct(set, quant, 1, n, k, B, ldb, t, eb, pb, s, nullptr, 0, true);
+  if (e == hipSuccess) e = scan_and_deconstruct(kInner, quant, 0, m, k, A, lda, t, ea, pa, s, eb, n);
+  if (e == hipSuccess) e = scan_and_deconstruct(kInner, quant, 1, n, k, B, ldb, t, eb, pb, s, nullptr, 0, true);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[2], s);
-  if (e == hipSuccess)
-    e = bytes ? oz::launch_residue_gemm_bytes_i8(m, n, kp, pa, pb, (int8_t*)cres, (int8_t*)part,
-                                                 w.splits, s)
-              : oz::launch_residue_gemm_i16(m, n, kp, pa, pb, (int16_t*)cres, (int16_t*)part,
-                                            w.splits, s);
+  if (e == hipSuccess) e = oz::launch_residue_gemm_bytes_i8(m, n, kp, pa, pb, cres, part, w.splits, s);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[3], s);
   const int sub = subtract ? 1 : 0;
   // outputs on rows / columns flagged non-finite are re-issued natively
   const oz::NativeOperands nat{A, lda, B, ldb, k};
-  if (e == hipSuccess)
-    e = bytes ? oz::launch_reconstruct_bytes_i8(m, n, (const int8_t*)cres, ea, eb, C, ldc, sub, nat, s)
-              : oz::launch_reconstruct_i16(m, n, (const int16_t*)cres, ea, eb, C, ldc, sub, nat, s);
+  if (e == hipSuccess) e = oz::launch_reconstruct_bytes_i8(m, n, cres, ea, eb, C, ldc, sub, nat, s);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[4], s);
   if (owned) {
     const hipError_t f = hipFreeAsync(ws, s);
@@ -488,7 +501,7 @@ ozaki25_status ozaki25_accurate_exponents(int64_t m, int64_t n, int64_t k, const
 
 size_t ozaki25_dgemm_accurate_workspace_size(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set) {
   if (!known_set(set) || m < 0 || n < 0 || k < 0) return 0;
-  return layout(m, n, k, set).total + acc_layout(m, n, k).bytes;
+  return workspace_total(m, n, k, set) + acc_layout(m, n, k).bytes;
 }
 
 ozaki25_status ozaki25_dgemm_accurate(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
@@ -529,10 +542,9 @@ ozaki25_status ozaki25_dgemm_accurate(int64_t m, int64_t n, int64_t k, const dou
   int8_t* pb = (int8_t*)(base + w.planes_b);
   int32_t* ea = (int32_t*)(base + w.exps_a);
   int32_t* eb = (int32_t*)(base + w.exps_b);
-  void* cres = base + w.cres;
-  void* part = w.splits > 1 ? base + w.part : nullptr;
-  const bool bytes = bytes_set(set);
-  const bool fused = fused_a(m, n, set);
+  int8_t* cres = (int8_t*)(base + w.cres);
+  int8_t* part = w.splits > 1 ? (int8_t*)(base + w.part) : nullptr;
+  const bool fused = fused_a(m, n);
   const int64_t kp = k_pad(k);
   const int sub = subtract ? 1 : 0;
   const oz::NativeOperands nat{A, lda, B, ldb, k};
@@ -542,25 +554,15 @@ ozaki25_status ozaki25_dgemm_accurate(int64_t m, int64_t n, int64_t k, const dou
   if (e == hipSuccess) e = accurate_exponents(set, m, n, k, A, lda, B, ldb, ea, eb, base + w.total, aw, s);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[1], s);
   if (e == hipSuccess && !fused)
-    e = oz::launch_deconstruct((int)set, (int)quant, 0, m, m, k, kp, kAccurateT, A, lda, ea, false, pa, s);
-  // (the published set's fused product makes B's digit planes itself)
-  if (e == hipSuccess && (bytes || !fused))
-    e = oz::launch_deconstruct((int)set, (int)quant, 1, n, n, k, kp, kAccurateT, B, ldb, eb, false, pb, s);
-  if (ev && e == hipSuccess) e = hipEventRecord(ev[2], s);
-  if (e == hipSuccess) {
-    if (fused && bytes)
-      e = oz::launch_fused_bytes((int)quant, m, n, k, kp, kAccurateT, A, lda, ea, pb, (int8_t*)cres, s);
-    else if (fused)
-      e = oz::launch_fused_pub((int)quant, m, n, k, kp, kAccurateT, A, lda, ea, B, ldb, eb, pb, (int16_t*)cres, s);
-    else if (bytes)
-      e = oz::launch_residue_gemm_bytes_i8(m, n, kp, pa, pb, (int8_t*)cres, (int8_t*)part, w.splits, s);
-    else
-      e = oz::launch_residue_gemm_i16(m, n, kp, pa, pb, (int16_t*)cres, (int16_t*)part, w.splits, s);
-  }
-  if (ev && e == hipSuccess) e = hipEventRecord(ev[3], s);
+    e = oz::launch_deconstruct((int)kInner, (int)quant, 0, m, m, k, kp, kAccurateT, A, lda, ea, false, pa, s);
   if (e == hipSuccess)
-    e = bytes ? oz::launch_reconstruct_bytes_i8(m, n, (const int8_t*)cres, ea, eb, C, ldc, sub, nat, s)
-              : oz::launch_reconstruct_i16(m, n, (const int16_t*)cres, ea, eb, C, ldc, sub, nat, s);
+    e = oz::launch_deconstruct((int)kInner, (int)quant, 1, n, n, k, kp, kAccurateT, B, ldb, eb, false, pb, s);
+  if (ev && e == hipSuccess) e = hipEventRecord(ev[2], s);
+  if (e == hipSuccess)
+    e = fused ? oz::launch_fused_bytes((int)quant, m, n, k, kp, kAccurateT, A, lda, ea, pb, cres, s)
+              : oz::launch_residue_gemm_bytes_i8(m, n, kp, pa, pb, cres, part, w.splits, s);
+  if (ev && e == hipSuccess) e = hipEventRecord(ev[3], s);
+  if (e == hipSuccess) e = oz::launch_reconstruct_bytes_i8(m, n, cres, ea, eb, C, ldc, sub, nat, s);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[4], s);
   if (owned) {
     const hipError_t f = hipFreeAsync(ws, s);
@@ -636,7 +638,7 @@ ozaki25_status ozaki25_dgemm_noalloc(int64_t m, int64_t n, int64_t k, const doub
   if (k == 0)
     return ozaki25_dgemm_ex(m, n, k, A, lda, B, ldb, C, ldc, set, quant, subtract, nullptr, 0, nullptr,
                             stream);
-  if (layout(m, n, k, set).total > kNoallocBytes) return OZAKI25_ERR_WORKSPACE;
+  if (workspace_total(m, n, k, set) > kNoallocBytes) return OZAKI25_ERR_WORKSPACE;
   void* ws = nullptr;
   if (scratch_address(&ws) != hipSuccess) return OZAKI25_ERR_HIP;
   return ozaki25_dgemm_ex(m, n, k, A, lda, B, ldb, C, ldc, set, quant, subtract, ws, kNoallocBytes,

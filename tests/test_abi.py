@@ -176,3 +176,11 @@ def test_noalloc_limit_is_checked_on_the_host():
     assert L.ozaki25_dgemm_noalloc(0, n, k, fake, k, fake, n, fake, n, oz.S12, oz.RN, 0, None) == oz.SUCCESS
     for s in (oz.S12, oz.A15):
         assert oz.ozaki25_dgemm_workspace_size(1024, 1024, 1024, s) <= oz.NOALLOC_SCRATCH_BYTES
+
+
+@pytest.mark.parametrize("m, n, k", [(1, 1, 1), (64, 64, 64), (256, 256, 8192), (1500, 1500, 3000), (16, 16, 32768),
+                                     (1024, 128, 4096), (1023, 128, 4096), (8192, 8192, 8192)])
+def test_published_workspace_holds_the_byte_planes(m, n, k):
+    """ozaki25_dgemm* run the byte moduli inside a workspace of the published
+    set's size: it is never smaller than the all-byte set's own."""
+    assert oz.ozaki25_dgemm_workspace_size(m, n, k, oz.S12) >= oz.ozaki25_dgemm_workspace_size(m, n, k, oz.A15)
