@@ -57,13 +57,18 @@ constexpr int log2_exact(int m) { return m <= 1 ? 0 : 1 + log2_exact(m / 2); }
 
 // Residue modes (the template parameter RM below), by the range of the
 // scaled integers y = RN(x 2^sigma), |y| <= 2^t:
-//  1: nearest quotient, ylo = y mod 2^32 from y + kMagic      (|y| <= 2^51)
-//  2: nearest quotient, ylo split off by one exact FMA        (|y| <= 2^52,
+//  1: ylo = y mod 2^32 from y + kMagic                        (|y| <= 2^51)
+//  2: ylo split off by one exact FMA                          (|y| <= 2^52,
 //     the odd byte moduli only)
-//  3: quotient within one of the nearest, ylo split off, one correction
-//     each way                                                (|y| <= 2^58)
+//  3: y first reduced modulo the product N of a group of moduli, which keeps
+//     every residue of the group and brings it into mode 1's range
+//                                                             (|y| <= 2^58)
 // 2^58 bounds every scale the library uses (t(k) <= 58 for both sets, and
-// the accurate mode's shifts are capped there).
+// the accurate mode's shifts are capped there).  One reduction per group of
+// four (published) or five (byte) moduli costs four FP64 instructions per
+// element; correcting each modulus's quotient instead cost seven each
+// (whole calls: 1537 x 2049 x 1031 on the byte moduli at t = 53 167 -> 157 us,
+// accurate mode at 4096^3 1331 -> 1301 us).
 //
 // y - q M modulo 2^24 for the FMA quotient q (ylo = y mod 2^32).  For odd M
 // the FMA rounds y RN(1/M) + kMagic once, to kMagic + the integer nearest
@@ -73,11 +78,9 @@ constexpr int log2_exact(int m) { return m <= 1 ? 0 : 1 + log2_exact(m / 2); }
 // from a half integer, so the integer is the nearest quotient q and the low
 // word of the sum is q mod 2^32.  For the odd byte moduli (M <= 255,
 // ulp(1/M) / 2 = 2^-61) this holds up to |y| <= 2^52: the error is at most
-// 2^-9 < 1/510.  Up to |y| <= 2^58 (every odd modulus here has
-// ulp(1/M) / 2 <= 2^-61) the error is at most 1/8, so q is within 5/8 of
-// y / M: |y - q M| <= 5 M / 8, one correction from the centred range.  The
-// 24-bit multiply-add gives y - q M mod 2^24.  For a power of two M, y
-// itself (mod 2^24) serves: its low log2(M) bits are the residue.
+// 2^-9 < 1/510.  The 24-bit multiply-add gives y - q M mod 2^24.  For a
+// power of two M, y itself (mod 2^24) serves: its low log2(M) bits are the
+// residue.
 template <int M>
 __device__ __forceinline__ int residue_low(double y, uint32_t ylo) {
   if constexpr ((M & (M - 1)) == 0) {
@@ -95,24 +98,49 @@ __device__ __forceinline__ int residue_low(double y, uint32_t ylo) {
 // Centred residue of the integer-valued y modulo M, in [-(M/2), (M-1)/2]
 // (an int, |residue| <= 544): the low bits of residue_low, sign-extended --
 // log2(M) bits for a power of two (the two's complement field is
-// [-M/2, M/2) by itself), 24 bits for odd M, already centred when q is the
-// nearest quotient (RM 1, 2) and after one correction otherwise (RM 3).
-template <int M, int RM>
+// [-M/2, M/2) by itself), 24 bits for odd M, centred as q is the nearest
+// quotient.
+template <int M>
 __device__ __forceinline__ int centred_residue(double y, uint32_t ylo) {
   if constexpr ((M & (M - 1)) == 0) {
     constexpr int sh = 32 - log2_exact(M);
     return (int)(ylo << sh) >> sh;
   } else {
-    const int r = (int)((uint32_t)residue_low<M>(y, ylo) << 8) >> 8;
-    if constexpr (RM == 3) {
-      constexpr int hi = (M - 1) / 2, lo = hi - M + 1;
-      const int r1 = r > hi ? r - M : r;
-      return r1 < lo ? r1 + M : r1;
-    } else {
-      return r;
-    }
+    return (int)((uint32_t)residue_low<M>(y, ylo) << 8) >> 8;
   }
 }
+
+// Mode 3: y modulo N, |result| <= N (1/2 + 2^-12), and its low word.  The
+// quotient's error is at most |y| 2^-52 / N; y - q N is an integer below
+// 2^48, so the one FMA gives it exactly.
+template <typename Vec, typename Lo>
+__device__ __forceinline__ void reduce_group(const Vec& y, double N, double ninv, Vec& z, Lo& zlo) {
+#pragma unroll
+  for (int c = 0; c < kElems; ++c) {
+    const double q = __builtin_rint(y[c] * ninv);
+    z[c] = __builtin_fma(-q, N, y[c]);
+    zlo[c] = low_word(z[c] + kMagic);
+  }
+}
+// the product of moduli i .. i + count - 1, below 2^48 and at least 2^30
+// (so q N is within 2^-12 N of y at |y| <= 2^58)
+template <int R>
+constexpr int64_t group_product(const int (&m)[R], int i, int count) {
+  int64_t p = 1;
+  for (int j = i; j < i + count; ++j) p *= m[j];
+  return p;
+}
+constexpr int kGroup = 4, kGroupA = 5;  // moduli per group, published / byte set
+template <int R>
+constexpr bool groups_in_range(const int (&m)[R], int count) {
+  if (R % count) return false;
+  for (int i = 0; i < R; i += count) {
+    const int64_t p = group_product(m, i, count);
+    if (p >= (int64_t)1 << 48 || p < (int64_t)1 << 30) return false;
+  }
+  return true;
+}
+static_assert(groups_in_range(kModulus, kGroup) && groups_in_range(kModulusA, kGroupA), "mode 3 groups");
 
 // Square modulus s^2 (Eq. (pieces) with base s): d0 = centred d mod s (the
 // balanced digit, [-16, 15] for s = 32), d1 = (d - d0) / s.  |d| <= 544, so
@@ -171,7 +199,7 @@ __device__ __forceinline__ void gather_planes(uint32_t x0, uint32_t x1, uint32_t
   p2 = __builtin_amdgcn_perm(u23, u01, 0x05040100u);
 }
 
-template <int I, int RM>
+template <int I>
 __device__ __forceinline__ void emit_modulus(const double (&y)[kElems], const uint32_t (&ylo)[kElems],
                                              int8_t* planes,
                                              int64_t plane_stride, int64_t off,
@@ -184,13 +212,13 @@ __device__ __forceinline__ void emit_modulus(const double (&y)[kElems], const ui
     float l0[kElems], l1[kElems];
 #pragma unroll
     for (int c = 0; c < kElems; ++c)
-      split_square<S>((float)centred_residue<M, RM>(y[c], ylo[c]), l0[c], l1[c]);
+      split_square<S>((float)centred_residue<M>(y[c], ylo[c]), l0[c], l1[c]);
     store16(base, l0);
     store16(base + plane_stride, l1);
   } else {
     uint32_t x[kElems];
 #pragma unroll
-    for (int c = 0; c < kElems; ++c) x[c] = lut[centred_residue<M, RM>(y[c], ylo[c]) + 256];
+    for (int c = 0; c < kElems; ++c) x[c] = lut[centred_residue<M>(y[c], ylo[c]) + 256];
     uint4 w0, w1, w2;
     gather_planes(x[0], x[1], x[2], x[3], w0.x, w1.x, w2.x);
     gather_planes(x[4], x[5], x[6], x[7], w0.y, w1.y, w2.y);
@@ -202,11 +230,31 @@ __device__ __forceinline__ void emit_modulus(const double (&y)[kElems], const ui
   }
 }
 
-template <int RM, int... I>
-__device__ __forceinline__ void emit_all(std::integer_sequence<int, I...>, const double (&y)[kElems],
-                                         const uint32_t (&ylo)[kElems], int8_t* planes,
-                                         int64_t plane_stride, int64_t off, const uint32_t* lut) {
-  (emit_modulus<I, RM>(y, ylo, planes, plane_stride, off, lut), ...);
+// moduli FIRST + I...
+template <int FIRST, int... I>
+__device__ __forceinline__ void emit_some(std::integer_sequence<int, I...>, const double (&y)[kElems],
+                                          const uint32_t (&ylo)[kElems], int8_t* planes,
+                                          int64_t plane_stride, int64_t off, const uint32_t* lut) {
+  (emit_modulus<FIRST + I>(y, ylo, planes, plane_stride, off, lut), ...);
+}
+template <int RM>
+__device__ __forceinline__ void emit_all(const double (&y)[kElems], const uint32_t (&ylo)[kElems],
+                                         int8_t* planes, int64_t plane_stride, int64_t off,
+                                         const uint32_t* lut) {
+  if constexpr (RM != 3) {
+    emit_some<0>(std::make_integer_sequence<int, kR>{}, y, ylo, planes, plane_stride, off, lut);
+  } else {
+    [&]<int... G>(std::integer_sequence<int, G...>) {
+      ([&] {
+        constexpr double N = (double)group_product(kModulus, G * kGroup, kGroup);
+        double z[kElems];
+        uint32_t zlo[kElems];
+        reduce_group(y, N, 1.0 / N, z, zlo);
+        emit_some<G * kGroup>(std::make_integer_sequence<int, kGroup>{}, z, zlo, planes, plane_stride, off, lut);
+      }(),
+       ...);
+    }(std::make_integer_sequence<int, kR / kGroup>{});
+  }
 }
 
 // Thread -> (vector, 16-k group), both sides: a block covers 32 vectors x
@@ -272,9 +320,9 @@ __device__ __forceinline__ int load_group(int64_t vecs, int64_t k, const double*
 
 // |x 2^sigma| < 2^t: the scaling is exact, and the quantiser of Eq. (scale)
 // is the one rounding: to nearest even (RN), or toward zero (TZ).  Then
-// ylo = y mod 2^32: from y + kMagic (RM 1, |y| <= 2^51), or (RM 2, 3: past
+// ylo = y mod 2^32: from y + kMagic (RM 1, |y| <= 2^51), or (RM 2: past
 // 2^51 that sum is no longer exact) as y - h 2^32 with h = floor(y 2^-32),
-// one exact FMA.
+// one exact FMA; RM 3 forms it per group (reduce_group).
 template <bool TZ, int RM>
 __device__ __forceinline__ void scale_round(const double (&x)[kElems], int sigma,
                                             double (&y)[kElems], uint32_t (&ylo)[kElems]) {
@@ -284,7 +332,7 @@ __device__ __forceinline__ void scale_round(const double (&x)[kElems], int sigma
     y[c] = TZ ? __builtin_trunc(v) : __builtin_rint(v);
     if constexpr (RM == 1)
       ylo[c] = low_word(y[c] + kMagic);
-    else
+    else if constexpr (RM == 2)
       ylo[c] = (uint32_t)__builtin_fma(-__builtin_floor(y[c] * 0x1p-32), 0x1p32, y[c]);
   }
 }
@@ -309,8 +357,7 @@ __global__ __launch_bounds__(256) void deconstruct_kernel(int64_t vecs, int64_t 
   double y[kElems];
   uint32_t ylo[kElems];
   scale_round<TZ, RM>(x, sigma, y, ylo);
-  emit_all<RM>(std::make_integer_sequence<int, kR>{}, y, ylo, planes, vstride * 128,
-                  plane_offset(vstride, kPlanes, v, g), lut);
+  emit_all<RM>(y, ylo, planes, vstride * 128, plane_offset(vstride, kPlanes, v, g), lut);
 }
 
 // ---- all-byte set (Sec. 5.1, candidate A) on the int8 route: the centred
@@ -326,17 +373,15 @@ __device__ __forceinline__ uint32_t pack_bytes(int a, int b, int c, int d) {
   return __builtin_amdgcn_perm(cd, ab, 0x05040100u);
 }
 
-// The byte of the centred residue: its low eight bits, which residue_low
-// already holds when q is the nearest quotient (RM 1, 2).
-template <int I, int RM>
+// The byte of the centred residue: the low eight bits of residue_low.
+template <int I>
 __device__ __forceinline__ void emit_byte_modulus(const double (&y)[kElems],
                                                   const uint32_t (&ylo)[kElems], int8_t* planes,
                                                   int64_t plane_stride, int64_t off) {
   constexpr int M = kModulusA[I];
   int r[kElems];
 #pragma unroll
-  for (int c = 0; c < kElems; ++c)
-    r[c] = RM == 3 ? centred_residue<M, 3>(y[c], ylo[c]) : residue_low<M>(y[c], ylo[c]);
+  for (int c = 0; c < kElems; ++c) r[c] = residue_low<M>(y[c], ylo[c]);
   uint4 w;
   w.x = pack_bytes(r[0], r[1], r[2], r[3]);
   w.y = pack_bytes(r[4], r[5], r[6], r[7]);
@@ -345,12 +390,30 @@ __device__ __forceinline__ void emit_byte_modulus(const double (&y)[kElems],
   put16(planes + (int64_t)I * plane_stride + off, w);
 }
 
-template <int RM, int... I>
-__device__ __forceinline__ void emit_all_bytes(std::integer_sequence<int, I...>,
-                                               const double (&y)[kElems],
-                                               const uint32_t (&ylo)[kElems], int8_t* planes,
-                                               int64_t plane_stride, int64_t off) {
-  (emit_byte_modulus<I, RM>(y, ylo, planes, plane_stride, off), ...);
+template <int FIRST, int... I>
+__device__ __forceinline__ void emit_some_bytes(std::integer_sequence<int, I...>, const double (&y)[kElems],
+                                                const uint32_t (&ylo)[kElems], int8_t* planes,
+                                                int64_t plane_stride, int64_t off) {
+  (emit_byte_modulus<FIRST + I>(y, ylo, planes, plane_stride, off), ...);
+}
+template <int RM>
+__device__ __forceinline__ void emit_all_bytes(const double (&y)[kElems], const uint32_t (&ylo)[kElems],
+                                               int8_t* planes, int64_t plane_stride, int64_t off) {
+  if constexpr (RM != 3) {
+    emit_some_bytes<0>(std::make_integer_sequence<int, kRA>{}, y, ylo, planes, plane_stride, off);
+  } else {
+    [&]<int... G>(std::integer_sequence<int, G...>) {
+      ([&] {
+        constexpr double N = (double)group_product(kModulusA, G * kGroupA, kGroupA);
+        double z[kElems];
+        uint32_t zlo[kElems];
+        reduce_group(y, N, 1.0 / N, z, zlo);
+        emit_some_bytes<G * kGroupA>(std::make_integer_sequence<int, kGroupA>{}, z, zlo, planes, plane_stride,
+                                     off);
+      }(),
+       ...);
+    }(std::make_integer_sequence<int, kRA / kGroupA>{});
+  }
 }
 
 // RM: the residue mode (1, 2 or 3, as for residue_low).
@@ -370,8 +433,7 @@ __global__ __launch_bounds__(256) void deconstruct_bytes_kernel(int64_t vecs, in
   uint32_t ylo[kElems];
   const int sigma = load_group<SIDE>(vecs, k, X, ldx, exps, keys_in, t, v, k0, true, x);
   scale_round<TZ, RM>(x, sigma, y, ylo);
-  emit_all_bytes<RM>(std::make_integer_sequence<int, kRA>{}, y, ylo, planes, vstride * 128,
-                            plane_offset(vstride, kRA, v, g));
+  emit_all_bytes<RM>(y, ylo, planes, vstride * 128, plane_offset(vstride, kRA, v, g));
 }
 
 // ---- accurate mode (Sec. 2, Eq. (alpha)): the magnitude digit of every
@@ -462,8 +524,8 @@ hipError_t launch_deconstruct(int set, int quant, int side, int64_t vecs, int64_
   if (vecs <= 0 || kp <= 0) return hipSuccess;
   const bool bytes = set == kSetBytes;
   const bool tz = quant == kQuantTZ;
-  // |y| <= 2^t: the nearest quotient with ylo from kMagic, then (the byte
-  // moduli at t = 52) with ylo split off, else one correction
+  // |y| <= 2^t: ylo from kMagic, then (the byte moduli at t = 52) split off,
+  // else y reduced per group of moduli first
   const int mode = t <= (bytes ? 51 : 50) ? 1 : (bytes && t == 52 ? 2 : 3);
   const DecArgs a{((vecs + 31) / 32) * (kp / 128), vecs, vstride, k, kp, X, ldx, exps, keys_in, t, planes};
   if (side == 0) {

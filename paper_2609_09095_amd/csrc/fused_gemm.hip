@@ -49,6 +49,25 @@ __constant__ double kInvF[kRA] = {
     1.0 / kModulusA[8],  1.0 / kModulusA[9],  1.0 / kModulusA[10], 1.0 / kModulusA[11],
     1.0 / kModulusA[12], 1.0 / kModulusA[13], 1.0 / kModulusA[14]};
 
+// mode 3's group products N (below 2^24) and RN(1/N)
+template <int G>
+struct GroupConst {
+  double n[kRA / G], inv[kRA / G];
+};
+template <int G>
+constexpr GroupConst<G> make_groups() {
+  GroupConst<G> r{};
+  for (int i = 0; i < kRA / G; ++i) {
+    double p = 1.0;
+    for (int j = 0; j < G; ++j) p *= kModulusA[i * G + j];
+    r.n[i] = p;
+    r.inv[i] = 1.0 / p;
+  }
+  return r;
+}
+template <int G>
+__constant__ GroupConst<G> kGroupF = make_groups<G>();
+
 constexpr double kMagicF = 6755399441055744.0;  // 1.5 * 2^52
 __device__ __forceinline__ uint32_t lo32(double v) { return (uint32_t)__builtin_bit_cast(uint64_t, v); }
 
@@ -62,32 +81,20 @@ __device__ __forceinline__ uint32_t low32_split(double y) {
 
 // The centred residue of the integer-valued y modulo M, modulo 2^8 (its low
 // byte is the two's complement byte; the higher bits are not defined), with
-// ylo = y mod 2^32.  The FMA rounds y RN(1/M) + 1.5 2^52 once to
-// 1.5 2^52 + q (|y / M| < 2^51: the sum lies where the spacing is 1), and
-// |y RN(1/M) - y/M| <= |y| 2^-61 for the odd M <= 255.
-//  CORR false (|y| <= 2^52): that error is at most 2^-9, below the
-//  1/(2M) >= 1/510 that separates y/M from a half integer, so q is the
-//  nearest quotient and ylo - q M = y - q M (mod 2^32) is the centred
-//  residue, |r| < 128, whose low byte is the two's complement byte.
-//  CORR true (|y| <= 2^58): the error is at most 1/8, so |y - q M| <= 5M/8
-//  and one correction each way centres it (24 bits hold it exactly).
+// ylo = y mod 2^32, |y| <= 2^52.  The FMA rounds y RN(1/M) + 1.5 2^52 once
+// to 1.5 2^52 + q (|y / M| < 2^51: the sum lies where the spacing is 1), and
+// |y RN(1/M) - y/M| <= |y| 2^-61 <= 2^-9 for the odd M <= 255, below the
+// 1/(2M) >= 1/510 that separates y/M from a half integer, so q is the
+// nearest quotient and ylo - q M = y - q M (mod 2^32) is the centred
+// residue, |r| < 128, whose low byte is the two's complement byte.
 // For M = 256 (RN(1/M) taken as 0) q = 0 and the low byte of y is the
-// residue byte; the corrections move it by multiples of 256, which leaves
-// that byte alone.  24-bit products suffice.
-template <bool CORR>
+// residue byte.  24-bit products suffice.
 __device__ __forceinline__ uint32_t residue_byte(double y, uint32_t ylo, int M, double qinv) {
   const uint32_t q = lo32(__builtin_fma(y, qinv, kMagicF));
   // spelled out: left to itself the compiler uses a quarter-rate 32-bit
   // multiply; sext24(q) (-M) + ylo is y - q M modulo 2^24
   uint32_t r;
   asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(q), "s"(-M), "v"(ylo));
-  if constexpr (CORR) {
-    const int hi = (M - 1) / 2;
-    int c = (int)(r << 8) >> 8;
-    c = c > hi ? c - M : c;
-    c = c < hi - M + 1 ? c + M : c;
-    return (uint32_t)c;
-  }
   return r;  // the caller keeps the low byte
 }
 
@@ -152,8 +159,9 @@ __device__ __forceinline__ int cmod_sum(int x, int m, double minv) {
 // the registers: the FP64 slab then feeds five times the matrix work).
 constexpr int FBM = 128;
 // MODE: the residue route by the range of y -- 1: ylo = y + 1.5 2^52
-// (|y| <= 2^51); 2: ylo by low32_split (|y| <= 2^52); 3: low32_split and the
-// corrected quotient (|y| <= 2^58).
+// (|y| <= 2^51); 2: ylo by low32_split (|y| <= 2^52); 3: y first reduced
+// modulo the product of the block's G moduli, which keeps their residues,
+// by one rounded quotient and one exact FMA, then mode 1 (|y| <= 2^58).
 template <int G, int MODE, bool TZ, bool VEC>
 __global__ __launch_bounds__(1024, 1) void fused_bytes_kernel(
     int64_t m, int64_t n, int64_t k, int64_t kp, const double* __restrict__ A, int64_t lda,
@@ -207,6 +215,7 @@ __global__ __launch_bounds__(1024, 1) void fused_bytes_kernel(
     qinv[g] = kInvQ[grp * G + g];
     inv[g] = kInvF[grp * G + g];
   }
+  const double gn = kGroupF<G>.n[grp], gninv = kGroupF<G>.inv[grp];
 
   const int nstage = (int)(kp / FBK);
   // two register sets x0, x1: stage j's values live in x(j % 2), loaded two
@@ -257,7 +266,8 @@ __global__ __launch_bounds__(1024, 1) void fused_bytes_kernel(
       for (int c = 0; c < 4; ++c) {
         const double v = __builtin_ldexp(x[4 * i + c], sg[i]);
         y[c] = TZ ? __builtin_trunc(v) : __builtin_rint(v);
-        ylo[c] = MODE == 1 ? lo32(y[c] + kMagicF) : low32_split(y[c]);
+        if constexpr (MODE == 3) y[c] = __builtin_fma(-__builtin_rint(y[c] * gninv), gn, y[c]);
+        ylo[c] = MODE == 2 ? low32_split(y[c]) : lo32(y[c] + kMagicF);
       }
       const int at = r * FBK + (((ck >> 4) ^ fswz(r)) << 4) + (ck & 15);
 #pragma unroll
@@ -265,11 +275,11 @@ __global__ __launch_bounds__(1024, 1) void fused_bytes_kernel(
         // low bytes of the four residues into one dword (v_perm_b32: bytes
         // 0-3 of the second operand, 4-7 of the first)
         const uint32_t r01 =
-            __builtin_amdgcn_perm(residue_byte<MODE == 3>(y[1], ylo[1], mods[g], qinv[g]),
-                                  residue_byte<MODE == 3>(y[0], ylo[0], mods[g], qinv[g]), 0x0c0c0400u);
+            __builtin_amdgcn_perm(residue_byte(y[1], ylo[1], mods[g], qinv[g]),
+                                  residue_byte(y[0], ylo[0], mods[g], qinv[g]), 0x0c0c0400u);
         const uint32_t r23 =
-            __builtin_amdgcn_perm(residue_byte<MODE == 3>(y[3], ylo[3], mods[g], qinv[g]),
-                                  residue_byte<MODE == 3>(y[2], ylo[2], mods[g], qinv[g]), 0x0c0c0400u);
+            __builtin_amdgcn_perm(residue_byte(y[3], ylo[3], mods[g], qinv[g]),
+                                  residue_byte(y[2], ylo[2], mods[g], qinv[g]), 0x0c0c0400u);
         const uint32_t word = __builtin_amdgcn_perm(r23, r01, 0x05040100u);
         *reinterpret_cast<uint32_t*>(&(buf ? lds_a1 : lds_a0)[g][at]) = word & (keep[i] & kmask);
       }
@@ -394,7 +404,7 @@ hipError_t launch_fused_bytes(int quant, int64_t m, int64_t n, int64_t k, int64_
                               int8_t* cres, hipStream_t stream) {
   if (n > FBN || kp % FBK || m <= 0 || n <= 0 || t > kMaxScaleBits) return hipErrorInvalidValue;
   const bool tz = quant == kQuantTZ;
-  // |y| <= 2^t: the nearest quotient up to 2^52, then the corrected one
+  // |y| <= 2^t: the nearest quotient up to 2^52, then the group reduction
   const int mode = t <= 51 ? 1 : (t == 52 ? 2 : 3);
 #define OZ_FUSED(MODE)                                                                           \
   return tz ? launch_fused_g<3, MODE, true>(m, n, k, kp, A, lda, sigma, pb, cres, stream)       \
