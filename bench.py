@@ -70,7 +70,7 @@ COUNTER_FILES = {"s12": os.path.join(ROOT, "profiles", "residue_gemm_square_coun
                  "a15": os.path.join(ROOT, "profiles", "residue_gemm_bytes_square_counters.txt")}
 GEMM_SOURCE = os.path.join(ROOT, "paper_2609_09095_amd", "csrc", "residue_gemm.hip")
 DEC_COUNTERS = os.path.join(ROOT, "profiles", "deconstruct_square_counters.txt")
-DEC_SOURCES = [os.path.join(ROOT, "paper_2609_09095_amd", "csrc", f) for f in ("scan.hip", "deconstruct.hip")]
+DEC_SOURCES = [os.path.join(ROOT, "paper_2609_09095_amd", "csrc", f) for f in ("scan.hip", "deconstruct.hip", "residues.hpp")]
 
 
 def log(msg):
