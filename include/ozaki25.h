@@ -218,7 +218,9 @@ ozaki25_status ozaki25_dgemm_sub(int64_t m, int64_t n, int64_t k, const double* 
  *   after the reconstruction, for per-stage timing.  The scans run
  *   interleaved with the deconstruction (runs of about 256 MiB of each
  *   operand, each deconstructed right after its scan), so the first two
- *   events are recorded together and the deconstruct stage holds the scans. */
+ *   events are recorded together and the deconstruct stage holds the scans.
+ *   Small products run as one kernel, without the workspace: the first three
+ *   events are recorded before it and the last two after it. */
 ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                                 const double* B, int64_t ldb, double* C, int64_t ldc,
                                 ozaki25_moduli_set set, ozaki25_quantiser quant, int subtract,

@@ -147,6 +147,20 @@ Workspace layout(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set) {
   return w;
 }
 
+// Whether a product runs as one launch (launch_one_kernel) rather than the
+// staged kernels: by the measured times of both, in us.  One launch takes
+// about 2 per 64-k chunk and 4 more, for every round of 256 32 x 32 tiles
+// (a block per CU); the staged path about 26, 14 per 2^20 outputs and 0.3
+// per chunk.  Both sides: 64^3 7.1 / 28.7, 512^3 22.7 / 41.0, 512 x 512 x
+// 768 30.9 / 47.7, 1024 x 1024 x 64 26.3 / 47.7; beyond the line 128 x 128 x
+// 2048 64.3 / 38.5, 2048 x 2048 x 64 98.7 / 86.5.
+bool one_kernel(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb) {
+  if (m > 65536 || n > 65536 || k > 4096 || lda > oz::kOneKernelMaxLd || ldb > oz::kOneKernelMaxLd) return false;
+  const int64_t tiles = ((m + 31) / 32) * ((n + 31) / 32), chunks = (k + 63) / 64;
+  const int64_t rounds = (tiles + 255) / 256;
+  return 10 * rounds * (4 + 2 * chunks) <= 260 + 140 * m * n / (1 << 20) + 3 * chunks;
+}
+
 // Exponent scan and deconstruction of one operand, in runs of whole
 // 256-vector tiles holding about 256 MiB of FP64 each (the size of the
 // MI355X last-level cache): each run's deconstruction reads the run right
@@ -405,6 +419,18 @@ ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A
     return hip_status(e);
   }
 
+  const int t = scale_bits(k, set);
+  if (one_kernel(m, n, k, lda, ldb)) {
+    // no workspace used, but one that is too small is refused all the same
+    if (workspace && (workspace_bytes < workspace_total(m, n, k, set) || ((uintptr_t)workspace & (kAlign - 1))))
+      return OZAKI25_ERR_WORKSPACE;
+    for (int i = 0; ev && e == hipSuccess && i < 3; ++i) e = hipEventRecord(ev[i], s);
+    if (e == hipSuccess)
+      e = oz::launch_one_kernel((int)quant, m, n, k, t, A, lda, B, ldb, C, ldc, subtract ? 1 : 0, s);
+    for (int i = 3; ev && e == hipSuccess && i < OZAKI25_NUM_STAGE_EVENTS; ++i) e = hipEventRecord(ev[i], s);
+    return hip_status(e);
+  }
+
   const Workspace w = layout(m, n, k, set);
   void* ws = workspace;
   bool owned = false;
@@ -421,7 +447,6 @@ ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A
   int32_t* eb = (int32_t*)(base + w.exps_b);
   int8_t* cres = (int8_t*)(base + w.cres);
   int8_t* part = w.splits > 1 ? (int8_t*)(base + w.part) : nullptr;
-  const int t = scale_bits(k, set);
   const int64_t kp = k_pad(k);
 
   if (ev) e = hipEventRecord(ev[0], s);

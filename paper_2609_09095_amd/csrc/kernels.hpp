@@ -73,6 +73,16 @@ hipError_t launch_residue_gemm_bytes_i8(int64_t m, int64_t n, int64_t kp, const 
                                         const int8_t* pb, int8_t* cres, int8_t* part, int splits,
                                         hipStream_t stream);
 
+// The whole product, scans to C, in one launch modulo the byte moduli, for
+// small products; no workspace.  k from 1 to kOneKernelMaxK, lda and ldb at
+// most kOneKernelMaxLd (32-bit offsets within a 64-row chunk); t as for
+// launch_deconstruct.  Outputs on non-finite rows and columns are re-issued
+// natively.
+constexpr int64_t kOneKernelMaxK = 65536, kOneKernelMaxLd = (int64_t)1 << 21;
+hipError_t launch_one_kernel(int quant, int64_t m, int64_t n, int64_t k, int t, const double* A, int64_t lda,
+                             const double* B, int64_t ldb, double* C, int64_t ldc, int subtract,
+                             hipStream_t stream);
+
 // Storage mode F for A (tall/skinny, at most 128 columns; all-byte set):
 // the per-modulus products [15][m][n] (compact int8, as
 // launch_residue_gemm_bytes_i8 writes them) straight from FP64 A, its row
