@@ -215,10 +215,11 @@ ozaki25_status ozaki25_dgemm_sub(int64_t m, int64_t n, int64_t k, const double* 
  * stage_events: NULL, or OZAKI25_NUM_STAGE_EVENTS hipEvent_t handles (passed as
  *   void*) that are recorded on `stream` before the first kernel, after the
  *   exponent scans, after the deconstruction, after the residue products and
- *   after the reconstruction, for per-stage timing.  The scans run
- *   interleaved with the deconstruction (runs of about 256 MiB of each
- *   operand, each deconstructed right after its scan), so the first two
- *   events are recorded together and the deconstruct stage holds the scans.
+ *   after the reconstruction, for per-stage timing.  Operands that do not fit
+ *   the last-level cache together are scanned and deconstructed interleaved
+ *   (runs of about 256 MiB of each operand, each deconstructed right after its
+ *   scan): the first two events are then recorded together and the
+ *   deconstruct stage holds the scans.
  *   Small products run as one kernel, without the workspace: the first three
  *   events are recorded before it and the last two after it. */
 ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,

@@ -148,17 +148,19 @@ Workspace layout(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set) {
 }
 
 // Whether a product runs as one launch (launch_one_kernel) rather than the
-// staged kernels: by the measured times of both, in us.  One launch takes
-// about 2 per 64-k chunk and 4 more, for every round of 256 32 x 32 tiles
-// (a block per CU); the staged path about 26, 14 per 2^20 outputs and 0.3
-// per chunk.  Both sides: 64^3 7.1 / 28.7, 512^3 22.7 / 41.0, 512 x 512 x
-// 768 30.9 / 47.7, 1024 x 1024 x 64 26.3 / 47.7; beyond the line 128 x 128 x
-// 2048 64.3 / 38.5, 2048 x 2048 x 64 98.7 / 86.5.
+// staged kernels: by the measured times of both, in tenths of a us.  One
+// launch takes about 5 us and 2.25 per 64-k chunk for every round of 256
+// 32 x 32 tiles (a block per CU); the staged path about 20, 12.5 per 2^20
+// outputs and 0.75 per chunk, or in storage mode F 22, 2.3 per 2^10 rows and
+// 0.75 per chunk.  Both sides: 64^3 7.1 / 20.1, 512^3 24.3 / 29.7, 512 x 512 x
+// 768 31.7 / 34.8, 1024 x 1024 x 64 26.3 / 35.7, 16384 x 32 x 128 18.0 / 62;
+// beyond the line 256 x 256 x 1024 35.1 / 31.9, 2048 x 2048 x 64 98.6 / 71.9.
 bool one_kernel(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb) {
   if (m > 65536 || n > 65536 || k > 4096 || lda > oz::kOneKernelMaxLd || ldb > oz::kOneKernelMaxLd) return false;
   const int64_t tiles = ((m + 31) / 32) * ((n + 31) / 32), chunks = (k + 63) / 64;
   const int64_t rounds = (tiles + 255) / 256;
-  return 10 * rounds * (4 + 2 * chunks) <= 260 + 140 * m * n / (1 << 20) + 3 * chunks;
+  const int64_t staged = fused_a(m, n) ? 220 + 23 * m / 1024 : 200 + 125 * m * n / (1 << 20);
+  return 2 * rounds * (50 + 22 * chunks) + rounds * chunks <= 2 * staged + 15 * chunks;
 }
 
 // Exponent scan and deconstruction of one operand, in runs of whole
@@ -199,6 +201,18 @@ hipError_t scan_and_deconstruct(ozaki25_moduli_set set, ozaki25_quantiser quant,
   }
   if (side == 1 && e == hipSuccess) e = oz::launch_keys_to_sigma(vecs, t, exps, s);
   return e;
+}
+
+// Whether both operands' scans share one launch and both deconstructions
+// another: the partial column maxima need room (the residues' part of the
+// workspace, unused until the products), and together the operands must fit
+// the last-level cache's 256 MiB, beyond which interleaved runs of one
+// operand at a time are faster (with A converted inside the product kernel,
+// only scanned here, there is no such limit).
+bool both_at_once(int64_t m, int64_t n, int64_t k, const Workspace& w) {
+  const size_t room = w.total - w.cres;
+  return (size_t)oz::scan_both_slabs(n, k) * n * sizeof(uint32_t) <= room &&
+         (fused_a(m, n) || (m + n) * k_pad(k) * (int64_t)sizeof(double) <= (int64_t)256 << 20);
 }
 
 // ---- accurate mode (Sec. 2, Eq. (alpha)) ---------------------------------
@@ -453,9 +467,15 @@ ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A
   if (fused_a(m, n)) {
     // storage mode F for A: its exponent scan (clearing B's column keys on
     // the side), B's scan and planes, then the products straight from FP64 A
-    if (e == hipSuccess) e = oz::launch_scan_rows(m, k, A, lda, t, ea, eb, n, s);
+    const bool both = both_at_once(m, n, k, w);
+    if (e == hipSuccess)
+      e = both ? oz::launch_scan_both(m, n, k, A, lda, B, ldb, t, ea, (uint32_t*)cres, s)
+               : oz::launch_scan_rows(m, k, A, lda, t, ea, eb, n, s);
     if (ev && e == hipSuccess) e = hipEventRecord(ev[1], s);
-    if (e == hipSuccess) e = scan_and_deconstruct(kInner, quant, 1, n, k, B, ldb, t, eb, pb, s, nullptr, 0, true);
+    if (e == hipSuccess)
+      e = both ? oz::launch_deconstruct_bytes_both((int)quant, m, n, k, kp, t, A, lda, ea, nullptr, B, ldb,
+                                                   (const uint32_t*)cres, oz::scan_both_slabs(n, k), eb, pb, s)
+               : scan_and_deconstruct(kInner, quant, 1, n, k, B, ldb, t, eb, pb, s, nullptr, 0, true);
     if (ev && e == hipSuccess) e = hipEventRecord(ev[2], s);
     if (e == hipSuccess) e = oz::launch_fused_bytes((int)quant, m, n, k, kp, t, A, lda, ea, pb, cres, s);
     if (ev && e == hipSuccess) e = hipEventRecord(ev[3], s);
@@ -469,12 +489,22 @@ ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A
     }
     return hip_status(e);
   }
-  // the scans run interleaved with the deconstruction (scan_and_deconstruct),
-  // so the scan stage is empty and the deconstruct stage holds both
-  if (ev && e == hipSuccess) e = hipEventRecord(ev[1], s);
-  // A's row scan clears B's column keys on the side
-  if (e == hipSuccess) e = scan_and_deconstruct(kInner, quant, 0, m, k, A, lda, t, ea, pa, s, eb, n);
-  if (e == hipSuccess) e = scan_and_deconstruct(kInner, quant, 1, n, k, B, ldb, t, eb, pb, s, nullptr, 0, true);
+  if (both_at_once(m, n, k, w)) {
+    uint32_t* part_keys = (uint32_t*)cres;
+    if (e == hipSuccess) e = oz::launch_scan_both(m, n, k, A, lda, B, ldb, t, ea, part_keys, s);
+    if (ev && e == hipSuccess) e = hipEventRecord(ev[1], s);
+    if (e == hipSuccess)
+      e = oz::launch_deconstruct_bytes_both((int)quant, m, n, k, kp, t, A, lda, ea, pa, B, ldb, part_keys,
+                                            oz::scan_both_slabs(n, k), eb, pb, s);
+  } else {
+    // the scans run interleaved with the deconstruction (scan_and_deconstruct),
+    // so the scan stage is empty and the deconstruct stage holds both
+    if (ev && e == hipSuccess) e = hipEventRecord(ev[1], s);
+    // A's row scan clears B's column keys on the side
+    if (e == hipSuccess) e = scan_and_deconstruct(kInner, quant, 0, m, k, A, lda, t, ea, pa, s, eb, n);
+    if (e == hipSuccess)
+      e = scan_and_deconstruct(kInner, quant, 1, n, k, B, ldb, t, eb, pb, s, nullptr, 0, true);
+  }
   if (ev && e == hipSuccess) e = hipEventRecord(ev[2], s);
   if (e == hipSuccess) e = oz::launch_residue_gemm_bytes_i8(m, n, kp, pa, pb, cres, part, w.splits, s);
   if (ev && e == hipSuccess) e = hipEventRecord(ev[3], s);

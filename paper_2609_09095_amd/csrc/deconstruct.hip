@@ -168,11 +168,11 @@ __device__ __forceinline__ void emit_all(const double (&y)[kElems], const uint32
 // consecutive blocks continue the same k-block: the stores sweep each plane
 // region linearly.  Lane l takes vector l%8 and k group l/8 (for B, eight
 // consecutive columns: each FP64 load reads 64 contiguous bytes of 8 rows).
-__device__ __forceinline__ void group_of(int64_t vecs, int64_t& v, int64_t& g) {
+__device__ __forceinline__ void group_of(int64_t block, int64_t vecs, int64_t& v, int64_t& g) {
   const int64_t vb = (vecs + 31) / 32;
   const int lane = threadIdx.x & 63;
-  v = (int64_t)(blockIdx.x % vb) * 32 + (threadIdx.x >> 6) * 8 + (lane & 7);
-  g = (int64_t)(blockIdx.x / vb) * 8 + (lane >> 3);
+  v = (block % vb) * 32 + (threadIdx.x >> 6) * 8 + (lane & 7);
+  g = (block / vb) * 8 + (lane >> 3);
 }
 
 // Byte offset of a thread's 16 plane bytes within plane 0, in the layout
@@ -185,13 +185,10 @@ __device__ __forceinline__ int64_t plane_offset(int64_t vecs, int nplanes, int64
 // addresses, then the mask, so no branches sit around the loads; zeros past
 // k, for inactive threads and for a non-finite vector.  Returns sigma (0 for
 // a non-finite vector).
-// keys_in: exps holds the column scan's exponent keys, turned into sigma here.
 template <int SIDE>
-__device__ __forceinline__ int load_group(int64_t vecs, int64_t k, const double* __restrict__ X,
-                                          int64_t ldx, const int32_t* __restrict__ exps, bool keys_in,
-                                          int t, int64_t v, int64_t k0, bool active, double (&x)[kElems]) {
-  const int raw = active ? exps[v] : 0;
-  int sigma = keys_in ? key_to_sigma((uint32_t)raw, t) : raw;
+__device__ __forceinline__ int load_scaled(int64_t vecs, int64_t k, const double* __restrict__ X, int64_t ldx,
+                                           int sigma, int64_t v, int64_t k0, bool active,
+                                           double (&x)[kElems]) {
   const bool finite = sigma != INT32_MIN;
   sigma = finite ? sigma : 0;
   // lim = last valid c of this group
@@ -223,6 +220,15 @@ __device__ __forceinline__ int load_group(int64_t vecs, int64_t k, const double*
   return sigma;
 }
 
+// sigma from exps (keys_in: the column scan's exponent keys)
+template <int SIDE>
+__device__ __forceinline__ int load_group(int64_t vecs, int64_t k, const double* __restrict__ X,
+                                          int64_t ldx, const int32_t* __restrict__ exps, bool keys_in,
+                                          int t, int64_t v, int64_t k0, bool active, double (&x)[kElems]) {
+  const int raw = active ? exps[v] : 0;
+  return load_scaled<SIDE>(vecs, k, X, ldx, keys_in ? key_to_sigma((uint32_t)raw, t) : raw, v, k0, active, x);
+}
+
 template <int SIDE, int RM, bool TZ>
 __global__ __launch_bounds__(256) void deconstruct_kernel(int64_t vecs, int64_t vstride, int64_t k,
                                                           int64_t kp, const double* __restrict__ X,
@@ -230,7 +236,7 @@ __global__ __launch_bounds__(256) void deconstruct_kernel(int64_t vecs, int64_t 
                                                           bool keys_in, int t,
                                                           int8_t* __restrict__ planes) {
   int64_t v, g;
-  group_of(vecs, v, g);
+  group_of(blockIdx.x, vecs, v, g);
   const bool active = v < vecs && g < kp / kElems;
   const int64_t k0 = g * kElems;
   double x[kElems];
@@ -301,7 +307,7 @@ __global__ __launch_bounds__(256) void deconstruct_bytes_kernel(int64_t vecs, in
                                                                 bool keys_in, int t,
                                                                 int8_t* __restrict__ planes) {
   int64_t v, g;
-  group_of(vecs, v, g);
+  group_of(blockIdx.x, vecs, v, g);
   const bool active = v < vecs && g < kp / kElems;
   if (!active) return;
   const int64_t k0 = g * kElems;
@@ -310,6 +316,55 @@ __global__ __launch_bounds__(256) void deconstruct_bytes_kernel(int64_t vecs, in
   const int sigma = load_group<SIDE>(vecs, k, X, ldx, exps, keys_in, t, v, k0, true, x);
   scale_round<TZ, RM>(x, sigma, y, ylo);
   emit_all_bytes<RM>(y, ylo, planes, vstride * 128, plane_offset(vstride, kRA, v, g));
+}
+
+// Both operands' byte planes in one launch, after scan_both_kernel: blocks
+// below `ablocks` take A (its sigma in ea), the others B, whose column keys
+// they combine from the scan's `slabs` partial maxima (in LDS: 32 vectors x 8
+// threads) and whose first k block writes eb for the reconstruction.
+// ablocks = 0: B alone.
+template <int RM, bool TZ>
+__global__ __launch_bounds__(256) void deconstruct_bytes_both_kernel(
+    int64_t ablocks, int64_t m, int64_t n, int64_t k, int64_t kp, const double* __restrict__ A, int64_t lda,
+    const int32_t* __restrict__ ea, int8_t* __restrict__ pa, const double* __restrict__ B, int64_t ldb,
+    const uint32_t* __restrict__ part, int slabs, int t, int32_t* __restrict__ eb, int8_t* __restrict__ pb) {
+  __shared__ uint32_t keys[8][32];
+  double x[kElems], y[kElems];
+  uint32_t ylo[kElems];
+  int64_t v, g;
+  if (blockIdx.x < ablocks) {
+    group_of(blockIdx.x, m, v, g);
+    if (v >= m) return;
+    const int sigma = load_scaled<0>(m, k, A, lda, ea[v], v, g * kElems, true, x);
+    scale_round<TZ, RM>(x, sigma, y, ylo);
+    emit_all_bytes<RM>(y, ylo, pa, m * 128, plane_offset(m, kRA, v, g));
+    return;
+  }
+  const int64_t block = (int64_t)blockIdx.x - ablocks, vb = (n + 31) / 32;
+  group_of(block, n, v, g);
+  {
+    const int64_t kv = (block % vb) * 32 + (threadIdx.x & 31);
+    uint32_t key = 0;
+    if (kv < n) {
+#pragma unroll 4
+      for (int i = threadIdx.x >> 5; i < slabs; i += 8) {
+        const uint32_t o = part[(int64_t)i * n + kv];
+        key = o > key ? o : key;
+      }
+    }
+    keys[threadIdx.x >> 5][threadIdx.x & 31] = key;
+  }
+  __syncthreads();
+  const int in = (int)(v % 32);  // the thread's vector within the block
+  uint32_t key = keys[0][in];
+#pragma unroll
+  for (int i = 1; i < 8; ++i) key = keys[i][in] > key ? keys[i][in] : key;
+  if (v >= n) return;
+  const int raw = key_to_sigma(key, t);
+  if (g == 0) eb[v] = raw;
+  const int sigma = load_scaled<1>(n, k, B, ldb, raw, v, g * kElems, true, x);
+  scale_round<TZ, RM>(x, sigma, y, ylo);
+  emit_all_bytes<RM>(y, ylo, pb, n * 128, plane_offset(n, kRA, v, g));
 }
 
 // ---- accurate mode (Sec. 2, Eq. (alpha)): the magnitude digit of every
@@ -324,7 +379,7 @@ __global__ __launch_bounds__(256) void digits_kernel(int64_t vecs, int64_t k, in
                                                      const int32_t* __restrict__ exps, bool keys_in,
                                                      int8_t* __restrict__ digits) {
   int64_t v, g;
-  group_of(vecs, v, g);
+  group_of(blockIdx.x, vecs, v, g);
   if (v >= vecs || g >= kp / kElems) return;
   double x[kElems];
   const int ne = load_group<SIDE>(vecs, k, X, ldx, exps, keys_in, 0, v, g * kElems, true, x);
@@ -411,6 +466,29 @@ hipError_t launch_deconstruct(int set, int quant, int side, int64_t vecs, int64_
     if (bytes) launch_side<1, true>(mode, tz, a, stream);
     else launch_side<1, false>(mode, tz, a, stream);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_deconstruct_bytes_both(int quant, int64_t m, int64_t n, int64_t k, int64_t kp, int t,
+                                         const double* A, int64_t lda, const int32_t* ea, int8_t* pa,
+                                         const double* B, int64_t ldb, const uint32_t* part, int64_t slabs,
+                                         int32_t* eb, int8_t* pb, hipStream_t stream) {
+  if (m <= 0 || n <= 0 || kp <= 0 || slabs > INT32_MAX || t > kMaxScaleBits) return hipErrorInvalidValue;
+  const int64_t ablocks = pa ? ((m + 31) / 32) * (kp / 128) : 0;
+  const int64_t blocks = ablocks + ((n + 31) / 32) * (kp / 128);
+  if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+  const bool tz = quant == kQuantTZ;
+  const int mode = t <= 51 ? 1 : (t == 52 ? 2 : 3);  // as in launch_deconstruct
+#define OZ_BOTH(MODE, TZ)                                                                                     \
+  hipLaunchKernelGGL((deconstruct_bytes_both_kernel<MODE, TZ>), dim3((unsigned)blocks), dim3(256), 0, stream, \
+                     ablocks, m, n, k, kp, A, lda, ea, pa, B, ldb, part, (int)slabs, t, eb, pb)
+  if (mode == 1 && tz) OZ_BOTH(1, true);
+  else if (mode == 1) OZ_BOTH(1, false);
+  else if (mode == 2 && tz) OZ_BOTH(2, true);
+  else if (mode == 2) OZ_BOTH(2, false);
+  else if (tz) OZ_BOTH(3, true);
+  else OZ_BOTH(3, false);
+#undef OZ_BOTH
   return hipGetLastError();
 }
 

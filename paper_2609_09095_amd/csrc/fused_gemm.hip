@@ -16,6 +16,7 @@
 // that XCD's L2 for the others.
 #include "kernels.hpp"
 #include "moduli.hpp"
+#include "residues.hpp"
 
 namespace oz {
 namespace {
@@ -68,34 +69,12 @@ constexpr GroupConst<G> make_groups() {
 template <int G>
 __constant__ GroupConst<G> kGroupF = make_groups<G>();
 
-constexpr double kMagicF = 6755399441055744.0;  // 1.5 * 2^52
-__device__ __forceinline__ uint32_t lo32(double v) { return (uint32_t)__builtin_bit_cast(uint64_t, v); }
-
 // y mod 2^32 of an integer-valued y with |y| <= 2^52, where y + 1.5 2^52 is
 // no longer exact: h = floor(y 2^-32) (the scaling is exact), y - h 2^32 in
 // [0, 2^32) by one exact FMA, converted.
 __device__ __forceinline__ uint32_t low32_split(double y) {
   const double h = __builtin_floor(y * 0x1p-32);
   return (uint32_t)__builtin_fma(-h, 0x1p32, y);
-}
-
-// The centred residue of the integer-valued y modulo M, modulo 2^8 (its low
-// byte is the two's complement byte; the higher bits are not defined), with
-// ylo = y mod 2^32, |y| <= 2^52.  The FMA rounds y RN(1/M) + 1.5 2^52 once
-// to 1.5 2^52 + q (|y / M| < 2^51: the sum lies where the spacing is 1), and
-// |y RN(1/M) - y/M| <= |y| 2^-61 <= 2^-9 for the odd M <= 255, below the
-// 1/(2M) >= 1/510 that separates y/M from a half integer, so q is the
-// nearest quotient and ylo - q M = y - q M (mod 2^32) is the centred
-// residue, |r| < 128, whose low byte is the two's complement byte.
-// For M = 256 (RN(1/M) taken as 0) q = 0 and the low byte of y is the
-// residue byte.  24-bit products suffice.
-__device__ __forceinline__ uint32_t residue_byte(double y, uint32_t ylo, int M, double qinv) {
-  const uint32_t q = lo32(__builtin_fma(y, qinv, kMagicF));
-  // spelled out: left to itself the compiler uses a quarter-rate 32-bit
-  // multiply; sext24(q) (-M) + ylo is y - q M modulo 2^24
-  uint32_t r;
-  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(q), "s"(-M), "v"(ylo));
-  return r;  // the caller keeps the low byte
 }
 
 // LDS slabs: rows of 64 bytes (one stage), the 16-byte chunk index XOR-ed
@@ -267,20 +246,16 @@ __global__ __launch_bounds__(1024, 1) void fused_bytes_kernel(
         const double v = __builtin_ldexp(x[4 * i + c], sg[i]);
         y[c] = TZ ? __builtin_trunc(v) : __builtin_rint(v);
         if constexpr (MODE == 3) y[c] = __builtin_fma(-__builtin_rint(y[c] * gninv), gn, y[c]);
-        ylo[c] = MODE == 2 ? low32_split(y[c]) : lo32(y[c] + kMagicF);
+        ylo[c] = MODE == 2 ? low32_split(y[c]) : low_word(y[c] + kMagic);
       }
+      const uint32_t y01 = low_halves(ylo[0], ylo[1]), y23 = low_halves(ylo[2], ylo[3]);
       const int at = r * FBK + (((ck >> 4) ^ fswz(r)) << 4) + (ck & 15);
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        // low bytes of the four residues into one dword (v_perm_b32: bytes
-        // 0-3 of the second operand, 4-7 of the first)
-        const uint32_t r01 =
-            __builtin_amdgcn_perm(residue_byte(y[1], ylo[1], mods[g], qinv[g]),
-                                  residue_byte(y[0], ylo[0], mods[g], qinv[g]), 0x0c0c0400u);
-        const uint32_t r23 =
-            __builtin_amdgcn_perm(residue_byte(y[3], ylo[3], mods[g], qinv[g]),
-                                  residue_byte(y[2], ylo[2], mods[g], qinv[g]), 0x0c0c0400u);
-        const uint32_t word = __builtin_amdgcn_perm(r23, r01, 0x05040100u);
+        // for M = 256 (RN(1/M) taken as 0) q = 0: y's own low bytes
+        const uint32_t word =
+            residue_bytes(y[0], y[1], y[2], y[3], y01, y23,
+                          u16x2{(uint16_t)-mods[g], (uint16_t)-mods[g]}, qinv[g]);
         *reinterpret_cast<uint32_t*>(&(buf ? lds_a1 : lds_a0)[g][at]) = word & (keep[i] & kmask);
       }
     }

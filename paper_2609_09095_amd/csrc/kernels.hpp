@@ -50,6 +50,19 @@ hipError_t launch_deconstruct(int set, int quant, int side, int64_t vecs, int64_
                               int64_t kp, int t, const double* X, int64_t ldx, const int32_t* exps,
                               bool keys_in, int8_t* planes, hipStream_t stream);
 
+// Both operands at once, where launches and not bytes are the cost: the scans
+// of A's rows (sigma into ea) and of B's columns (partial maxima of the
+// exponent keys, scan_both_slabs(n, k) x n uint32, into part) in one launch,
+// and the byte planes of both in another, which also turns the partial
+// maxima into eb.  pa == nullptr: B's planes alone.
+int64_t scan_both_slabs(int64_t n, int64_t k);
+hipError_t launch_scan_both(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, const double* B,
+                            int64_t ldb, int t, int32_t* ea, uint32_t* part, hipStream_t stream);
+hipError_t launch_deconstruct_bytes_both(int quant, int64_t m, int64_t n, int64_t k, int64_t kp, int t,
+                                         const double* A, int64_t lda, const int32_t* ea, int8_t* pa,
+                                         const double* B, int64_t ldb, const uint32_t* part, int64_t slabs,
+                                         int32_t* eb, int8_t* pb, hipStream_t stream);
+
 // Eq. (residueprod): r centred per-modulus products [r][m][n], on FP8 MFMA
 // from limb planes (published set) or int8 MFMA from residue planes
 // (all-byte set).  n must not exceed kMaxResidueCols.

@@ -180,6 +180,15 @@ __device__ __forceinline__ void block_coords(uint32_t id, uint32_t tiles_m, uint
   tn = __builtin_amdgcn_readfirstlane((int)c);
 }
 
+// Block index -> place in the block order.  Blocks are dealt round-robin over
+// the 8 XCDs; with `ranges` each XCD instead takes one contiguous range of
+// the order, so that the few tiles of a modulus meet in one L2.
+__device__ __forceinline__ uint32_t block_place(uint32_t b, uint32_t total, bool ranges) {
+  if (!ranges) return b;
+  const uint32_t x = b & 7, per = total >> 3, rem = total & 7;
+  return x * per + (x < rem ? x : rem) + (b >> 3);
+}
+
 using lds_ptr = __attribute__((address_space(3))) void*;
 
 // Block-uniform values computed with 64-bit VALU arithmetic: pin them to
@@ -785,7 +794,7 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_bytes_kernel(int64_t m, 
                                                                     const int8_t* __restrict__ pb,
                                                                     OT* __restrict__ cres,
                                                                     int splits, int group,
-                                                                    int bt = 0, uint64_t ttop = 0,
+                                                                    int ranges, int bt = 0, uint64_t ttop = 0,
                                                                     int8_t* colpart = nullptr) {
   constexpr int BM = Tile<S>::BM, BN = Tile<S>::BN, NB = Tile<S>::BB, WC = Tile<S>::WC;
   constexpr int NPL = BOUND ? 1 : kRA;  // planes in the layout
@@ -794,10 +803,11 @@ __global__ __launch_bounds__(1024, 1) void residue_gemm_bytes_kernel(int64_t m, 
   __shared__ __attribute__((aligned(1024))) int8_t lds_a1[BM * BK];
   __shared__ __attribute__((aligned(1024))) int8_t lds_b1[BN * BK];
   const int64_t tiles_m = (m + BM - 1) / BM, tiles_n = (n + BN - 1) / BN;
-  const int split = (int)(blockIdx.x % (unsigned)splits);
+  const uint32_t place = block_place(blockIdx.x, gridDim.x, ranges);
+  const int split = (int)(place % (unsigned)splits);
   int mod;
   int64_t tm, tn;
-  block_coords(blockIdx.x / (unsigned)splits, (uint32_t)tiles_m, (uint32_t)tiles_n, (uint32_t)group, mod,
+  block_coords(place / (unsigned)splits, (uint32_t)tiles_m, (uint32_t)tiles_n, (uint32_t)group, mod,
                tm, tn);
   const int mm = kModA[mod];
   cres += (int64_t)split * NPL * m * n;
@@ -942,22 +952,38 @@ __global__ __launch_bounds__(256) void bound_totals_kernel(int64_t m, int64_t n,
 // quotient of an integer below 2^16 by m errs far less than the 1/(2m)
 // that separates it from a half integer for odd m; for even m (1024, 256)
 // the tie +m/2 maps to -m/2.  Grid: x over m n, y over the moduli.
-template <bool BYTES, typename OT>
+// V: values per thread, loaded as one piece (the host takes V > 1 where every
+// slice starts on such a piece); the loads of eight splits in flight.
+template <bool BYTES, typename OT, int V>
 __global__ __launch_bounds__(256) void reduce_splits_kernel(int64_t mn, int splits,
                                                             const OT* __restrict__ part,
                                                             OT* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  typedef OT piece __attribute__((ext_vector_type(V)));
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * V;
   if (i >= mn) return;
   const int q = blockIdx.y;
   const int mm = BYTES ? kModA[q] : kSched[q].m;
   const int64_t stride = (int64_t)(BYTES ? kRA : kR) * mn;
   const int64_t at = (int64_t)q * mn + i;
-  int sum = 0;
-  for (int sp = 0; sp < splits; ++sp) sum += (int)part[sp * stride + at];
-  const float qf = __builtin_rintf((float)sum * (1.0f / (float)mm));
-  int r = sum - (int)qf * mm;
-  r = 2 * r == mm ? -r : r;
-  out[at] = (OT)r;
+  int sum[V] = {};
+  for (int sp = 0; sp < splits; sp += 8) {
+    piece p[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      p[u] = *reinterpret_cast<const piece*>(part + (sp + u < splits ? sp + u : sp) * stride + at);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int j = 0; j < V; ++j) sum[j] += sp + u < splits ? (int)p[u][j] : 0;
+  }
+  piece r;
+#pragma unroll
+  for (int j = 0; j < V; ++j) {
+    const float qf = __builtin_rintf((float)sum[j] * (1.0f / (float)mm));
+    const int c = sum[j] - (int)qf * mm;
+    r[j] = (OT)(2 * c == mm ? -c : c);
+  }
+  *reinterpret_cast<piece*>(out + at) = r;
 }
 
 // Tile shape for n columns, on both routes: at most 128 columns take the
@@ -1136,12 +1162,16 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const
     }
   }
   if constexpr (BYTES) {
+    // few tiles per modulus: one range of the order per XCD (1537 x 2049 x
+    // 1031, 63 tiles, 143 -> 136 us for the call; 1024^3, 16 tiles, 50.0 ->
+    // 47.9; no change at 64 tiles of long k, and 4096^3, 256 tiles, 1 % slower)
+    const int ranges = blocks * splits / kRA <= 128;
     if (shape == 3)
       hipLaunchKernelGGL((residue_gemm_bytes_kernel<OT, 3>), grid, dim3(1024), 0, stream, m, n, kp, pa,
-                         pb, dst, splits, group);
+                         pb, dst, splits, group, ranges);
     else
       hipLaunchKernelGGL((residue_gemm_bytes_kernel<OT, 2>), grid, dim3(1024), 0, stream, m, n, kp, pa,
-                         pb, dst, splits, group);
+                         pb, dst, splits, group, ranges);
   } else {
     if (shape == 3)
       hipLaunchKernelGGL((residue_gemm_kernel<OT, 3>), grid, dim3(1024), 0, stream, m, n, kp, pa, pb,
@@ -1152,9 +1182,13 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const
   }
   if (splits > 1) {
     const int64_t mn = m * n;
-    hipLaunchKernelGGL((reduce_splits_kernel<BYTES, OT>),
-                       dim3((unsigned)((mn + 255) / 256), (unsigned)(BYTES ? kRA : kR)), dim3(256), 0,
-                       stream, mn, splits, part, cres);
+    constexpr int V = 8 / (int)sizeof(OT);
+    const int64_t per = mn % V == 0 && ((uintptr_t)part % 8) == 0 && ((uintptr_t)cres % 8) == 0 ? 256 * V : 256;
+    const dim3 rgrid((unsigned)((mn + per - 1) / per), (unsigned)(BYTES ? kRA : kR));
+    if (per > 256)
+      hipLaunchKernelGGL((reduce_splits_kernel<BYTES, OT, V>), rgrid, dim3(256), 0, stream, mn, splits, part, cres);
+    else
+      hipLaunchKernelGGL((reduce_splits_kernel<BYTES, OT, 1>), rgrid, dim3(256), 0, stream, mn, splits, part, cres);
   }
   return hipGetLastError();
 }
@@ -1215,17 +1249,17 @@ hipError_t launch_bound_gemm(int64_t m, int64_t n, int64_t kp, const int8_t* da,
   if (splits == 1) {
     if (shape == 3)
       hipLaunchKernelGGL((residue_gemm_bytes_kernel<int8_t, 3, true>), grid, dim3(1024), 0, stream, m, n,
-                         kp, da, db, total, 1, group, bt, ttop, colpart);
+                         kp, da, db, total, 1, group, 0, bt, ttop, colpart);
     else
       hipLaunchKernelGGL((residue_gemm_bytes_kernel<int8_t, 2, true>), grid, dim3(1024), 0, stream, m, n,
-                         kp, da, db, total, 1, group, bt, ttop, colpart);
+                         kp, da, db, total, 1, group, 0, bt, ttop, colpart);
   } else {
     if (shape == 3)
       hipLaunchKernelGGL((residue_gemm_bytes_kernel<int32_t, 3, true>), grid, dim3(1024), 0, stream, m, n,
-                         kp, da, db, part, splits, group, bt, ttop);
+                         kp, da, db, part, splits, group, 0, bt, ttop);
     else
       hipLaunchKernelGGL((residue_gemm_bytes_kernel<int32_t, 2, true>), grid, dim3(1024), 0, stream, m, n,
-                         kp, da, db, part, splits, group, bt, ttop);
+                         kp, da, db, part, splits, group, 0, bt, ttop);
     const int64_t groups = (m + 63) / 64;
     if ((n + 255) / 256 > (int64_t)UINT32_MAX || groups > 65535) return hipErrorInvalidValue;
     hipLaunchKernelGGL(bound_totals_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)groups), dim3(256), 0,

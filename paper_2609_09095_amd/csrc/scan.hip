@@ -86,39 +86,12 @@ __device__ __forceinline__ void resident_digits(int64_t vecs, int64_t k, int64_t
         *reinterpret_cast<const uint4*>(dl + 16 * c);
 }
 
-// DIGITS (the accurate mode, Sec. 2, Eq. (alpha)): once the row's exponent
-// e is known, the block reads its row a second time -- from cache: it has
-// just streamed it -- and writes the magnitude digits ceil(16 |x| 2^-e) in
-// {0..16} (0 past k and on a non-finite row) as one int8 plane of the plane
-// layout [kp/128][vecs][128]: each wavefront takes 128-element chunks, a
-// lane two elements 64 apart, so loads and byte stores stay contiguous
-// across the wavefront.
-// DIG: 0 no digits; 1 digits by a second read of the row; 8 or 16 digits
-// from registers (resident_digits<DIG>, chosen by the host for 16-byte
-// aligned rows of at most 512 DIG elements; any other row falls back to the
-// second read).
-template <int DIG>
-__global__ __launch_bounds__(256) void scan_rows_kernel(int64_t vecs, int64_t k, const double* X,
-                                                        int64_t ldx, int t, int32_t* exps,
-                                                        int32_t* zero, int64_t nzero, int64_t kp,
-                                                        int8_t* digits) {
-  __shared__ uint32_t part[4];
-  if (zero) {
-    const int64_t z = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (z < nzero) zero[z] = 0;
-  }
+// The exponent key of a row, by the 256 threads of a block (part: four words
+// of LDS): 16-byte pairs from the row's first 16-byte boundary (head: the
+// elements before it), eight independent loads in flight.
+__device__ __forceinline__ uint32_t row_key(const uint64_t* row, int64_t head, const ulonglong2* body,
+                                            int64_t pairs, int64_t k, uint32_t* part) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t v = blockIdx.x;
-  const uint64_t* row = reinterpret_cast<const uint64_t*>(X + v * ldx);
-  const int64_t head = ((uintptr_t)row & 15) ? 1 : 0;  // elements before the 16-byte boundary
-  const int64_t pairs = (k - head) / 2;
-  const ulonglong2* body = reinterpret_cast<const ulonglong2*>(row + head);
-  if constexpr (DIG >= 8) {
-    if (head == 0 && kp <= 512 * DIG) {
-      resident_digits<DIG>(vecs, k, kp, row, body, pairs, t, exps, digits, part);
-      return;
-    }
-  }
   uint64_t mx[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   int64_t p = threadIdx.x;
   for (; p + 7 * 256 < pairs; p += 8 * 256) {
@@ -153,6 +126,43 @@ __global__ __launch_bounds__(256) void scan_rows_kernel(int64_t vecs, int64_t k,
   __syncthreads();
   uint32_t m = part[0];
   for (int w = 1; w < 4; ++w) m = part[w] > m ? part[w] : m;
+  return m;
+}
+
+// DIGITS (the accurate mode, Sec. 2, Eq. (alpha)): once the row's exponent
+// e is known, the block reads its row a second time -- from cache: it has
+// just streamed it -- and writes the magnitude digits ceil(16 |x| 2^-e) in
+// {0..16} (0 past k and on a non-finite row) as one int8 plane of the plane
+// layout [kp/128][vecs][128]: each wavefront takes 128-element chunks, a
+// lane two elements 64 apart, so loads and byte stores stay contiguous
+// across the wavefront.
+// DIG: 0 no digits; 1 digits by a second read of the row; 8 or 16 digits
+// from registers (resident_digits<DIG>, chosen by the host for 16-byte
+// aligned rows of at most 512 DIG elements; any other row falls back to the
+// second read).
+template <int DIG>
+__global__ __launch_bounds__(256) void scan_rows_kernel(int64_t vecs, int64_t k, const double* X,
+                                                        int64_t ldx, int t, int32_t* exps,
+                                                        int32_t* zero, int64_t nzero, int64_t kp,
+                                                        int8_t* digits) {
+  __shared__ uint32_t part[4];
+  if (zero) {
+    const int64_t z = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (z < nzero) zero[z] = 0;
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t v = blockIdx.x;
+  const uint64_t* row = reinterpret_cast<const uint64_t*>(X + v * ldx);
+  const int64_t head = ((uintptr_t)row & 15) ? 1 : 0;  // elements before the 16-byte boundary
+  const int64_t pairs = (k - head) / 2;
+  const ulonglong2* body = reinterpret_cast<const ulonglong2*>(row + head);
+  if constexpr (DIG >= 8) {
+    if (head == 0 && kp <= 512 * DIG) {
+      resident_digits<DIG>(vecs, k, kp, row, body, pairs, t, exps, digits, part);
+      return;
+    }
+  }
+  const uint32_t m = row_key(row, head, body, pairs, k, part);
   if (threadIdx.x == 0) exps[v] = key_to_sigma(m, t);
   if constexpr (DIG != 0) {
     const int32_t ne = key_to_sigma(m, 0);  // -e, or INT32_MIN
@@ -209,6 +219,49 @@ __global__ __launch_bounds__(256) void scan_cols_kernel(int64_t vecs, int64_t k,
   }
 }
 
+// Both operands' scans in one launch: blocks below m take a row of A each
+// (sigma into ea), the others a slab of 64 columns x rows_per_block rows of B,
+// whose column keys go to part[slab][n] -- plain stores, combined by the
+// deconstruction on load, where atomics would need cleared keys.  Sixteen
+// loads in flight per wavefront: the launch is one latency, not its bytes,
+// at the sizes that take it.
+__global__ __launch_bounds__(256) void scan_both_kernel(int64_t m, int64_t n, int64_t k, const double* A,
+                                                        int64_t lda, const double* B, int64_t ldb, int t,
+                                                        int32_t* ea, int64_t rows_per_block, uint32_t* part) {
+  __shared__ uint32_t lds[4][64];
+  if (blockIdx.x < m) {
+    const int64_t v = blockIdx.x;
+    const uint64_t* row = reinterpret_cast<const uint64_t*>(A + v * lda);
+    const int64_t head = ((uintptr_t)row & 15) ? 1 : 0;
+    const uint32_t key = row_key(row, head, reinterpret_cast<const ulonglong2*>(row + head), (k - head) / 2, k,
+                                 lds[0]);
+    if (threadIdx.x == 0) ea[v] = key_to_sigma(key, t);
+    return;
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t strips = (n + 63) / 64, b = (int64_t)blockIdx.x - m;
+  const int64_t strip = b % strips, kb = b / strips;
+  const int64_t v = strip * 64 + lane;
+  const int64_t l0 = kb * rows_per_block;
+  const int64_t l1 = l0 + rows_per_block < k ? l0 + rows_per_block : k;
+  const uint64_t* col = reinterpret_cast<const uint64_t*>(B) + (v < n ? v : n - 1);
+  uint64_t mx = 0;
+  for (int64_t l = l0 + wave; l < l1; l += 64) {
+    uint64_t a[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) a[u] = col[(l + 4 * u < l1 ? l + 4 * u : l) * ldb];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) mx = (a[u] & kAbsMask) > mx ? (a[u] & kAbsMask) : mx;
+  }
+  lds[wave][lane] = exponent_key(mx);
+  __syncthreads();
+  if (wave == 0 && v < n) {
+    uint32_t key = lds[0][lane];
+    for (int w = 1; w < 4; ++w) key = lds[w][lane] > key ? lds[w][lane] : key;
+    part[kb * n + v] = key;
+  }
+}
+
 __global__ __launch_bounds__(256) void keys_to_sigma_kernel(int64_t vecs, int t, int32_t* exps) {
   const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (v < vecs) exps[v] = key_to_sigma((uint32_t)exps[v], t);
@@ -259,6 +312,24 @@ hipError_t launch_scan_cols(int64_t vecs, int64_t k, const double* X, int64_t ld
   if (kblocks > 0)
     hipLaunchKernelGGL(scan_cols_kernel, dim3((unsigned)(strips * kblocks)), dim3(256), 0, stream,
                        vecs, k, X, ldx, rows_per_block, keys);
+  return hipGetLastError();
+}
+
+int64_t scan_both_slabs(int64_t n, int64_t k) {
+  const int64_t strips = (n + 63) / 64;
+  const int64_t rows = strips * ((k + 63) / 64) <= 1024 ? 64 : 256;
+  return (k + rows - 1) / rows;
+}
+
+hipError_t launch_scan_both(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, const double* B,
+                            int64_t ldb, int t, int32_t* ea, uint32_t* part, hipStream_t stream) {
+  if (m <= 0 || n <= 0 || k <= 0) return hipErrorInvalidValue;
+  const int64_t strips = (n + 63) / 64, slabs = scan_both_slabs(n, k);
+  const int64_t rows = strips * ((k + 63) / 64) <= 1024 ? 64 : 256;
+  const int64_t blocks = m + strips * slabs;
+  if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(scan_both_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, m, n, k, A, lda, B, ldb, t,
+                     ea, rows, part);
   return hipGetLastError();
 }
 
