@@ -7,13 +7,21 @@
 // output tile spans all of B (lambda_A = 1: every element of A is converted
 // once per modulus it serves).
 //
-// A block owns 128 rows of A, all (at most 128) columns and G moduli; its
-// 8 wavefronts convert a 128 x 64 slab per stage (coalesced: 16 lanes per
-// row, 4 consecutive k each), then multiply it with B's slabs on v_mfma_i32_32x32x32_i8
-// (64 x 32 outputs per wavefront), the next slab's FP64 loads in flight
-// meanwhile.  The blocks of one row strip (15 / G of them) are dealt to the
-// same XCD back to back, so the strip's FP64 comes from HBM once and from
-// that XCD's L2 for the others.
+// A block owns 128 rows of A, all (at most 128) columns and G = 5 moduli; its
+// 16 wavefronts convert a 128 x 64 slab per stage, then multiply it with B's
+// slabs on v_mfma_i32_32x32x32_i8 (32 x 32 outputs per wavefront and
+// modulus), the next slab's FP64 loads in flight meanwhile.  The blocks of one
+// row strip (15 / G of them) are dealt to the same XCD back to back, so the
+// strip's FP64 comes from HBM once and from that XCD's L2 for the others.
+//
+// VALU work bounds it (61 % of the cycles with G = 3, the matrix cores 19 %,
+// and the stage barriers keep the two phases apart), and loads, quantising
+// and addresses are paid once per group of moduli: three moduli per block
+// took 5.53 ms at 262144 x 128 x 4096, five 4.64 ms.  Five fit 128 registers
+// (80 accumulators) because a row's FP64 values are reloaded in place as soon
+// as they are converted, one stage ahead (two sets, two stages ahead, were
+// worth 3 % with three moduli), addresses are 32-bit offsets recomputed from
+// the lane index, and no masks are kept.
 #include "kernels.hpp"
 #include "moduli.hpp"
 #include "residues.hpp"
@@ -35,6 +43,10 @@ __constant__ int kModF[kRA] = {kModulusA[0],  kModulusA[1],  kModulusA[2],  kMod
                                kModulusA[4],  kModulusA[5],  kModulusA[6],  kModulusA[7],
                                kModulusA[8],  kModulusA[9],  kModulusA[10], kModulusA[11],
                                kModulusA[12], kModulusA[13], kModulusA[14]};
+__constant__ double kModD[kRA] = {kModulusA[0],  kModulusA[1],  kModulusA[2],  kModulusA[3],
+                                  kModulusA[4],  kModulusA[5],  kModulusA[6],  kModulusA[7],
+                                  kModulusA[8],  kModulusA[9],  kModulusA[10], kModulusA[11],
+                                  kModulusA[12], kModulusA[13], kModulusA[14]};
 // RN(1/m) for the quotient route; 0 for m = 256, whose residue
 // byte is the low byte of y itself
 __constant__ double kInvQ[kRA] = {
@@ -126,22 +138,23 @@ __device__ __forceinline__ void stage_barrier(bool keep_a) {
 }
 
 // Centred residue of an int32 sum modulo m (as cmod_i32 in the residue GEMM).
-__device__ __forceinline__ int cmod_sum(int x, int m, double minv) {
+// m as a double from the table: converted in the kernel it would be held in
+// vector registers across the k loop.
+__device__ __forceinline__ int cmod_sum(int x, double m, double minv) {
   const double xd = (double)x;
   const double q = __builtin_rint(xd * minv);
-  return (int)__builtin_fma(-q, (double)m, xd);
+  return (int)__builtin_fma(-q, m, xd);
 }
 
 // 128 rows of A per block, 16 wavefronts: wavefront w converts rows
 // 8 w .. 8 w + 7 of each slab and owns the 32 x 32 outputs (w / 4, w % 4) of
-// every modulus of its group (one MFMA block each, so that G = 5 moduli fit
-// the registers: the FP64 slab then feeds five times the matrix work).
+// every modulus of its group.
 constexpr int FBM = 128;
 // MODE: the residue route by the range of y -- 1: ylo = y + 1.5 2^52
 // (|y| <= 2^51); 2: ylo by low32_split (|y| <= 2^52); 3: y first reduced
 // modulo the product of the block's G moduli, which keeps their residues,
 // by one rounded quotient and one exact FMA, then mode 1 (|y| <= 2^58).
-template <int G, int MODE, bool TZ, bool VEC>
+template <int G, int MODE, bool TZ, bool BUF>
 __global__ __launch_bounds__(1024, 1) void fused_bytes_kernel(
     int64_t m, int64_t n, int64_t k, int64_t kp, const double* __restrict__ A, int64_t lda,
     const int32_t* __restrict__ sigma, const int8_t* __restrict__ pb, int8_t* __restrict__ cres,
@@ -168,12 +181,11 @@ __global__ __launch_bounds__(1024, 1) void fused_bytes_kernel(
   const int wr = wave >> 2, wc = wave & 3;  // 4 x 4 wavefronts of 32 x 32 outputs
   const int fr = lane & 31, fh = lane >> 5;
 
-  // conversion: lane l takes 4 consecutive k (4 (l % 16) ..) of row
-  // 8 wave + 4 i + l / 16, i = 0, 1: 16 lanes sweep a row's 512 bytes
-  const int ck = 4 * (lane & 15);
+  // conversion: lane l takes k = 2 (l % 16), + 1 and the same 32 on of row
+  // 8 wave + 4 i + l / 16, i = 0, 1: 16 lanes sweep a row's 512 bytes in two
+  // loads of whole cache lines (four consecutive k per lane, each line
+  // touched by both loads, cost 3 %)
   int sg[2];
-  uint32_t keep[2];  // all ones for a live row, 0 past m or for a non-finite row
-  const double* arow_p[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int r = 8 * wave + 4 * i + (lane >> 4);
@@ -181,83 +193,84 @@ __global__ __launch_bounds__(1024, 1) void fused_bytes_kernel(
     const bool ok = arow < m;
     const int sv = ok ? sigma[arow] : 0;
     const bool live = ok && sv != INT32_MIN;
-    keep[i] = live ? 0xFFFFFFFFu : 0u;
     sg[i] = live ? sv : 0;
-    arow_p[i] = A + (ok ? arow : m - 1) * lda;
   }
 
   int mods[G];
-  double qinv[G], inv[G];
+  double qinv[G];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     mods[g] = kModF[grp * G + g];
     qinv[g] = kInvQ[grp * G + g];
-    inv[g] = kInvF[grp * G + g];
   }
   const double gn = kGroupF<G>.n[grp], gninv = kGroupF<G>.inv[grp];
 
   const int nstage = (int)(kp / FBK);
-  // two register sets x0, x1: stage j's values live in x(j % 2), loaded two
-  // stages ahead; x[4 i + c] is row 8 wave + 4 i + lane / 16, k = ck + c
-  double x0[8], x1[8];
-  // x holds the raw values (rows past m or holding a NaN or an infinity,
-  // and k past the end, are masked after the conversion); whole stages take
-  // the 16-byte loads, the last, partial one clamped single loads; full:
-  // stage s is known to lie inside k
-  auto load_a = [&](int s, double (&x)[8], bool full) __attribute__((always_inline)) {
-    const int64_t k0 = (int64_t)s * FBK + 4 * (lane_now() & 15);
-    if (VEC && (full || (int64_t)s * FBK + FBK <= k)) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const double2 p = *reinterpret_cast<const double2*>(arow_p[i] + k0);
-        const double2 q = *reinterpret_cast<const double2*>(arow_p[i] + k0 + 2);
-        x[4 * i] = p.x;
-        x[4 * i + 1] = p.y;
-        x[4 * i + 2] = q.x;
-        x[4 * i + 3] = q.y;
-      }
+  // x[4 i + c]: row 8 wave + 4 i + lane / 16, k = 2 (lane % 16) + c % 2 +
+  // 32 (c / 2) of the next stage to convert; a row's four are reloaded for
+  // the stage after it as soon as they are converted.
+  // x holds the raw values.  Nothing is masked: rows past m feed outputs that
+  // are not stored, rows holding a NaN or an infinity outputs that the
+  // reconstruction replaces, and k past the end meets B's zero padding, so
+  // any residue bytes will do there.  Whole stages take the 16-byte loads,
+  // the last, partial one clamped single loads; full: stage s is known to
+  // lie inside k.
+  // BUF: whole stages read the strip's rows through one buffer resource, at
+  // 32-bit byte offsets from its first row by 24-bit products (the host takes
+  // it for lda < 2^21 only, so 128 rows stay below 2^31 bytes); rows past m
+  // read as zero, and a row may start at any double.
+  const int lda8 = (int)(lda * 8);
+  const int arec = BUF ? (int)((m - row0 < FBM ? m - row0 : FBM) * lda8) : 0;
+  const __amdgpu_buffer_rsrc_t ars = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)uniform_ptr_f((const int8_t*)(A + row0 * lda)), (short)0, arec, 0x00020000);
+  double x[8];
+  auto load_a = [&](int i, int s, bool full) __attribute__((always_inline)) {
+    const int l = lane_now();
+    if (BUF && (full || (int64_t)s * FBK + FBK <= k)) {
+      const int off = __mul24(8 * wave + 4 * i + (l >> 4), lda8) + 16 * (l & 15);
+      const int so = s * FBK * 8;
+      const double2 p = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(ars, off, so, 0));
+      const double2 q = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(ars, off + 256, so, 0));
+      x[4 * i] = p.x;
+      x[4 * i + 1] = p.y;
+      x[4 * i + 2] = q.x;
+      x[4 * i + 3] = q.y;
     } else {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          // clamped into the row; convert zeroes the digits past k
-          x[4 * i + c] = arow_p[i][k0 + c < k ? k0 + c : k - 1];
-        }
-    }
-  };
-  // one dword (4 residue bytes) per row and modulus, written at chunk
-  // ck / 16 of the row, swizzled
-  auto convert = [&](int buf, const double (&x)[8], int t) __attribute__((always_inline)) {
-    // byte c of a digit word is element k0 + c: the bytes at or past k of
-    // the last (partial) stage t are cleared with the dead rows'
-    uint32_t kmask = 0xFFFFFFFFu;
-    if ((int64_t)(t + 1) * FBK > k) {
-      const int64_t rem = k - ((int64_t)t * FBK + ck);
-      kmask = rem >= 4 ? 0xFFFFFFFFu : rem <= 0 ? 0u : 0xFFFFFFFFu >> (32 - 8 * (int)rem);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int r = 8 * wave + 4 * i + (lane >> 4);
-      double y[4];
-      uint32_t ylo[4];
+      const int64_t arow = row0 + 8 * wave + 4 * i + (l >> 4);
+      const double* row = A + (arow < m ? arow : m - 1) * lda;
+      const int64_t k0 = (int64_t)s * FBK + 2 * (l & 15);
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const double v = __builtin_ldexp(x[4 * i + c], sg[i]);
-        y[c] = TZ ? __builtin_trunc(v) : __builtin_rint(v);
-        if constexpr (MODE == 3) y[c] = __builtin_fma(-__builtin_rint(y[c] * gninv), gn, y[c]);
-        ylo[c] = MODE == 2 ? low32_split(y[c]) : low_word(y[c] + kMagic);
+        const int64_t kk = k0 + (c & 1) + 32 * (c >> 1);
+        x[4 * i + c] = row[kk < k ? kk : k - 1];
       }
-      const uint32_t y01 = low_halves(ylo[0], ylo[1]), y23 = low_halves(ylo[2], ylo[3]);
-      const int at = r * FBK + (((ck >> 4) ^ fswz(r)) << 4) + (ck & 15);
+    }
+  };
+  // two byte pairs per row and modulus: k = ck, ck + 1 in chunk ck / 16 of
+  // the row, swizzled, and k + 32 two chunks on
+  auto convert = [&](int i, int buf) __attribute__((always_inline)) {
+    const int l = lane_now(), ck = 2 * (l & 15);
+    const int r = 8 * wave + 4 * i + (l >> 4);
+    double y[4];
+    uint32_t ylo[4];
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        // for M = 256 (RN(1/M) taken as 0) q = 0: y's own low bytes
-        const uint32_t word =
-            residue_bytes(y[0], y[1], y[2], y[3], y01, y23,
-                          u16x2{(uint16_t)-mods[g], (uint16_t)-mods[g]}, qinv[g]);
-        *reinterpret_cast<uint32_t*>(&(buf ? lds_a1 : lds_a0)[g][at]) = word & (keep[i] & kmask);
-      }
+    for (int c = 0; c < 4; ++c) {
+      const double v = __builtin_ldexp(x[4 * i + c], sg[i]);
+      y[c] = TZ ? __builtin_trunc(v) : __builtin_rint(v);
+      if constexpr (MODE == 3) y[c] = __builtin_fma(-__builtin_rint(y[c] * gninv), gn, y[c]);
+      ylo[c] = MODE == 2 ? low32_split(y[c]) : low_word(y[c] + kMagic);
+    }
+    const uint32_t y01 = low_halves(ylo[0], ylo[1]), y23 = low_halves(ylo[2], ylo[3]);
+    const int at = r * FBK + (((ck >> 4) ^ fswz(r)) << 4) + (ck & 15);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      // for M = 256 (RN(1/M) taken as 0) q = 0: y's own low bytes
+      const uint32_t word = residue_bytes(y[0], y[1], y[2], y[3], y01, y23,
+                                          u16x2{(uint16_t)-mods[g], (uint16_t)-mods[g]}, qinv[g]);
+      int8_t* slab = (buf ? lds_a1 : lds_a0)[g];
+      *reinterpret_cast<uint16_t*>(slab + at) = (uint16_t)word;
+      *reinterpret_cast<uint16_t*>(slab + (at ^ 32)) = (uint16_t)(word >> 16);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
   // B's slabs of stage s: for each of the G moduli, 128 rows x 64 bytes,
@@ -267,7 +280,10 @@ __global__ __launch_bounds__(1024, 1) void fused_bytes_kernel(
   const int brecs = __builtin_amdgcn_readfirstlane((int)(n * 128));
   auto load_b = [&](int s, int buf) __attribute__((always_inline)) {
     const int64_t kb = s >> 1, h = s & 1;
-    for (int d = wave; d < 8 * G; d += 16) {
+#pragma unroll
+    for (int j = 0; j < (8 * G + 15) / 16; ++j) {
+      const int d = wave + 16 * j;
+      if (d >= 8 * G) break;
       const int g = d >> 3, dd = d & 7;
       const int mod = grp * G + g;
       const int8_t* piece = uniform_ptr_f(pb + ((kb * kRA + mod) * n) * 128 + h * 64);
@@ -284,62 +300,74 @@ __global__ __launch_bounds__(1024, 1) void fused_bytes_kernel(
 #pragma unroll
   for (int g = 0; g < G; ++g) acc[g] = v16i{};
 
-  // stage s: the loads of stage s + 2 go out, the MFMAs of stage s run on
-  // the LDS buffers cur = s % 2, and stage s + 1 (loaded during stage
-  // s - 1) is converted into the other buffers.
+  // stage s: the MFMAs of stage s run on the LDS buffers cur = s % 2, then
+  // stage s + 1 (loaded during stage s - 1) is converted into the other
+  // buffers, each row's values giving way to its loads of stage s + 2.
   // inner: a stage of the main loop, whose next stage exists and whose
   // look-ahead stage lies inside k. The look-ahead there is unconditional
   // and takes one load path, so that the compiler sees every look-ahead
   // register consumed and keeps the loads in flight across the barrier.
   // B's DMA goes out before A's loads, so that the end-of-stage wait can
   // leave the latter outstanding.
-  auto step = [&](int s, double (&xs)[8], double (&xn)[8], int cur, bool inner)
-                  __attribute__((always_inline)) {
+  auto step = [&](int s, int cur, bool inner) __attribute__((always_inline)) {
     const int nxt = cur ^ 1;
     const bool next = inner || s + 1 < nstage;
     const bool more = inner || s + 2 < nstage;
     if (next) load_b(s + 1, nxt);
-    if (more) load_a(s + 2, xs, inner);
+    // the lane's fragment offsets recomputed (lane_now), not held
+    const int l = lane_now(), r = l & 31, f = l >> 5;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const int8_t* la = (cur ? lds_a1 : lds_a0)[g];
       const int8_t* lb = (cur ? lds_b1 : lds_b0)[g];
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
-        acc[g] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ffrag(la, wr * 32 + fr, ks, fh),
-                                                       ffrag(lb, wc * 32 + fr, ks, fh), acc[g], 0, 0, 0);
+        acc[g] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ffrag(la, wr * 32 + r, ks, f),
+                                                       ffrag(lb, wc * 32 + r, ks, f), acc[g], 0, 0, 0);
       // one modulus's fragments at a time in registers
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (next) convert(nxt, xn, s + 1);
+    if (next) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        // one row's values at a time in registers
+        __builtin_amdgcn_sched_barrier(0);
+        convert(i, nxt);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) load_a(i, s + 2, inner);
+      }
+    }
     if (((s + 1) % kSegF) == 0 && next) {
 #pragma unroll
       for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[g][v] = cmod_sum(acc[g][v], mods[g], inv[g]);
+        for (int v = 0; v < 16; ++v) acc[g][v] = cmod_sum(acc[g][v], kModD[grp * G + g], kInvF[grp * G + g]);
     }
     stage_barrier(more);
   };
 
-  if (nstage > 0) {
-    load_a(0, x0, false);
-    load_b(0, 0);
-    if (nstage > 1) load_a(1, x1, false);
-    convert(0, x0, 0);
+  // (kp is a multiple of 128: at least two stages)
+#pragma unroll
+  for (int i = 0; i < 2; ++i) load_a(i, 0, false);
+  load_b(0, 0);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    convert(i, 0);
+    load_a(i, 1, false);
   }
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  // the main loop runs while both look-ahead stages are full; the last
-  // (at most four) stages take the guarded steps
+  // the main loop runs while the look-ahead stages are full; the last
+  // stages take the guarded steps
   const int nfull = (int)(k / FBK);
   int s = 0;
   for (; s + 3 < nfull; s += 2) {
-    step(s, x0, x1, 0, true);
-    step(s + 1, x1, x0, 1, true);
+    step(s, 0, true);
+    step(s + 1, 1, true);
   }
   for (; s < nstage; s += 2) {
-    step(s, x0, x1, 0, false);
-    if (s + 1 < nstage) step(s + 1, x1, x0, 1, false);
+    step(s, 0, false);
+    if (s + 1 < nstage) step(s + 1, 1, false);
   }
 
   // epilogue: centred residues (+m/2 of m = 256 stores as -128), int8, into
@@ -351,7 +379,7 @@ __global__ __launch_bounds__(1024, 1) void fused_bytes_kernel(
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int64_t row = row0 + wr * 32 + 8 * (v >> 2) + 4 * fh + (v & 3);
-      if (row < m && col < n) out[row * n + col] = (int8_t)cmod_sum(acc[g][v], mods[g], inv[g]);
+      if (row < m && col < n) out[row * n + col] = (int8_t)cmod_sum(acc[g][v], kModD[grp * G + g], kInvF[grp * G + g]);
     }
   }
 }
@@ -362,8 +390,7 @@ hipError_t launch_fused_g(int64_t m, int64_t n, int64_t k, int64_t kp, const dou
   const int64_t strips = (m + FBM - 1) / FBM;
   const int64_t blocks = (strips + 7) / 8 * 8 * (kRA / G);
   if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
-  // 16-byte loads when every row starts 16-byte aligned
-  if ((((uintptr_t)A) & 15) == 0 && (lda & 1) == 0)
+  if (lda < (1 << 21))
     hipLaunchKernelGGL((fused_bytes_kernel<G, MODE, TZ, true>), dim3((unsigned)blocks), dim3(1024), 0,
                        stream, m, n, k, kp, A, lda, sigma, pb, cres, strips);
   else
@@ -377,13 +404,13 @@ hipError_t launch_fused_g(int64_t m, int64_t n, int64_t k, int64_t kp, const dou
 hipError_t launch_fused_bytes(int quant, int64_t m, int64_t n, int64_t k, int64_t kp, int t,
                               const double* A, int64_t lda, const int32_t* sigma, const int8_t* pb,
                               int8_t* cres, hipStream_t stream) {
-  if (n > FBN || kp % FBK || m <= 0 || n <= 0 || t > kMaxScaleBits) return hipErrorInvalidValue;
+  if (n > FBN || kp % 128 || kp <= 0 || m <= 0 || n <= 0 || t > kMaxScaleBits) return hipErrorInvalidValue;
   const bool tz = quant == kQuantTZ;
   // |y| <= 2^t: the nearest quotient up to 2^52, then the group reduction
   const int mode = t <= 51 ? 1 : (t == 52 ? 2 : 3);
 #define OZ_FUSED(MODE)                                                                           \
-  return tz ? launch_fused_g<3, MODE, true>(m, n, k, kp, A, lda, sigma, pb, cres, stream)       \
-            : launch_fused_g<3, MODE, false>(m, n, k, kp, A, lda, sigma, pb, cres, stream)
+  return tz ? launch_fused_g<5, MODE, true>(m, n, k, kp, A, lda, sigma, pb, cres, stream)       \
+            : launch_fused_g<5, MODE, false>(m, n, k, kp, A, lda, sigma, pb, cres, stream)
   if (mode == 1) OZ_FUSED(1);
   if (mode == 2) OZ_FUSED(2);
   OZ_FUSED(3);
