@@ -156,7 +156,7 @@ Workspace layout(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set) {
 // 768 31.7 / 34.8, 1024 x 1024 x 64 26.3 / 35.7, 16384 x 32 x 128 18.0 / 62;
 // beyond the line 256 x 256 x 1024 35.1 / 31.9, 2048 x 2048 x 64 98.6 / 71.9.
 bool one_kernel(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb) {
-  if (m > 65536 || n > 65536 || k > 4096 || lda > oz::kOneKernelMaxLd || ldb > oz::kOneKernelMaxLd) return false;
+  if (m > (1 << 24) || n > (1 << 24) || k > 4096 || lda > oz::kOneKernelMaxLd || ldb > oz::kOneKernelMaxLd) return false;
   const int64_t tiles = ((m + 31) / 32) * ((n + 31) / 32), chunks = (k + 63) / 64;
   const int64_t rounds = (tiles + 255) / 256;
   const int64_t staged = fused_a(m, n) ? 220 + 23 * m / 1024 : 200 + 125 * m * n / (1 << 20);

@@ -219,17 +219,44 @@ __global__ __launch_bounds__(256) void scan_cols_kernel(int64_t vecs, int64_t k,
   }
 }
 
-// Both operands' scans in one launch: blocks below m take a row of A each
-// (sigma into ea), the others a slab of 64 columns x rows_per_block rows of B,
+// Both operands' scans in one launch: blocks below ablocks take a row of A
+// each, or four rows of at most kShortRow elements, a wavefront per row, as a
+// block would spend such a row on starting and joining its wavefronts
+// (262144 rows of 256: 254 -> 161 us; 100000 of 300: 103 -> 58); sigma goes
+// to ea.  The others take a slab of 64 columns x rows_per_block rows of B,
 // whose column keys go to part[slab][n] -- plain stores, combined by the
 // deconstruction on load, where atomics would need cleared keys.  Sixteen
 // loads in flight per wavefront: the launch is one latency, not its bytes,
 // at the sizes that take it.
+constexpr int kShortRow = 1024;
 __global__ __launch_bounds__(256) void scan_both_kernel(int64_t m, int64_t n, int64_t k, const double* A,
                                                         int64_t lda, const double* B, int64_t ldb, int t,
-                                                        int32_t* ea, int64_t rows_per_block, uint32_t* part) {
+                                                        int32_t* ea, int64_t ablocks, int64_t rows_per_block,
+                                                        uint32_t* part) {
   __shared__ uint32_t lds[4][64];
-  if (blockIdx.x < m) {
+  if (blockIdx.x < ablocks) {
+    if (k <= kShortRow) {
+      // a wavefront per row, eight loads in flight
+      const int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+      if (v >= m) return;
+      const uint64_t* row = reinterpret_cast<const uint64_t*>(A + v * lda);
+      const int l = threadIdx.x & 63;
+      const int64_t head = ((uintptr_t)row & 15) ? 1 : 0, pairs = (k - head) / 2;
+      const ulonglong2* body = reinterpret_cast<const ulonglong2*>(row + head);
+      uint64_t mx = l == 0 ? row[0] & kAbsMask : (l == 1 ? row[k - 1] & kAbsMask : 0);
+      ulonglong2 q[kShortRow / 128];
+#pragma unroll
+      for (int u = 0; u < kShortRow / 128; ++u) q[u] = l + 64 * u < pairs ? body[l + 64 * u] : ulonglong2{0, 0};
+#pragma unroll
+      for (int u = 0; u < kShortRow / 128; ++u) {
+        const uint64_t a = q[u].x & kAbsMask, b = q[u].y & kAbsMask;
+        mx = a > mx ? a : mx;
+        mx = b > mx ? b : mx;
+      }
+      const uint32_t key = wave_max(exponent_key(mx));
+      if (l == 0) ea[v] = key_to_sigma(key, t);
+      return;
+    }
     const int64_t v = blockIdx.x;
     const uint64_t* row = reinterpret_cast<const uint64_t*>(A + v * lda);
     const int64_t head = ((uintptr_t)row & 15) ? 1 : 0;
@@ -239,7 +266,7 @@ __global__ __launch_bounds__(256) void scan_both_kernel(int64_t m, int64_t n, in
     return;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t strips = (n + 63) / 64, b = (int64_t)blockIdx.x - m;
+  const int64_t strips = (n + 63) / 64, b = (int64_t)blockIdx.x - ablocks;
   const int64_t strip = b % strips, kb = b / strips;
   const int64_t v = strip * 64 + lane;
   const int64_t l0 = kb * rows_per_block;
@@ -326,10 +353,11 @@ hipError_t launch_scan_both(int64_t m, int64_t n, int64_t k, const double* A, in
   if (m <= 0 || n <= 0 || k <= 0) return hipErrorInvalidValue;
   const int64_t strips = (n + 63) / 64, slabs = scan_both_slabs(n, k);
   const int64_t rows = strips * ((k + 63) / 64) <= 1024 ? 64 : 256;
-  const int64_t blocks = m + strips * slabs;
+  const int64_t ablocks = k <= kShortRow ? (m + 3) / 4 : m;
+  const int64_t blocks = ablocks + strips * slabs;
   if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
   hipLaunchKernelGGL(scan_both_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, m, n, k, A, lda, B, ldb, t,
-                     ea, rows, part);
+                     ea, ablocks, rows, part);
   return hipGetLastError();
 }
 
