@@ -167,7 +167,8 @@ __device__ __forceinline__ double reconstruct_one_a(const RT* rowq, int64_t mn, 
   return garner_bytes(c, -sa - sb);
 }
 
-// Grid: x over 256-column strips, y over rows (strided by gridDim.y).
+// Grid: x over 256-column strips, y over rows (strided by gridDim.y).  (The
+// byte moduli's compact residues come here for small outputs only.)
 template <bool BYTES, typename RT>
 __global__ __launch_bounds__(256) void reconstruct_kernel(int64_t m, int64_t n,
                                                           const RT* __restrict__ cres,
@@ -187,6 +188,75 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(int64_t m, int64_t n,
     // set and 8192^3 unchanged)
     double* out = C + row * ldc + col;
     __builtin_nontemporal_store(subtract ? __builtin_nontemporal_load(out) - r : r, out);
+  }
+}
+
+// The byte moduli's compact residues through LDS: a block takes kRun
+// consecutive outputs in row-major order -- the planes are row-major without
+// gaps, so rows of any length fill every lane -- and brings their kRun bytes
+// of each plane in by LDS-DMA, sixteen bytes a lane.  Byte loads by the
+// threads themselves (64 bytes a wavefront and plane) left too few bytes in
+// flight for the memory's latency.  A thread then takes outputs tid + 256 j,
+// so that C moves in whole lines.  ALIGNED: every plane starts on a dword
+// (m n a multiple of 4); otherwise a plane's bytes start up to three bytes
+// into its slab.
+// With the CRT sum's shorter arithmetic, strips of columns against runs:
+// 32768^2 C -= AB 7.6 -> 5.9 ms (5.6 TB/s), 8192^2 476 -> 413 us, 4096^2 115 ->
+// 94 us, 100000 x 100 114 -> 65 us, 262144 x 8 131 -> 20 us; with Garner's
+// digits runs gained nothing on square outputs.
+constexpr int kRun = 1024, kSlab = kRun + 256;
+using lds_ptr_r = __attribute__((address_space(3))) void*;
+
+template <bool ALIGNED>
+__global__ __launch_bounds__(256) void reconstruct_runs_kernel(int64_t mn, int n, int64_t ldc,
+                                                               const int8_t* __restrict__ cres,
+                                                               const int32_t* __restrict__ ea,
+                                                               const int32_t* __restrict__ eb,
+                                                               double* __restrict__ C, int subtract,
+                                                               double fill) {
+  __shared__ __attribute__((aligned(16))) int8_t slab[kRA * kSlab];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t i0 = (int64_t)blockIdx.x * kRun;
+  for (int q = wave; q < kRA; q += 4) {
+    const int64_t at = q * mn + i0, start = ALIGNED ? at : at & ~(int64_t)3;
+    // reads past the residues give zero; their last dword is read whole (the
+    // residues' buffer is padded to 256 bytes)
+    const int64_t left = (kRA * mn - start + 3) & ~(int64_t)3;
+    const uint64_t v = (uint64_t)(cres + start);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(((uint64_t)hi << 32) | lo), (short)0,
+        __builtin_amdgcn_readfirstlane(left < kSlab ? (int)left : kSlab), 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_r)(slab + q * kSlab), 16, lane * 16, 0, 0, 2);
+    if (!ALIGNED)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_r)(slab + q * kSlab + kRun), 4, kRun + lane * 4, 0, 0, 2);
+  }
+  const int64_t row0 = i0 / n;
+  const int col0 = (int)(i0 - row0 * n);
+  const float rn = 1.0f / (float)n;
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kRun / 256; ++j) {
+    const int o = threadIdx.x + 256 * j;
+    if (i0 + o >= mn) break;
+    // rows onward from row0: below 1024 columns the FP32 quotient of
+    // c + 1/2 (c < 2^11) is off by far less than the 1/(2n) to an integer
+    int col = col0 + o;
+    const int dr = n >= kRun ? (col >= n ? 1 : 0) : (int)(((float)col + 0.5f) * rn);
+    col -= dr * n;
+    const int sa = ea[row0 + dr], sb = eb[col];
+    double* out = C + (row0 + dr) * ldc + col;
+    const double old = subtract ? __builtin_nontemporal_load(out) : 0.0;
+    double r = fill;
+    if (sa != INT32_MIN && sb != INT32_MIN) {
+      int c[kRA];
+#pragma unroll
+      for (int q = 0; q < kRA; ++q)
+        c[q] = slab[q * kSlab + (ALIGNED ? 0 : (int)((q * mn + i0) & 3)) + o];
+      r = garner_bytes(c, -sa - sb);
+    }
+    __builtin_nontemporal_store(subtract ? old - r : r, out);
   }
 }
 
@@ -253,8 +323,23 @@ hipError_t launch_rec(int64_t m, int64_t n, const RT* cres, const int32_t* ea, c
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((reconstruct_kernel<BYTES, RT>), grid, dim3(256), 0, stream, m, n, cres, ea, eb, C,
-                     ldc, subtract, nat.A ? 0.0 : __builtin_nan(""));
+  const double fill = nat.A ? 0.0 : __builtin_nan("");
+  // runs from about one block per CU (2^18 outputs), and wherever strips of
+  // 256 columns leave more than a fifth of their lanes idle; below, strips
+  // (256 x 256: 4.3 us against 5.0)
+  if (BYTES && sizeof(RT) == 1 && (m * n >= 1 << 18 || 4 * (int64_t)grid.x * 256 > 5 * n)) {
+    const int64_t blocks = (m * n + kRun - 1) / kRun;
+    if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+    if (m * n % 4 == 0)
+      hipLaunchKernelGGL(reconstruct_runs_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, m * n, (int)n, ldc,
+                         (const int8_t*)cres, ea, eb, C, subtract, fill);
+    else
+      hipLaunchKernelGGL(reconstruct_runs_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, m * n, (int)n,
+                         ldc, (const int8_t*)cres, ea, eb, C, subtract, fill);
+  } else {
+    hipLaunchKernelGGL((reconstruct_kernel<BYTES, RT>), grid, dim3(256), 0, stream, m, n, cres, ea, eb, C, ldc,
+                       subtract, fill);
+  }
   if (nat.A && !subtract) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

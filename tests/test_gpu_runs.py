@@ -1,0 +1,44 @@
+"""The byte moduli's reconstruction in runs of 1024 outputs: rows shorter than,
+equal to and longer than a run, single rows and columns, a partial last run,
+residue planes on and off a dword boundary, C -= AB and flagged rows and
+columns -- through stored planes, against the oracle, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2609_09095_amd as oz
+import workloads
+from gpu_util import assert_bits_equal, log, require_gpu, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    require_gpu()
+
+
+@pytest.mark.parametrize("m, n, pad", [(257, 1023, 0), (300, 1024, 1), (259, 1025, 3), (2049, 129, 0), (5000, 53, 1),
+                                       (3, 7, 0), (1, 262147, 0), (262147, 1, 2), (513, 513, 1)])
+def test_runs_match_oracle(m, n, pad):
+    import torch
+    k = 3
+    A = workloads.random_matrix(m, k, 1.0, 700 + n % 97)
+    B = workloads.random_matrix(k, n, 1.0, 701 + m % 89)
+    if m > 2 and n > 2:
+        A[m - 1, 1] = np.inf
+        B[2, n // 2] = np.nan
+    C0 = workloads.random_matrix(m, n, 1.0, 702)
+    pA, eA = oz.ozaki25_deconstruct(0, to_dev(A), set=oz.A15)
+    pB, eB = oz.ozaki25_deconstruct(1, to_dev(B), set=oz.A15)
+    for c in (None, C0):
+        log(f"runs m={m} n={n} pad={pad} subtract={c is not None}")
+        full = torch.full((m, n + pad), 5.0, dtype=torch.float64, device="cuda")
+        C = full[:, :n]
+        if c is not None:
+            C.copy_(torch.from_numpy(c))
+        oz.ozaki25_dgemm_planes(k, pA, eA, pB, eB, C, subtract=c is not None, set=oz.A15)
+        torch.cuda.synchronize()
+        want = oracle.dgemm(A, B, C_in=c, set=1, want_planes=False, fallback=False).C
+        assert_bits_equal(C.cpu().numpy(), want, "C")
+        assert bool((full[:, n:] == 5.0).all())
