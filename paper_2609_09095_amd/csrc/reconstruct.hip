@@ -167,8 +167,7 @@ __device__ __forceinline__ double reconstruct_one_a(const RT* rowq, int64_t mn, 
   return garner_bytes(c, -sa - sb);
 }
 
-// Grid: x over 256-column strips, y over rows (strided by gridDim.y).  (The
-// byte moduli's compact residues come here for small outputs only.)
+// Grid: x over 256-column strips, y over rows (strided by gridDim.y).
 template <bool BYTES, typename RT>
 __global__ __launch_bounds__(256) void reconstruct_kernel(int64_t m, int64_t n,
                                                           const RT* __restrict__ cres,
@@ -207,13 +206,14 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(int64_t m, int64_t n,
 constexpr int kRun = 1024, kSlab = kRun + 256;
 using lds_ptr_r = __attribute__((address_space(3))) void*;
 
-template <bool ALIGNED>
+// NATIVE: flagged outputs are re-issued here; else they get `fill`.
+template <bool ALIGNED, bool NATIVE>
 __global__ __launch_bounds__(256) void reconstruct_runs_kernel(int64_t mn, int n, int64_t ldc,
                                                                const int8_t* __restrict__ cres,
                                                                const int32_t* __restrict__ ea,
                                                                const int32_t* __restrict__ eb,
                                                                double* __restrict__ C, int subtract,
-                                                               double fill) {
+                                                               double fill, NativeOperands nat) {
   __shared__ __attribute__((aligned(16))) int8_t slab[kRA * kSlab];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t i0 = (int64_t)blockIdx.x * kRun;
@@ -255,6 +255,8 @@ __global__ __launch_bounds__(256) void reconstruct_runs_kernel(int64_t mn, int n
       for (int q = 0; q < kRA; ++q)
         c[q] = slab[q * kSlab + (ALIGNED ? 0 : (int)((q * mn + i0) & 3)) + o];
       r = garner_bytes(c, -sa - sb);
+    } else if constexpr (NATIVE) {
+      r = native_dot(nat.A + (row0 + dr) * nat.lda, nat.B + col, nat.ldb, nat.k);
     }
     __builtin_nontemporal_store(subtract ? old - r : r, out);
   }
@@ -311,42 +313,54 @@ dim3 grid_for(int64_t m, int64_t n) {
   return dim3((unsigned)((n + 255) / 256), (unsigned)(y < 65535 ? y : 65535));
 }
 
+hipError_t launch_native(int64_t m, int64_t n, const int32_t* ea, const int32_t* eb, const NativeOperands& nat,
+                         double* C, int64_t ldc, int subtract, hipStream_t stream) {
+  hipLaunchKernelGGL(native_reissue_kernel,
+                     dim3((unsigned)((n + 255) / 256), (unsigned)(m < 16776960 ? (m + 255) / 256 : 65535)), dim3(256),
+                     0, stream, m, n, ea, eb, nat, C, ldc, subtract);
+  return hipGetLastError();
+}
+
+// The byte moduli's compact residues, in runs; the native re-issue inside
+// the kernel for up to 2^22 outputs, where a launch of its own is 5 to 10 %
+// of the call (1024^3: 4 of 52 us), and apart beyond.
+template <bool NATIVE>
+void launch_runs(int64_t m, int64_t n, const int8_t* cres, const int32_t* ea, const int32_t* eb, double* C,
+                 int64_t ldc, int subtract, double fill, const NativeOperands& nat, hipStream_t stream) {
+  const dim3 grid((unsigned)((m * n + kRun - 1) / kRun));
+  if (m * n % 4 == 0)
+    hipLaunchKernelGGL((reconstruct_runs_kernel<true, NATIVE>), grid, dim3(256), 0, stream, m * n, (int)n, ldc, cres,
+                       ea, eb, C, subtract, fill, nat);
+  else
+    hipLaunchKernelGGL((reconstruct_runs_kernel<false, NATIVE>), grid, dim3(256), 0, stream, m * n, (int)n, ldc, cres,
+                       ea, eb, C, subtract, fill, nat);
+}
+
 template <bool BYTES, typename RT>
 hipError_t launch_rec(int64_t m, int64_t n, const RT* cres, const int32_t* ea, const int32_t* eb,
                       double* C, int64_t ldc, int subtract, const NativeOperands& nat,
                       hipStream_t stream) {
   if (m <= 0 || n <= 0) return hipSuccess;
-  const dim3 grid = grid_for(m, n);
-  if (nat.A && subtract) {
-    hipLaunchKernelGGL(native_reissue_kernel, dim3(grid.x, (unsigned)(m < 16776960 ? (m + 255) / 256 : 65535)),
-                       dim3(256), 0, stream, m, n, ea, eb, nat, C, ldc, subtract);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+  constexpr bool RUNS = BYTES && sizeof(RT) == 1;
+  if (RUNS && (m * n + kRun - 1) / kRun > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+  const bool inside = RUNS && nat.A && m * n <= 1 << 22, apart = nat.A && !inside;
   const double fill = nat.A ? 0.0 : __builtin_nan("");
-  // runs from about one block per CU (2^18 outputs), and wherever strips of
-  // 256 columns leave more than a fifth of their lanes idle; below, strips
-  // (256 x 256: 4.3 us against 5.0)
-  if (BYTES && sizeof(RT) == 1 && (m * n >= 1 << 18 || 4 * (int64_t)grid.x * 256 > 5 * n)) {
-    const int64_t blocks = (m * n + kRun - 1) / kRun;
-    if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
-    if (m * n % 4 == 0)
-      hipLaunchKernelGGL(reconstruct_runs_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, m * n, (int)n, ldc,
-                         (const int8_t*)cres, ea, eb, C, subtract, fill);
-    else
-      hipLaunchKernelGGL(reconstruct_runs_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, m * n, (int)n,
-                         ldc, (const int8_t*)cres, ea, eb, C, subtract, fill);
-  } else {
-    hipLaunchKernelGGL((reconstruct_kernel<BYTES, RT>), grid, dim3(256), 0, stream, m, n, cres, ea, eb, C, ldc,
-                       subtract, fill);
-  }
-  if (nat.A && !subtract) {
-    const hipError_t e = hipGetLastError();
+  if (apart && subtract) {
+    const hipError_t e = launch_native(m, n, ea, eb, nat, C, ldc, subtract, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(native_reissue_kernel, dim3(grid.x, (unsigned)(m < 16776960 ? (m + 255) / 256 : 65535)),
-                       dim3(256), 0, stream, m, n, ea, eb, nat, C, ldc, subtract);
   }
-  return hipGetLastError();
+  if constexpr (RUNS) {
+    if (inside)
+      launch_runs<true>(m, n, cres, ea, eb, C, ldc, subtract, fill, nat, stream);
+    else
+      launch_runs<false>(m, n, cres, ea, eb, C, ldc, subtract, fill, nat, stream);
+  } else {
+    hipLaunchKernelGGL((reconstruct_kernel<BYTES, RT>), grid_for(m, n), dim3(256), 0, stream, m, n, cres, ea, eb, C,
+                       ldc, subtract, fill);
+  }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !apart || subtract) return e;
+  return launch_native(m, n, ea, eb, nat, C, ldc, subtract, stream);
 }
 
 }  // namespace
