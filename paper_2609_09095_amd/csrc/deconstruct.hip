@@ -28,8 +28,13 @@ constexpr int kElems = 16;  // k values per thread
 // 16 plane bytes: a streaming store (the planes are read back by the
 // residue GEMM long after, from HBM)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+template <bool NT = true>
 __device__ __forceinline__ void put16(int8_t* p, uint4 w) {
-  __builtin_nontemporal_store(u32x4{w.x, w.y, w.z, w.w}, reinterpret_cast<u32x4*>(p));
+  const u32x4 v{w.x, w.y, w.z, w.w};
+  if constexpr (NT)
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
+  else
+    *reinterpret_cast<u32x4*>(p) = v;
 }
 
 // four limbs as e4m3 bytes (OCP E4M3FN), the first in the low byte
@@ -256,7 +261,7 @@ __global__ __launch_bounds__(256) void deconstruct_kernel(int64_t vecs, int64_t 
 // residue of a byte modulus lies in [-128, 127] and is stored as it stands,
 // one int8 plane per modulus (8 bytes read, 15 written per element).
 
-template <int I>
+template <int I, bool NT>
 __device__ __forceinline__ void emit_byte_modulus(const double (&y)[kElems],
                                                   const uint32_t (&yp)[kElems / 2], int8_t* planes,
                                                   int64_t plane_stride, int64_t off) {
@@ -266,23 +271,23 @@ __device__ __forceinline__ void emit_byte_modulus(const double (&y)[kElems],
   w.y = residue_bytes<M>(y[4], y[5], y[6], y[7], yp[2], yp[3]);
   w.z = residue_bytes<M>(y[8], y[9], y[10], y[11], yp[4], yp[5]);
   w.w = residue_bytes<M>(y[12], y[13], y[14], y[15], yp[6], yp[7]);
-  put16(planes + (int64_t)I * plane_stride + off, w);
+  put16<NT>(planes + (int64_t)I * plane_stride + off, w);
 }
 
-template <int FIRST, int... I>
+template <int FIRST, bool NT, int... I>
 __device__ __forceinline__ void emit_some_bytes(std::integer_sequence<int, I...>, const double (&y)[kElems],
                                                 const uint32_t (&ylo)[kElems], int8_t* planes,
                                                 int64_t plane_stride, int64_t off) {
   uint32_t yp[kElems / 2];
 #pragma unroll
   for (int c = 0; c < kElems / 2; ++c) yp[c] = low_halves(ylo[2 * c], ylo[2 * c + 1]);
-  (emit_byte_modulus<FIRST + I>(y, yp, planes, plane_stride, off), ...);
+  (emit_byte_modulus<FIRST + I, NT>(y, yp, planes, plane_stride, off), ...);
 }
-template <int RM>
+template <int RM, bool NT = true>
 __device__ __forceinline__ void emit_all_bytes(const double (&y)[kElems], const uint32_t (&ylo)[kElems],
                                                int8_t* planes, int64_t plane_stride, int64_t off) {
   if constexpr (RM != 3) {
-    emit_some_bytes<0>(std::make_integer_sequence<int, kRA>{}, y, ylo, planes, plane_stride, off);
+    emit_some_bytes<0, NT>(std::make_integer_sequence<int, kRA>{}, y, ylo, planes, plane_stride, off);
   } else {
     [&]<int... G>(std::integer_sequence<int, G...>) {
       ([&] {
@@ -290,7 +295,7 @@ __device__ __forceinline__ void emit_all_bytes(const double (&y)[kElems], const 
         double z[kElems];
         uint32_t zlo[kElems];
         reduce_group(y, N, 1.0 / N, z, zlo);
-        emit_some_bytes<G * kGroupA>(std::make_integer_sequence<int, kGroupA>{}, z, zlo, planes, plane_stride,
+        emit_some_bytes<G * kGroupA, NT>(std::make_integer_sequence<int, kGroupA>{}, z, zlo, planes, plane_stride,
                                      off);
       }(),
        ...);
@@ -323,7 +328,7 @@ __global__ __launch_bounds__(256) void deconstruct_bytes_kernel(int64_t vecs, in
 // they combine from the scan's `slabs` partial maxima (in LDS: 32 vectors x 8
 // threads) and whose first k block writes eb for the reconstruction.
 // ablocks = 0: B alone.
-template <int RM, bool TZ>
+template <int RM, bool TZ, bool NT>
 __global__ __launch_bounds__(256) void deconstruct_bytes_both_kernel(
     int64_t ablocks, int64_t m, int64_t n, int64_t k, int64_t kp, const double* __restrict__ A, int64_t lda,
     const int32_t* __restrict__ ea, int8_t* __restrict__ pa, const double* __restrict__ B, int64_t ldb,
@@ -337,7 +342,7 @@ __global__ __launch_bounds__(256) void deconstruct_bytes_both_kernel(
     if (v >= m) return;
     const int sigma = load_scaled<0>(m, k, A, lda, ea[v], v, g * kElems, true, x);
     scale_round<TZ, RM>(x, sigma, y, ylo);
-    emit_all_bytes<RM>(y, ylo, pa, m * 128, plane_offset(m, kRA, v, g));
+    emit_all_bytes<RM, NT>(y, ylo, pa, m * 128, plane_offset(m, kRA, v, g));
     return;
   }
   const int64_t block = (int64_t)blockIdx.x - ablocks, vb = (n + 31) / 32;
@@ -364,7 +369,7 @@ __global__ __launch_bounds__(256) void deconstruct_bytes_both_kernel(
   if (g == 0) eb[v] = raw;
   const int sigma = load_scaled<1>(n, k, B, ldb, raw, v, g * kElems, true, x);
   scale_round<TZ, RM>(x, sigma, y, ylo);
-  emit_all_bytes<RM>(y, ylo, pb, n * 128, plane_offset(n, kRA, v, g));
+  emit_all_bytes<RM, NT>(y, ylo, pb, n * 128, plane_offset(n, kRA, v, g));
 }
 
 // ---- accurate mode (Sec. 2, Eq. (alpha)): the magnitude digit of every
@@ -479,15 +484,28 @@ hipError_t launch_deconstruct_bytes_both(int quant, int64_t m, int64_t n, int64_
   if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
   const bool tz = quant == kQuantTZ;
   const int mode = t <= 51 ? 1 : (t == 52 ? 2 : 3);  // as in launch_deconstruct
-#define OZ_BOTH(MODE, TZ)                                                                                     \
-  hipLaunchKernelGGL((deconstruct_bytes_both_kernel<MODE, TZ>), dim3((unsigned)blocks), dim3(256), 0, stream, \
+  // streaming plane stores, but for long k and planes that the last-level
+  // cache holds with room plain ones, which the products then find there
+  // (2048^3, 120 MiB, 202 -> 192 us a call, 256 x 256 x 8192 56.7 -> 53.8, 700 x 900
+  // x 3000 79.7 -> 76.6; at short k no better, 3000 x 2500 x 700 1 % slower, and
+  // 2000 x 4000 x 4000, 343 MiB, likewise)
+  const bool nt = kp < 2048 || kRA * (m + n) * kp > (int64_t)128 << 20;
+#define OZ_BOTH(MODE, TZ, NT)                                                                                     \
+  hipLaunchKernelGGL((deconstruct_bytes_both_kernel<MODE, TZ, NT>), dim3((unsigned)blocks), dim3(256), 0, stream, \
                      ablocks, m, n, k, kp, A, lda, ea, pa, B, ldb, part, (int)slabs, t, eb, pb)
-  if (mode == 1 && tz) OZ_BOTH(1, true);
-  else if (mode == 1) OZ_BOTH(1, false);
-  else if (mode == 2 && tz) OZ_BOTH(2, true);
-  else if (mode == 2) OZ_BOTH(2, false);
-  else if (tz) OZ_BOTH(3, true);
-  else OZ_BOTH(3, false);
+#define OZ_BOTH_TZ(MODE)                  \
+  if (tz && nt) OZ_BOTH(MODE, true, true); \
+  else if (tz) OZ_BOTH(MODE, true, false); \
+  else if (nt) OZ_BOTH(MODE, false, true); \
+  else OZ_BOTH(MODE, false, false)
+  if (mode == 1) {
+    OZ_BOTH_TZ(1);
+  } else if (mode == 2) {
+    OZ_BOTH_TZ(2);
+  } else {
+    OZ_BOTH_TZ(3);
+  }
+#undef OZ_BOTH_TZ
 #undef OZ_BOTH
   return hipGetLastError();
 }
