@@ -112,44 +112,68 @@ def _check(status: int, what: str):
         raise Ozaki25Error(status, what)
 
 
+_torch = None     # torch, imported by the first call that handles tensors
+_raw_stream = None  # () -> the current stream's handle
+
+
+def _tensors():
+    """torch; also picks the cheapest way to the current stream's handle (a
+    Stream object costs a few microseconds, as much as a small product)."""
+    global _torch, _raw_stream
+    if _torch is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        dev = getattr(torch._C, "_cuda_getDevice", None)
+        if raw is not None and dev is not None:
+            _raw_stream = lambda: raw(dev())  # noqa: E731
+        else:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+        _torch = torch
+    return _torch
+
+
+# pointers and streams go to ctypes as plain integers (argtypes c_void_p)
 def _stream(stream):
-    import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        _tensors()
+        return _raw_stream()
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else 0
 
 
 def _on_gpu(ts):
     """Every tensor on one CUDA device (checked after the shapes and sizes,
     so that shape errors are reported first)."""
-    dev = None
+    dev, first = None, None
     for name, t in ts:
         if t is None:
             continue
         if not t.is_cuda:
             raise ValueError(f"{name} must be a CUDA tensor")
+        d = t.get_device()
         if dev is None:
-            dev = t.device
-        elif t.device != dev:
-            raise ValueError(f"{name} is on {t.device}, not on {dev} like the other operands")
+            dev, first = d, t
+        elif d != dev:
+            raise ValueError(f"{name} is on {t.device}, not on {first.device} like the other operands")
 
 
 def _matrix(t, name, shape=None):
     """A 2-D float64 row-major matrix; returns (t, leading dimension)."""
-    import torch
+    torch = _torch or _tensors()
     if not (isinstance(t, torch.Tensor) and t.dtype == torch.float64 and t.dim() == 2):
         raise ValueError(f"{name} must be a 2-D float64 tensor")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    rows, cols = t.shape
+    if shape is not None and (rows, cols) != tuple(shape):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    if t.stride(1) != 1 and t.shape[1] > 1:
+    s0, s1 = t.stride()
+    if s1 != 1 and cols > 1:
         raise ValueError(f"{name} must be row-major (unit column stride)")
-    if t.shape[0] > 1 and t.stride(0) < t.shape[1]:
+    if rows > 1 and s0 < cols:
         raise ValueError(f"{name} rows overlap (row stride below the row length)")
-    return t, max(t.stride(0), t.shape[1], 1)
+    return t, max(s0, cols, 1)
 
 
 def _buffer(t, name, dtypes, numel):
@@ -277,7 +301,7 @@ def ozaki25_reconstruct(Cres, expsA, expsB, C=None, subtract: bool = False, set:
 # ----------------------------------------------------------------- GEMM
 def _workspace(workspace):
     if workspace is None:
-        return ctypes.c_void_p(0), 0
+        return 0, 0
     _buffer(workspace, "workspace", _u8(), 0)
     return _ptr(workspace), workspace.numel()
 
