@@ -1,5 +1,7 @@
-"""MI355X-native emulated FP64 GEMM by Ozaki Scheme II on FP8 MFMA (published
-moduli) or int8 MFMA (the all-byte moduli of Sec. 5.1, candidate A).
+"""MI355X-native emulated FP64 GEMM by Ozaki Scheme II: the published moduli's
+or the all-byte moduli's (Sec. 5.1, candidate A) scale and results, computed
+on int8 MFMA inside ozaki25_dgemm*; stages and stored planes on the set's own
+planes, FP8 MFMA for the published moduli.
 
 Python binding of ``libozaki25.so`` (the C ABI declared in
 ``include/ozaki25.h``).  Argument marshalling only: every step of the
@@ -28,8 +30,8 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libozaki25.so")
 _HEADER = os.path.join(os.path.dirname(_PKG), "include", "ozaki25.h")
 
-S12 = 0           # published moduli, FP8 limb route
-A15 = 1           # all-byte moduli (Sec. 5.1 candidate A), int8 route
+S12 = 0           # published moduli (own planes: FP8 limbs)
+A15 = 1           # all-byte moduli (Sec. 5.1 candidate A; int8 planes)
 RN = 0            # quantiser: round to nearest, ties to even (Ozaki-II-RN)
 TZ = 1            # quantiser: toward zero (Ozaki-II-TZ)
 NUM_MODULI = 12
