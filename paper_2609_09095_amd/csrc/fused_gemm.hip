@@ -150,6 +150,10 @@ __device__ __forceinline__ int cmod_sum(int x, double m, double minv) {
 // 8 w .. 8 w + 7 of each slab and owns the 32 x 32 outputs (w / 4, w % 4) of
 // every modulus of its group.
 constexpr int FBM = 128;
+// Leading dimensions of A below this go through a buffer resource: 8 lda is
+// then a positive signed 24-bit factor and 128 rows stay below 2^31 bytes.
+constexpr int64_t kBufLda = (int64_t)1 << 20;
+static_assert(8 * (kBufLda - 1) < (1 << 23) && FBM * 8 * kBufLda < (int64_t)1 << 31, "row offsets of the buffer loads");
 // MODE: the residue route by the range of y -- 1: ylo = y + 1.5 2^52
 // (|y| <= 2^51); 2: ylo by low32_split (|y| <= 2^52); 3: y first reduced
 // modulo the product of the block's G moduli, which keeps their residues,
@@ -216,9 +220,10 @@ __global__ __launch_bounds__(1024, 1) void fused_bytes_kernel(
   // the last, partial one clamped single loads; full: stage s is known to
   // lie inside k.
   // BUF: whole stages read the strip's rows through one buffer resource, at
-  // 32-bit byte offsets from its first row by 24-bit products (the host takes
-  // it for lda < 2^21 only, so 128 rows stay below 2^31 bytes); rows past m
-  // read as zero, and a row may start at any double.
+  // 32-bit byte offsets from its first row by signed 24-bit products (the host
+  // takes it for lda < kBufLda only, so that a row's bytes fit one and 128
+  // rows stay below 2^31); rows past m read as zero, and a row may start at
+  // any double.
   const int lda8 = (int)(lda * 8);
   const int arec = BUF ? (int)((m - row0 < FBM ? m - row0 : FBM) * lda8) : 0;
   const __amdgpu_buffer_rsrc_t ars = __builtin_amdgcn_make_buffer_rsrc(
@@ -390,7 +395,7 @@ hipError_t launch_fused_g(int64_t m, int64_t n, int64_t k, int64_t kp, const dou
   const int64_t strips = (m + FBM - 1) / FBM;
   const int64_t blocks = (strips + 7) / 8 * 8 * (kRA / G);
   if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
-  if (lda < (1 << 21))
+  if (lda < kBufLda)
     hipLaunchKernelGGL((fused_bytes_kernel<G, MODE, TZ, true>), dim3((unsigned)blocks), dim3(1024), 0,
                        stream, m, n, k, kp, A, lda, sigma, pb, cres, strips);
   else

@@ -129,3 +129,25 @@ def test_fused_published_constant_vectors():
     B[:, 2] = -3.0
     log("fused S12 constant rows and columns")
     assert_bits_equal(_run(A, B, oz.S12), oracle.dgemm(A, B, set=0, want_planes=False).C, "C")
+
+
+@pytest.mark.parametrize("set", SETS)
+@pytest.mark.parametrize("lda", [(1 << 20) - 1, 1 << 20, (1 << 20) + 1, (1 << 21) - 1])
+def test_fused_leading_dimension_limit(set, lda):
+    """Leading dimensions of A on either side of 2^20, up to which the kernel
+    takes 24-bit row offsets (8 lda must not reach the sign bit, 2^23), and
+    at 2^21 - 1, where such an offset wraps to a small negative one.  NaN
+    beyond the k columns: no output may see it."""
+    import torch
+    m, n, k = 1030, 5, 1000
+    A = workloads.random_matrix(m, k, 1.0, 81)
+    B = workloads.random_matrix(k, n, 1.0, 82)
+    log(f"fused set={set} lda={lda}")
+    flat = torch.empty((m - 1) * lda + k, dtype=torch.float64, device="cuda")
+    flat.fill_(float("nan"))
+    Ad = flat.as_strided((m, k), (lda, 1))
+    Ad.copy_(torch.from_numpy(A))
+    C = torch.full((m, n), 7.0, dtype=torch.float64, device="cuda")
+    oz.ozaki25_dgemm_ex(Ad, to_dev(B), C, set=set)
+    torch.cuda.synchronize()
+    assert_bits_equal(C.cpu().numpy(), oracle.dgemm(A, B, set=set, want_planes=False).C, "C")
