@@ -7,6 +7,7 @@
 #include <cstring>
 #include <mutex>
 
+#include "dispatch.hpp"
 #include "kernels.hpp"
 #include "moduli.hpp"
 #include "ozaki25.h"
@@ -81,11 +82,7 @@ size_t products_bytes(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set, i
   return align_up(one) + (sp > 1 ? align_up(one * sp) : 0);
 }
 
-// Storage mode F for A (at most 128 columns, at least kFusedMinRows rows):
-// A is converted inside the product kernel, so the workspace holds no planes
-// of A and the products need no split of k.
-constexpr int64_t kFusedMinRows = 1024;
-bool fused_a(int64_t m, int64_t n) { return n <= 128 && m >= kFusedMinRows; }
+using oz::fused_a;
 
 // Bytes of the ozaki25_dgemm* workspace: the set's own planes of A (none in
 // storage mode F) and B, both exponents and the residue products.
@@ -147,22 +144,6 @@ Workspace layout(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set) {
   return w;
 }
 
-// Whether a product runs as one launch (launch_one_kernel) rather than the
-// staged kernels: by the measured times of both, in tenths of a us.  One
-// launch takes about 5 us and 2.25 per 64-k chunk for every round of 256
-// 32 x 32 tiles (a block per CU); the staged path about 20, 12.5 per 2^20
-// outputs and 0.75 per chunk, or in storage mode F 22, 2.3 per 2^10 rows and
-// 0.75 per chunk.  Both sides: 64^3 7.1 / 20.1, 512^3 24.3 / 29.7, 512 x 512 x
-// 768 31.7 / 34.8, 1024 x 1024 x 64 26.3 / 35.7, 16384 x 32 x 128 18.0 / 62;
-// beyond the line 256 x 256 x 1024 35.1 / 31.9, 2048 x 2048 x 64 98.6 / 71.9.
-bool one_kernel(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb) {
-  if (m > (1 << 24) || n > (1 << 24) || k > 4096 || lda > oz::kOneKernelMaxLd || ldb > oz::kOneKernelMaxLd) return false;
-  const int64_t tiles = ((m + 31) / 32) * ((n + 31) / 32), chunks = (k + 63) / 64;
-  const int64_t rounds = (tiles + 255) / 256;
-  const int64_t staged = fused_a(m, n) ? 220 + 23 * m / 1024 : 200 + 125 * m * n / (1 << 20);
-  return 2 * rounds * (50 + 22 * chunks) + rounds * chunks <= 2 * staged + 15 * chunks;
-}
-
 // Exponent scan and deconstruction of one operand, in runs of whole
 // 256-vector tiles holding about 256 MiB of FP64 each (the size of the
 // MI355X last-level cache): each run's deconstruction reads the run right
@@ -204,15 +185,10 @@ hipError_t scan_and_deconstruct(ozaki25_moduli_set set, ozaki25_quantiser quant,
 }
 
 // Whether both operands' scans share one launch and both deconstructions
-// another: the partial column maxima need room (the residues' part of the
-// workspace, unused until the products), and together the operands must fit
-// the last-level cache's 256 MiB, beyond which interleaved runs of one
-// operand at a time are faster (with A converted inside the product kernel,
-// only scanned here, there is no such limit).
+// another; the partial column maxima go to the residues' part of the
+// workspace, unused until the products.
 bool both_at_once(int64_t m, int64_t n, int64_t k, const Workspace& w) {
-  const size_t room = w.total - w.cres;
-  return (size_t)oz::scan_both_slabs(n, k) * n * sizeof(uint32_t) <= room &&
-         (fused_a(m, n) || (m + n) * k_pad(k) * (int64_t)sizeof(double) <= (int64_t)256 << 20);
+  return oz::both_at_once(m, n, k, k_pad(k), (int64_t)(w.total - w.cres));
 }
 
 // ---- accurate mode (Sec. 2, Eq. (alpha)) ---------------------------------
@@ -434,7 +410,7 @@ ozaki25_status ozaki25_dgemm_ex(int64_t m, int64_t n, int64_t k, const double* A
   }
 
   const int t = scale_bits(k, set);
-  if (one_kernel(m, n, k, lda, ldb)) {
+  if (oz::one_kernel(m, n, k, lda, ldb)) {
     // no workspace used, but one that is too small is refused all the same
     if (workspace && (workspace_bytes < workspace_total(m, n, k, set) || ((uintptr_t)workspace & (kAlign - 1))))
       return OZAKI25_ERR_WORKSPACE;

@@ -1,0 +1,75 @@
+// The rules by which ozaki25_dgemm* choose between their launches, from sizes
+// alone.  Plain C++, so that they also compile for the host's tests.
+#pragma once
+
+#include <cstdint>
+
+namespace oz {
+
+// Storage mode F for A (at most 128 columns, at least kFusedMinRows rows):
+// A is converted inside the product kernel, so the workspace holds no planes
+// of A and the products need no split of k.
+constexpr int64_t kFusedMinRows = 1024;
+constexpr bool fused_a(int64_t m, int64_t n) { return n <= 128 && m >= kFusedMinRows; }
+
+// The one-launch product's limits: rows and columns (32-bit indices), k
+// (exact int32 sums; the rule below never asks for more), and leading
+// dimensions (32-bit offsets within a 64-row chunk).
+constexpr int64_t kOneKernelMaxVecs = (int64_t)1 << 24, kOneKernelMaxK = 4096, kOneKernelMaxLd = (int64_t)1 << 21;
+
+// Whether a product runs as one launch (launch_one_kernel) rather than the
+// staged kernels: by the measured times of both on the whole card (256 CUs),
+// in tenths of a us.  One launch takes about 5 us and 2.25 per 64-k chunk for
+// every round of 256 32 x 32 tiles (a block per CU); the staged path about 20,
+// 12.5 per 2^20 outputs and 0.75 per chunk, or in storage mode F 22, 2.3 per
+// 2^10 rows and 0.75 per chunk.  Both sides: 64^3 7.1 / 20.1, 512^3 24.3 / 29.7,
+// 512 x 512 x 768 31.7 / 34.8, 1024 x 1024 x 64 26.3 / 35.7, 16384 x 32 x 128
+// 18.0 / 62; beyond the line 256 x 256 x 1024 35.1 / 31.9, 2048 x 2048 x 64
+// 98.6 / 71.9.
+constexpr bool one_kernel(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb) {
+  if (m > kOneKernelMaxVecs || n > kOneKernelMaxVecs || k > kOneKernelMaxK || lda > kOneKernelMaxLd ||
+      ldb > kOneKernelMaxLd)
+    return false;
+  const int64_t tiles = ((m + 31) / 32) * ((n + 31) / 32), chunks = (k + 63) / 64;
+  const int64_t rounds = (tiles + 255) / 256;
+  const int64_t staged = fused_a(m, n) ? 220 + 23 * m / 1024 : 200 + 125 * m * n / (1 << 20);
+  return 2 * rounds * (50 + 22 * chunks) + rounds * chunks <= 2 * staged + 15 * chunks;
+}
+
+// The joint exponent scan: rows of B per slab (each slab leaves one partial
+// maximum per column), slabs, and blocks -- one per row of A, or per four rows
+// of at most kShortRow elements, and one per slab and strip of 64 columns.
+constexpr int64_t kShortRow = 1024;
+constexpr int64_t scan_both_rows(int64_t n, int64_t k) {
+  return (n + 63) / 64 * ((k + 63) / 64) <= 1024 ? 64 : 256;
+}
+constexpr int64_t scan_both_slabs(int64_t n, int64_t k) {
+  const int64_t rows = scan_both_rows(n, k);
+  return (k + rows - 1) / rows;
+}
+constexpr int64_t scan_both_blocks(int64_t m, int64_t n, int64_t k) {
+  return (k <= kShortRow ? (m + 3) / 4 : m) + (n + 63) / 64 * scan_both_slabs(n, k);
+}
+
+// Whether both operands' scans share one launch and both deconstructions
+// another (k padded to kp):
+//  - the partial column maxima need room (bytes);
+//  - at most kJointSlabs of them per column: every block of B's deconstruction
+//    reads the maxima of its columns, so that work grows with slabs times
+//    blocks, that is with k^2.  Calls with joint and with separate launches:
+//    512 x 128 x 32768 (512 slabs) 179 / 199 us, 64 x 64 x 262000 (1024) 388 /
+//    415, 16 x 16 x 524288 (2048) 439 / 459, 1 x 1 x 2^20 (4096) 769 / 712, 1 x
+//    1 x 2^22 (16384) 4.52 / 2.71 ms; in storage mode F 1024 x 64 x 262144 (1024)
+//    9.64 / 9.63, 1024 x 128 x 524288 (2048) 19.28 / 19.21;
+//  - together the operands must fit the last-level cache's 256 MiB, beyond
+//    which interleaved runs of one operand at a time are faster (with A
+//    converted inside the product kernel, only scanned here, there is no such
+//    limit).
+constexpr int64_t kJointSlabs = 2048;
+constexpr bool both_at_once(int64_t m, int64_t n, int64_t k, int64_t kp, int64_t room) {
+  const int64_t slabs = scan_both_slabs(n, k);
+  return slabs <= kJointSlabs && slabs * n * (int64_t)sizeof(uint32_t) <= room &&
+         (fused_a(m, n) || (m + n) * kp * (int64_t)sizeof(double) <= (int64_t)256 << 20);
+}
+
+}  // namespace oz

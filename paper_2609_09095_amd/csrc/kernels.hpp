@@ -52,10 +52,9 @@ hipError_t launch_deconstruct(int set, int quant, int side, int64_t vecs, int64_
 
 // Both operands at once, where launches and not bytes are the cost: the scans
 // of A's rows (sigma into ea) and of B's columns (partial maxima of the
-// exponent keys, scan_both_slabs(n, k) x n uint32, into part) in one launch,
+// exponent keys, scan_both_slabs(n, k) (dispatch.hpp) x n uint32, into part) in one launch,
 // and the byte planes of both in another, which also turns the partial
 // maxima into eb.  pa == nullptr: B's planes alone.
-int64_t scan_both_slabs(int64_t n, int64_t k);
 hipError_t launch_scan_both(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, const double* B,
                             int64_t ldb, int t, int32_t* ea, uint32_t* part, hipStream_t stream);
 hipError_t launch_deconstruct_bytes_both(int quant, int64_t m, int64_t n, int64_t k, int64_t kp, int t,
@@ -87,11 +86,10 @@ hipError_t launch_residue_gemm_bytes_i8(int64_t m, int64_t n, int64_t kp, const 
                                         hipStream_t stream);
 
 // The whole product, scans to C, in one launch modulo the byte moduli, for
-// small products; no workspace.  k from 1 to kOneKernelMaxK, lda and ldb at
-// most kOneKernelMaxLd (32-bit offsets within a 64-row chunk); t as for
-// launch_deconstruct.  Outputs on non-finite rows and columns are re-issued
+// small products; no workspace.  k from 1 to kOneKernelMaxK, m and n at most
+// kOneKernelMaxVecs, lda and ldb at most kOneKernelMaxLd (dispatch.hpp); t as
+// for launch_deconstruct.  Outputs on non-finite rows and columns are re-issued
 // natively.
-constexpr int64_t kOneKernelMaxK = 65536, kOneKernelMaxLd = (int64_t)1 << 21;
 hipError_t launch_one_kernel(int quant, int64_t m, int64_t n, int64_t k, int t, const double* A, int64_t lda,
                              const double* B, int64_t ldb, double* C, int64_t ldc, int subtract,
                              hipStream_t stream);

@@ -19,6 +19,7 @@
 // the next one.
 #include <utility>
 
+#include "dispatch.hpp"
 #include "exponent_key.hpp"
 #include "garner_bytes.hpp"
 #include "kernels.hpp"
@@ -218,8 +219,8 @@ hipError_t launch_one_kernel(int quant, int64_t m, int64_t n, int64_t k, int t, 
                              hipStream_t stream) {
   if (m <= 0 || n <= 0) return hipSuccess;
   const int64_t tm = (m + OT - 1) / OT, tn = (n + OT - 1) / OT;
-  if (k < 1 || k > kOneKernelMaxK || lda > kOneKernelMaxLd || ldb > kOneKernelMaxLd || m > INT32_MAX - OT || n > INT32_MAX - OT || tm * tn > INT32_MAX ||
-      t > kMaxScaleBits)
+  if (k < 1 || k > kOneKernelMaxK || lda > kOneKernelMaxLd || ldb > kOneKernelMaxLd || m > kOneKernelMaxVecs ||
+      n > kOneKernelMaxVecs || tm * tn > INT32_MAX || t > kMaxScaleBits)
     return hipErrorInvalidValue;
   const bool tz = quant == kQuantTZ;
   // |y| <= 2^t, as in the deconstruction of the byte moduli

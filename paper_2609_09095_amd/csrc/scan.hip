@@ -2,6 +2,7 @@
 // row of A / column of B the frexp exponent e of its largest magnitude, and
 // sigma = t - e.  HBM-bound: one FP64 read per element.  The reduction key
 // is in exponent_key.hpp.
+#include "dispatch.hpp"
 #include "exponent_key.hpp"
 #include "kernels.hpp"
 
@@ -228,7 +229,6 @@ __global__ __launch_bounds__(256) void scan_cols_kernel(int64_t vecs, int64_t k,
 // deconstruction on load, where atomics would need cleared keys.  Sixteen
 // loads in flight per wavefront: the launch is one latency, not its bytes,
 // at the sizes that take it.
-constexpr int kShortRow = 1024;
 __global__ __launch_bounds__(256) void scan_both_kernel(int64_t m, int64_t n, int64_t k, const double* A,
                                                         int64_t lda, const double* B, int64_t ldb, int t,
                                                         int32_t* ea, int64_t ablocks, int64_t rows_per_block,
@@ -342,22 +342,14 @@ hipError_t launch_scan_cols(int64_t vecs, int64_t k, const double* X, int64_t ld
   return hipGetLastError();
 }
 
-int64_t scan_both_slabs(int64_t n, int64_t k) {
-  const int64_t strips = (n + 63) / 64;
-  const int64_t rows = strips * ((k + 63) / 64) <= 1024 ? 64 : 256;
-  return (k + rows - 1) / rows;
-}
-
 hipError_t launch_scan_both(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, const double* B,
                             int64_t ldb, int t, int32_t* ea, uint32_t* part, hipStream_t stream) {
   if (m <= 0 || n <= 0 || k <= 0) return hipErrorInvalidValue;
-  const int64_t strips = (n + 63) / 64, slabs = scan_both_slabs(n, k);
-  const int64_t rows = strips * ((k + 63) / 64) <= 1024 ? 64 : 256;
-  const int64_t ablocks = k <= kShortRow ? (m + 3) / 4 : m;
-  const int64_t blocks = ablocks + strips * slabs;
+  const int64_t blocks = scan_both_blocks(m, n, k);
+  const int64_t ablocks = blocks - (n + 63) / 64 * scan_both_slabs(n, k);
   if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
   hipLaunchKernelGGL(scan_both_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, m, n, k, A, lda, B, ldb, t,
-                     ea, ablocks, rows, part);
+                     ea, ablocks, scan_both_rows(n, k), part);
   return hipGetLastError();
 }
 

@@ -1,0 +1,29 @@
+"""The dispatch rules of paper_2609_09095_amd/csrc/dispatch.hpp, on the CPU,
+over the sizes that the entry points accept."""
+import itertools
+
+import paper_2609_09095_amd as oz
+from routes import rules
+
+PLENTY = 1 << 40  # bytes of room for the partial maxima
+KS = (1, 63, 64, 65, 256, 1000, 1024, 1025, 4096, 8192, 32768, 65536, 65537, 131072, 262143, 262144, 262145, 1 << 19,
+      1 << 20, 1 << 21, oz.MAX_K)
+
+
+def k_pad(k):
+    return -(-k // 128) * 128
+
+
+def test_joint_deconstruction_key_reads_are_linear_in_k():
+    """Every 32-column x 128-k block of the joint deconstruction of B reads the
+    scan's partial maxima of its columns, four bytes each: wherever the joint
+    launches are taken, at most 2048 per block and column (eight times the
+    block's own FP64 bytes), however long k is."""
+    L = rules()
+    taken = 0
+    for m, n, k in itertools.product((1, 16, 64, 512, 1024, 100000), (1, 16, 64, 128, 256, 4096), KS):
+        if L.rule_both_at_once(m, n, k, k_pad(k), PLENTY):
+            taken += 1
+            reads = L.rule_scan_both_slabs(n, k) * 4
+            assert reads <= 8 * 128 * 8, (m, n, k, reads)
+    assert taken > 100
