@@ -61,14 +61,17 @@ constexpr int64_t scan_both_blocks(int64_t m, int64_t n, int64_t k) {
 //    415, 16 x 16 x 524288 (2048) 439 / 459, 1 x 1 x 2^20 (4096) 769 / 712, 1 x
 //    1 x 2^22 (16384) 4.52 / 2.71 ms; in storage mode F 1024 x 64 x 262144 (1024)
 //    9.64 / 9.63, 1024 x 128 x 524288 (2048) 19.28 / 19.21;
+//  - the launch's work-items must stay below 2^32 (16777215 rows of more than
+//    1024 elements are within it alone, but not with B's slabs beside them);
 //  - together the operands must fit the last-level cache's 256 MiB, beyond
 //    which interleaved runs of one operand at a time are faster (with A
 //    converted inside the product kernel, only scanned here, there is no such
 //    limit).
-constexpr int64_t kJointSlabs = 2048;
+constexpr int64_t kJointSlabs = 2048, kJointBlocks = ((int64_t)1 << 24) - 1;  // blocks of 256 work-items
 constexpr bool both_at_once(int64_t m, int64_t n, int64_t k, int64_t kp, int64_t room) {
   const int64_t slabs = scan_both_slabs(n, k);
-  return slabs <= kJointSlabs && slabs * n * (int64_t)sizeof(uint32_t) <= room &&
+  return slabs <= kJointSlabs && scan_both_blocks(m, n, k) <= kJointBlocks &&
+         slabs * n * (int64_t)sizeof(uint32_t) <= room &&
          (fused_a(m, n) || (m + n) * kp * (int64_t)sizeof(double) <= (int64_t)256 << 20);
 }
 

@@ -347,7 +347,7 @@ hipError_t launch_scan_both(int64_t m, int64_t n, int64_t k, const double* A, in
   if (m <= 0 || n <= 0 || k <= 0) return hipErrorInvalidValue;
   const int64_t blocks = scan_both_blocks(m, n, k);
   const int64_t ablocks = blocks - (n + 63) / 64 * scan_both_slabs(n, k);
-  if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+  if (blocks > kJointBlocks) return hipErrorInvalidValue;
   hipLaunchKernelGGL(scan_both_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, m, n, k, A, lda, B, ldb, t,
                      ea, ablocks, scan_both_rows(n, k), part);
   return hipGetLastError();

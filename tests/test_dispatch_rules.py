@@ -27,3 +27,16 @@ def test_joint_deconstruction_key_reads_are_linear_in_k():
             reads = L.rule_scan_both_slabs(n, k) * 4
             assert reads <= 8 * 128 * 8, (m, n, k, reads)
     assert taken > 100
+
+
+def test_joint_scan_grid_fits():
+    """A launch holds fewer than 2^32 work-items: rows that the separate row
+    scan (256 per row) just holds must not be sent to the joint one, whose
+    grid has B's slabs beside them."""
+    L = rules()
+    for n, k in itertools.product((1, 2, 64, 65, 128), (1, 64, 1024, 1025, 4096)):
+        for m in (1024, 1 << 20, (1 << 24) - 1000, (1 << 24) - 65, (1 << 24) - 2, (1 << 24) - 1, 1 << 24, 1 << 26):
+            if L.rule_both_at_once(m, n, k, k_pad(k), PLENTY):
+                assert L.rule_scan_both_blocks(m, n, k) * 256 < 1 << 32, (m, n, k)
+    assert not L.rule_both_at_once((1 << 24) - 1, 1, 1025, k_pad(1025), PLENTY)
+    assert L.rule_both_at_once((1 << 24) - 100, 1, 1025, k_pad(1025), PLENTY)
