@@ -12,6 +12,22 @@ namespace oz {
 constexpr int64_t kFusedMinRows = 1024;
 constexpr bool fused_a(int64_t m, int64_t n) { return n <= 128 && m >= kFusedMinRows; }
 
+// Moduli per block of the tall/skinny product (three or five).  A block has
+// 128 rows, strips are dealt to the 8 XCDs in turn, and a CU holds one block,
+// so an XCD with `per` strips runs its 15 / G blocks each in rounds of 32.  A
+// round of five moduli takes 4/3 of one of three (conversion is paid once per
+// group): five wherever that gives fewer or cheaper rounds, three where it
+// would only leave CUs idle.  All-byte calls with n = 128, k = 2000, five /
+// three: 1100 rows (1 round / 1) 105 / 83 us, 4096 (1 / 1) 112 / 94, 6528 (1 /
+// 2) 120 / 160, 10880 (2 / 2) 219 / 171, 13056 (2 / 3) 223 / 241, 22000 (3 / 4)
+// 348 / 348, 44000 (5 / 7) 618 / 648; 1024 x 128 x 131072 4.67 / 3.55 ms.
+constexpr int64_t kFusedRows = 128;
+constexpr int fused_moduli(int64_t m) {
+  const int64_t per = ((m + kFusedRows - 1) / kFusedRows + 7) / 8;
+  const int64_t r5 = (3 * per + 31) / 32, r3 = (5 * per + 31) / 32;
+  return 4 * r5 > 3 * r3 ? 3 : 5;
+}
+
 // The one-launch product's limits: rows and columns (32-bit indices), k
 // (exact int32 sums; the rule below never asks for more), and leading
 // dimensions (32-bit offsets within a 64-row chunk).

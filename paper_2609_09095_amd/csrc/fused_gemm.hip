@@ -7,7 +7,8 @@
 // output tile spans all of B (lambda_A = 1: every element of A is converted
 // once per modulus it serves).
 //
-// A block owns 128 rows of A, all (at most 128) columns and G = 5 moduli; its
+// A block owns 128 rows of A, all (at most 128) columns and G = 5 moduli, or G =
+// 3 where so few strips leave CUs idle (fused_moduli in dispatch.hpp); its
 // 16 wavefronts convert a 128 x 64 slab per stage, then multiply it with B's
 // slabs on v_mfma_i32_32x32x32_i8 (32 x 32 outputs per wavefront and
 // modulus), the next slab's FP64 loads in flight meanwhile.  The blocks of one
@@ -22,6 +23,7 @@
 // as they are converted, one stage ahead (two sets, two stages ahead, were
 // worth 3 % with three moduli), addresses are 32-bit offsets recomputed from
 // the lane index, and no masks are kept.
+#include "dispatch.hpp"
 #include "kernels.hpp"
 #include "moduli.hpp"
 #include "residues.hpp"
@@ -62,9 +64,10 @@ __constant__ double kInvF[kRA] = {
     1.0 / kModulusA[8],  1.0 / kModulusA[9],  1.0 / kModulusA[10], 1.0 / kModulusA[11],
     1.0 / kModulusA[12], 1.0 / kModulusA[13], 1.0 / kModulusA[14]};
 
-// mode 3's group products N (below 2^24) and RN(1/N)
+// mode 3's group products N (below 2^24 for G = 3, 2^40 for G = 5) and RN(1/N)
 template <int G>
 struct GroupConst {
+  static_assert(groups_in_range(kModulusA, G), "one exact reduction per group");
   double n[kRA / G], inv[kRA / G];
 };
 template <int G>
@@ -149,7 +152,7 @@ __device__ __forceinline__ int cmod_sum(int x, double m, double minv) {
 // 128 rows of A per block, 16 wavefronts: wavefront w converts rows
 // 8 w .. 8 w + 7 of each slab and owns the 32 x 32 outputs (w / 4, w % 4) of
 // every modulus of its group.
-constexpr int FBM = 128;
+constexpr int FBM = kFusedRows;
 // Leading dimensions of A below this go through a buffer resource: 8 lda is
 // then a positive signed 24-bit factor and 128 rows stay below 2^31 bytes.
 constexpr int64_t kBufLda = (int64_t)1 << 20;
@@ -413,13 +416,22 @@ hipError_t launch_fused_bytes(int quant, int64_t m, int64_t n, int64_t k, int64_
   const bool tz = quant == kQuantTZ;
   // |y| <= 2^t: the nearest quotient up to 2^52, then the group reduction
   const int mode = t <= 51 ? 1 : (t == 52 ? 2 : 3);
-#define OZ_FUSED(MODE)                                                                           \
-  return tz ? launch_fused_g<5, MODE, true>(m, n, k, kp, A, lda, sigma, pb, cres, stream)       \
-            : launch_fused_g<5, MODE, false>(m, n, k, kp, A, lda, sigma, pb, cres, stream)
-  if (mode == 1) OZ_FUSED(1);
-  if (mode == 2) OZ_FUSED(2);
+  const bool three = fused_moduli(m) == 3;
+#define OZ_FUSED_G(G, MODE)                                                                \
+  return tz ? launch_fused_g<G, MODE, true>(m, n, k, kp, A, lda, sigma, pb, cres, stream) \
+            : launch_fused_g<G, MODE, false>(m, n, k, kp, A, lda, sigma, pb, cres, stream)
+#define OZ_FUSED(MODE)           \
+  if (three) OZ_FUSED_G(3, MODE); \
+  OZ_FUSED_G(5, MODE)
+  if (mode == 1) {
+    OZ_FUSED(1);
+  }
+  if (mode == 2) {
+    OZ_FUSED(2);
+  }
   OZ_FUSED(3);
 #undef OZ_FUSED
+#undef OZ_FUSED_G
 }
 
 }  // namespace oz

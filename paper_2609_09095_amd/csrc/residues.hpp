@@ -113,8 +113,9 @@ __device__ __forceinline__ void reduce_group(const double (&y)[E], double N, dou
     zlo[c] = low_word(z[c] + kMagic);
   }
 }
-// the product of moduli i .. i + count - 1, below 2^48 and at least 2^30
-// (so q N is within 2^-12 N of y at |y| <= 2^58)
+// the product of moduli i .. i + count - 1, below 2^48 and at least 2^18
+// (at |y| <= 2^58 the quotient then errs by at most 2^-12, so that |y - q N| is
+// at most N (1/2 + 2^-12))
 template <int R>
 constexpr int64_t group_product(const int (&m)[R], int i, int count) {
   int64_t p = 1;
@@ -127,7 +128,7 @@ constexpr bool groups_in_range(const int (&m)[R], int count) {
   if (R % count) return false;
   for (int i = 0; i < R; i += count) {
     const int64_t p = group_product(m, i, count);
-    if (p >= (int64_t)1 << 48 || p < (int64_t)1 << 30) return false;
+    if (p >= (int64_t)1 << 48 || p < (int64_t)1 << 18) return false;
   }
   return true;
 }

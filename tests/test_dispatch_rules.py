@@ -40,3 +40,17 @@ def test_joint_scan_grid_fits():
                 assert L.rule_scan_both_blocks(m, n, k) * 256 < 1 << 32, (m, n, k)
     assert not L.rule_both_at_once((1 << 24) - 1, 1, 1025, k_pad(1025), PLENTY)
     assert L.rule_both_at_once((1 << 24) - 100, 1, 1025, k_pad(1025), PLENTY)
+
+
+def test_tall_product_fills_its_rounds():
+    """Moduli per block of the tall/skinny product: with either count a CU
+    holds one block and an XCD (32 CUs) every eighth strip of 128 rows; a
+    round with five moduli takes 4/3 of one with three.  The chosen count is
+    never the slower one by that reckoning, and few strips take three."""
+    L = rules()
+    for m in [*range(1024, 60000, 97), 262144, 1 << 22, 1 << 24]:
+        per = -(-(-(-m // 128)) // 8)
+        cost = {g: (4 if g == 5 else 3) * -(-(15 // g) * per // 32) for g in (3, 5)}
+        g = L.rule_fused_moduli(m)
+        assert cost[g] == min(cost.values()), m
+    assert [L.rule_fused_moduli(m) for m in (1024, 6144, 6145, 10241, 12288, 12289, 262144)] == [3, 3, 5, 3, 3, 5, 5]
