@@ -23,4 +23,21 @@ __device__ __forceinline__ double native_dot(const double* __restrict__ a, const
   return s;
 }
 
+// N such outputs at once, each as above: the dots' chains run side by side,
+// since one is bound by the latency of its loads and additions.
+template <int N>
+__device__ __forceinline__ void native_dots(const double* const (&a)[N], const double* const (&b)[N], int64_t ldb,
+                                            int64_t k, double (&s)[N]) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int j = 0; j < N; ++j) s[j] = 0.0;
+  for (int64_t l = 0; l < k; ++l) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const double p = a[j][l] * b[j][l * ldb];
+      s[j] = s[j] + p;
+    }
+  }
+}
+
 }  // namespace oz

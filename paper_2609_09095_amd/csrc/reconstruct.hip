@@ -29,6 +29,7 @@
 //    integer and rounded once.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
 #include <utility>
 
 #include "fp64_round.hpp"
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(int64_t m, int64_t n,
 // 32768^2 C -= AB 7.6 -> 5.9 ms (5.6 TB/s), 8192^2 476 -> 413 us, 4096^2 115 ->
 // 94 us, 100000 x 100 114 -> 65 us, 262144 x 8 131 -> 20 us; with Garner's
 // digits runs gained nothing on square outputs.
-constexpr int kRun = 1024, kSlab = kRun + 256;
+constexpr int kRun = 1024, kSlab = kRun + 256, kPerThread = kRun / 256;
 using lds_ptr_r = __attribute__((address_space(3))) void*;
 
 // NATIVE: flagged outputs are re-issued here; else they get `fill`.
@@ -236,15 +237,45 @@ __global__ __launch_bounds__(256) void reconstruct_runs_kernel(int64_t mn, int n
   const float rn = 1.0f / (float)n;
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
+  // output o of the run: rows onward from row0 and the column; below 1024
+  // columns the FP32 quotient of c + 1/2 (c < 2^11) is off by far less than the
+  // 1/(2n) to an integer
+  auto place = [&](int o, int& dr, int& col) __attribute__((always_inline)) {
+    col = col0 + o;
+    dr = n >= kRun ? (col >= n ? 1 : 0) : (int)(((float)col + 0.5f) * rn);
+    col -= dr * n;
+  };
+  [[maybe_unused]] unsigned flagged = 0;  // bit j: output tid + 256 j awaits its re-issue
+  // N = kPerThread: bit j's output is dot j, with an unflagged one repeating the
+  // first flagged; N = 1: that one
+  [[maybe_unused]] auto reissue = [&]<int N>(std::integral_constant<int, N>) __attribute__((always_inline)) {
+    const double *a[N], *b[N];
+    double s[N];
+    const int first = __builtin_ctz(flagged);
+    auto output = [&](int j) { return N > 1 && (flagged >> j & 1) ? j : first; };
 #pragma unroll
-  for (int j = 0; j < kRun / 256; ++j) {
+    for (int j = 0; j < N; ++j) {
+      int dr, col;
+      place(threadIdx.x + 256 * output(j), dr, col);
+      a[j] = nat.A + (row0 + dr) * nat.lda;
+      b[j] = nat.B + col;
+    }
+    native_dots(a, b, nat.ldb, nat.k, s);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      if (N > 1 && !(flagged >> j & 1)) continue;
+      int dr, col;
+      place(threadIdx.x + 256 * output(j), dr, col);
+      double* out = C + (row0 + dr) * ldc + col;
+      *out = subtract ? *out - s[j] : s[j];
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < kPerThread; ++j) {
     const int o = threadIdx.x + 256 * j;
     if (i0 + o >= mn) break;
-    // rows onward from row0: below 1024 columns the FP32 quotient of
-    // c + 1/2 (c < 2^11) is off by far less than the 1/(2n) to an integer
-    int col = col0 + o;
-    const int dr = n >= kRun ? (col >= n ? 1 : 0) : (int)(((float)col + 0.5f) * rn);
-    col -= dr * n;
+    int dr, col;
+    place(o, dr, col);
     const int sa = ea[row0 + dr], sb = eb[col];
     double* out = C + (row0 + dr) * ldc + col;
     const double old = subtract ? __builtin_nontemporal_load(out) : 0.0;
@@ -256,9 +287,22 @@ __global__ __launch_bounds__(256) void reconstruct_runs_kernel(int64_t mn, int n
         c[q] = slab[q * kSlab + (ALIGNED ? 0 : (int)((q * mn + i0) & 3)) + o];
       r = garner_bytes(c, -sa - sb);
     } else if constexpr (NATIVE) {
-      r = native_dot(nat.A + (row0 + dr) * nat.lda, nat.B + col, nat.ldb, nat.k);
+      flagged |= 1u << j;
+      continue;
     }
     __builtin_nontemporal_store(subtract ? old - r : r, out);
+  }
+  if constexpr (NATIVE) {
+    if (!flagged) return;
+    // the thread's flagged outputs together: a flagged row of 1024 columns is
+    // four of every thread, and one after another they took 1.02 ms at 1024^3
+    // (0.36 together).  Where no thread of the wavefront has more than one (a
+    // flagged column, short rows), that one alone: the others' loads would
+    // cost 20 to 100 %.
+    if (__any(flagged & (flagged - 1)))
+      reissue(std::integral_constant<int, kPerThread>{});
+    else
+      reissue(std::integral_constant<int, 1>{});
   }
 }
 

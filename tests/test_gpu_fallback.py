@@ -13,7 +13,8 @@ import pytest
 import oracle
 import paper_2609_09095_amd as oz
 import workloads
-from gpu_util import assert_bits_equal, log, require_gpu, to_dev
+from gpu_util import assert_bits_equal, log, require_gpu, sample_indices, to_dev
+from routes import route
 
 pytestmark = pytest.mark.gpu
 
@@ -99,3 +100,61 @@ def test_stage_api_and_stored_planes_keep_nan(set):
     torch.cuda.synchronize()
     assert_bits_equal(got, want, "stored-planes C")
     assert np.all(np.isnan(got[[1, 2, 3, 4]])) and np.all(np.isnan(got[:, [2, n - 1]]))
+
+
+# up to 2^22 outputs the re-issue runs inside the reconstruction (each thread
+# has four outputs of a run of 1024, any of which may be flagged), beyond in a
+# launch of its own
+@pytest.mark.parametrize("subtract", [False, True])
+@pytest.mark.parametrize("m, n, k", [(70, 1500, 900), (9, 5000, 800), (3000, 129, 250), (2100, 2050, 130)])
+def test_reissue_of_whole_rows(m, n, k, subtract):
+    import torch
+    assert route(m, n, k) == "staged"
+    A, B = _inputs(m, n, k, 21)
+    A[m - 1, k - 1], A[m // 2, 7] = np.inf, np.nan
+    C0 = workloads.random_matrix(m, n, 1.0, 23) if subtract else None
+    rows = np.unique(np.r_[np.arange(9), m // 2, m - 1, sample_indices(m, 40, 24)])
+    log(f"native re-issue of rows m={m} n={n} k={k} subtract={subtract}")
+    full = torch.full((m, n + 3), 5.0, dtype=torch.float64, device="cuda")
+    C = full[:, :n]
+    if subtract:
+        C.copy_(torch.from_numpy(C0))
+    oz.ozaki25_dgemm_ex(to_dev(A), to_dev(B), C, subtract=subtract)
+    torch.cuda.synchronize()
+    got = C.cpu().numpy()[rows]
+    want = oracle.dgemm(A, B, C_in=C0, rows=rows, want_planes=False).C
+    assert_bits_equal(got, want, "C (sampled rows)")
+    _assert_inf_signs(got, want, "C (sampled rows)")
+    assert bool((full[:, n:] == 5.0).all())
+
+
+def test_reissue_of_a_long_row_costs_one_dot_product():
+    """A flagged row of 1024 columns is four outputs of every thread of its
+    run, one of 256 columns a single one: the dot products run side by side,
+    so the longer row may not add several times the shorter one's time
+    (measured 1.4 to 1.7; one after another 4.5)."""
+    import torch
+    m, k = 1024, 4096
+
+    def best(A, B, C):
+        times = []
+        for _ in range(7):
+            s, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            s.record()
+            oz.ozaki25_dgemm_ex(A, B, C)
+            e.record()
+            torch.cuda.synchronize()
+            times.append(s.elapsed_time(e))
+        return min(times)
+
+    added = {}
+    for n in (256, 1024):
+        assert route(m, n, k) == "staged"
+        A = to_dev(workloads.random_matrix(m, k, 1.0, 31))
+        B = to_dev(workloads.random_matrix(k, n, 1.0, 32))
+        C = torch.empty((m, n), dtype=torch.float64, device="cuda")
+        clean = best(A, B, C)
+        A[300, 5] = float("nan")
+        added[n] = best(A, B, C) - clean
+        log(f"flagged row, n={n}: clean {clean:.3f} ms, added {added[n]:.3f} ms")
+    assert added[1024] < 3.0 * added[256], added
