@@ -91,4 +91,17 @@ constexpr bool both_at_once(int64_t m, int64_t n, int64_t k, int64_t kp, int64_t
          (fused_a(m, n) || (m + n) * kp * (int64_t)sizeof(double) <= (int64_t)256 << 20);
 }
 
+// Whether the reconstruction from stored byte planes (no native re-issue)
+// takes strips of 256 columns, a thread per output and row, rather than runs
+// of 1024 consecutive outputs: where runs are too few to fill the chip, and for
+// whole strips (every store then starts on a line) of up to 2^21 outputs.
+// Strips / runs: 64 x 1024 4.2 / 5.2 us, 256 x 1024 4.6 / 6.1, 128 x 4096 6.4 /
+// 7.0, 11 x 93106 8.9 / 10.2, 2048 x 1024 13.9 / 15.1, level at 4096 x 1024; the
+// other way 4080 x 257 16.6 / 9.7, 16384 x 64 12.2 / 9.1, 1023 x 1025 11.3 /
+// 10.3, 262144 x 8 131 / 20.
+constexpr bool reconstruct_strips(int64_t m, int64_t n) {
+  const int64_t mn = m * n;
+  return n >= 64 && (mn <= 1 << 18 || (mn <= 1 << 20 && n >= 4096) || (mn <= 1 << 21 && n % 256 == 0));
+}
+
 }  // namespace oz

@@ -32,6 +32,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "dispatch.hpp"
 #include "fp64_round.hpp"
 #include "garner_bytes.hpp"
 #include "kernels.hpp"
@@ -386,21 +387,22 @@ hipError_t launch_rec(int64_t m, int64_t n, const RT* cres, const int32_t* ea, c
                       hipStream_t stream) {
   if (m <= 0 || n <= 0) return hipSuccess;
   constexpr bool RUNS = BYTES && sizeof(RT) == 1;
-  if (RUNS && (m * n + kRun - 1) / kRun > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+  const bool strips = !RUNS || (!nat.A && reconstruct_strips(m, n));
+  if (!strips && (m * n + kRun - 1) / kRun > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
   const bool inside = RUNS && nat.A && m * n <= 1 << 22, apart = nat.A && !inside;
   const double fill = nat.A ? 0.0 : __builtin_nan("");
   if (apart && subtract) {
     const hipError_t e = launch_native(m, n, ea, eb, nat, C, ldc, subtract, stream);
     if (e != hipSuccess) return e;
   }
-  if constexpr (RUNS) {
+  if (strips) {
+    hipLaunchKernelGGL((reconstruct_kernel<BYTES, RT>), grid_for(m, n), dim3(256), 0, stream, m, n, cres, ea, eb, C,
+                       ldc, subtract, fill);
+  } else if constexpr (RUNS) {
     if (inside)
       launch_runs<true>(m, n, cres, ea, eb, C, ldc, subtract, fill, nat, stream);
     else
       launch_runs<false>(m, n, cres, ea, eb, C, ldc, subtract, fill, nat, stream);
-  } else {
-    hipLaunchKernelGGL((reconstruct_kernel<BYTES, RT>), grid_for(m, n), dim3(256), 0, stream, m, n, cres, ea, eb, C,
-                       ldc, subtract, fill);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || !apart || subtract) return e;

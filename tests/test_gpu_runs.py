@@ -1,7 +1,8 @@
 """The byte moduli's reconstruction in runs of 1024 outputs: rows shorter than,
 equal to and longer than a run, single rows and columns, a partial last run,
 residue planes on and off a dword boundary, C -= AB and flagged rows and
-columns -- through stored planes, against the oracle, bit for bit."""
+columns -- and in strips of 256 columns, whole and partial, which small and
+wide outputs take: through stored planes, against the oracle, bit for bit."""
 import numpy as np
 import pytest
 
@@ -9,6 +10,7 @@ import oracle
 import paper_2609_09095_amd as oz
 import workloads
 from gpu_util import assert_bits_equal, log, require_gpu, to_dev
+from routes import rules
 
 pytestmark = pytest.mark.gpu
 
@@ -18,10 +20,15 @@ def gpu():
     require_gpu()
 
 
-@pytest.mark.parametrize("m, n, pad", [(257, 1023, 0), (300, 1024, 1), (259, 1025, 3), (2049, 129, 0), (5000, 53, 1),
-                                       (3, 7, 0), (1, 262147, 0), (262147, 1, 2), (513, 513, 1)])
-def test_runs_match_oracle(m, n, pad):
+RUNS = [(257, 1023, 0), (301, 1028, 1), (259, 1025, 3), (2049, 129, 0), (5000, 53, 1), (3, 7, 0), (4, 63, 2),
+        (1, 1048579, 0), (262147, 1, 2), (513, 513, 1), (2049, 1024, 0)]
+STRIPS = [(4, 64, 0), (300, 1024, 1), (1, 262147, 0), (255, 1028, 2), (9, 93106, 1), (2050, 512, 0), (2, 100, 3)]
+
+
+@pytest.mark.parametrize("m, n, pad, strips", [(*c, False) for c in RUNS] + [(*c, True) for c in STRIPS])
+def test_runs_and_strips_match_oracle(m, n, pad, strips):
     import torch
+    assert bool(rules().rule_reconstruct_strips(m, n)) == strips
     k = 3
     A = workloads.random_matrix(m, k, 1.0, 700 + n % 97)
     B = workloads.random_matrix(k, n, 1.0, 701 + m % 89)
