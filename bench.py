@@ -126,7 +126,7 @@ def measured_deconstruction(w, moduli, scan_ms, dec_ms):
     if b is None:
         return {"measured_bytes": None, "measured_frac": None}
     return {"measured_bytes": b,
-            "measured_frac": round(b / ((scan_ms + dec_ms) * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+            "measured_frac": scaled(per_second(b, scan_ms + dec_ms), HBM_PEAK_GBS * 1e9, 4),
             "measured_note": "bytes beyond L2 (HBM or the last-level cache); an upper bound on HBM use"}
 
 
@@ -312,30 +312,73 @@ def fused(w):
     return w.n <= 128 and w.m >= 1024
 
 
+def one_launch(w):
+    """Whether ozaki25_dgemm* run the product as one kernel (the library's
+    rule for small products): its stage events then bracket that kernel as the
+    residue-GEMM stage, and there are no planes, scan, deconstruction or
+    reconstruction to price.  fused(w) matters only where this is false."""
+    if max(w.m, w.n) > 1 << 24 or w.k > 4096:
+        return False
+    rounds = -(-(-(-w.m // 32) * -(-w.n // 32)) // 256)
+    chunks = -(-w.k // 64)
+    staged = 220 + 23 * w.m // 1024 if fused(w) else 200 + 125 * w.m * w.n // (1 << 20)
+    return 2 * rounds * (50 + 22 * chunks) + rounds * chunks <= 2 * staged + 15 * chunks
+
+
+def joint(w):
+    """Whether both operands' deconstructions share a launch (the library's
+    rule, on a workspace whose residues leave room for the partial maxima, as
+    every staged workload's do)."""
+    rows = 64 if -(-w.n // 64) * -(-w.k // 64) <= 1024 else 256
+    return -(-w.k // rows) <= 2048 and (w.m + w.n) * (-(-w.k // 128) * 128) * 8 <= 256 << 20
+
+
+ONE_LAUNCH_NOTE = "the whole product runs as one kernel (one_kernel): this stage does not exist"
+
+
+def per_second(amount, ms):
+    """amount per second over ms, None where the events read no time."""
+    return amount / (ms * 1e-3) if ms > 0 else None
+
+
+def scaled(x, scale, digits):
+    return None if x is None else round(x / scale, digits)
+
+
 def rates(w, cfg, ms, stages):
     scan_ms, dec_ms, gemm_ms, rec_ms = stages
+    one = one_launch(w)
     elems = w.m * w.k + w.k * w.n
-    dec_bytes = elems * (8 + cfg["plane_bytes"])
-    rec_bytes = w.m * w.n * (cfg["cres_bytes"] + 8 + (8 if w.subtract else 0))
-    gemm_ops = 2.0 * (cfg["fused_products"] if fused(w) else cfg["products"]) * w.m * w.n * w.k
-    return dict(tflops=w.flops / (ms * 1e-3) / 1e12, gemm_ops=gemm_ops,
-                gemm_tops=gemm_ops / (gemm_ms * 1e-3) / 1e12, dec_bytes=dec_bytes,
-                dec_gbs=dec_bytes / (dec_ms * 1e-3) / 1e9,
-                stage_gbs=(dec_bytes + elems * 8) / ((dec_ms + scan_ms) * 1e-3) / 1e9,
-                rec_gbs=rec_bytes / (rec_ms * 1e-3) / 1e9,
-                roof=cfg["peak"] / cfg["products"])
+    dec_bytes = None if one else elems * (8 + cfg["plane_bytes"])
+    rec_bytes = None if one else w.m * w.n * (cfg["cres_bytes"] + 8 + (8 if w.subtract else 0))
+    gemm_ops = 2.0 * (cfg["fused_products"] if not one and fused(w) else cfg["products"]) * w.m * w.n * w.k
+    return dict(tflops=w.flops / (ms * 1e-3) / 1e12, gemm_ops=gemm_ops, gemm_ops_s=per_second(gemm_ops, gemm_ms),
+                dec_bytes=dec_bytes, dec_bytes_s=None if one else per_second(dec_bytes, dec_ms),
+                stage_bytes_s=None if one else per_second(dec_bytes + elems * 8, dec_ms + scan_ms),
+                rec_bytes_s=None if one else per_second(rec_bytes, rec_ms), roof=cfg["peak"] / cfg["products"])
+
+
+def hbm_roofline(bytes_s, **extra):
+    return {"bound": "hbm", "achieved": scaled(bytes_s, 1e9, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": scaled(bytes_s, HBM_PEAK_GBS * 1e9, 4), **extra}
+
+
+def rec_roofline(w, rt):
+    return hbm_roofline(rt["rec_bytes_s"], **({"note": ONE_LAUNCH_NOTE} if one_launch(w) else {}))
 
 
 def dec_roofline(w, cfg, rt, scan_ms, dec_ms):
+    if one_launch(w):
+        return hbm_roofline(None, kernel=None, bytes_per_call=None, note=ONE_LAUNCH_NOTE)
     if fused(w):
-        return {"bound": "hbm", "kernel": None, "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": None, "bytes_per_call": None,
-                "note": "storage mode F for A: no planes of A are made (the product kernel " + cfg["fused_kernel"]
-                        + " quantises A); the scan stage holds A's exponent scan, the deconstruct stage B's"}
-    return {"bound": "hbm", "kernel": cfg["dec_kernel"], "achieved": round(rt["dec_gbs"], 1),
-            "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(rt["dec_gbs"] / HBM_PEAK_GBS, 4),
-            "bytes_per_call": rt["dec_bytes"], "stage_with_scan_gbs": round(rt["stage_gbs"], 1),
-            **measured_deconstruction(w, "a15", scan_ms, dec_ms)}
+        return hbm_roofline(None, kernel=None, bytes_per_call=None,
+                            note="storage mode F for A: no planes of A are made (the product kernel "
+                                 + cfg["fused_kernel"] + " quantises A); the scan stage holds the exponent scans, "
+                                 "the deconstruct stage B's planes")
+    return hbm_roofline(rt["dec_bytes_s"], kernel="deconstruct_bytes_both_kernel" if joint(w) else cfg["dec_kernel"],
+                        bytes_per_call=rt["dec_bytes"],
+                        stage_with_scan_gbs=scaled(rt["stage_bytes_s"], 1e9, 1),
+                        **measured_deconstruction(w, "a15", scan_ms, dec_ms))
 
 
 def gemm_kernel_name(w, cfg):
@@ -355,12 +398,16 @@ def gemm_kernel_name(w, cfg):
 
 
 def gemm_roofline(w, cfg, rt):
-    r = {"bound": "mfma", "kernel": cfg["fused_kernel"] if fused(w) else gemm_kernel_name(w, cfg),
-         "achieved": round(rt["gemm_tops"], 2), "peak": cfg["peak"], "unit": "TOP/s",
-         "frac": round(rt["gemm_tops"] / cfg["peak"], 4),
-         "traffic": None if fused(w) else measured_traffic(w, "a15"), "ops_per_launch": rt["gemm_ops"],
+    one = one_launch(w)
+    kernel = "one_kernel" if one else cfg["fused_kernel"] if fused(w) else gemm_kernel_name(w, cfg)
+    r = {"bound": "mfma", "kernel": kernel, "achieved": scaled(rt["gemm_ops_s"], 1e12, 2), "peak": cfg["peak"],
+         "unit": "TOP/s", "frac": scaled(rt["gemm_ops_s"], cfg["peak"] * 1e12, 4),
+         "traffic": None if one or fused(w) else measured_traffic(w, "a15"), "ops_per_launch": rt["gemm_ops"],
          "note": cfg["note"]}
-    if fused(w):
+    if one:
+        r["note"] = (f"one launch: scans, residues, {cfg['products']} products and reconstruction per 32 x 32 tile; "
+                     "the kernel is bound by latency and by converting A and B (VALU), not by the matrix cores")
+    elif fused(w):
         r["note"] = (f"storage mode F: {cfg['fused_products']} products x 2mnk per launch; the kernel is bound by "
                      "converting A (VALU), not by the matrix cores")
     return r
@@ -493,9 +540,8 @@ def main():
         del Cn
         log("[bench] vendor low-precision GEMM on one residue product's shape")
         vendor = vendor_lowp_gemm(torch, w, cfg, args.steps)
-        if vendor.get("achieved"):
-            per_product = rt["gemm_tops"]
-            vendor["residue_gemm_over_vendor"] = round(per_product / vendor["achieved"], 4)
+        if vendor.get("achieved") and not one_launch(w):
+            vendor["residue_gemm_over_vendor"] = scaled(rt["gemm_ops_s"], vendor["achieved"] * 1e12, 4)
 
     result = {
         "metric": "emulated FP64 TFLOPS (2mnk/s) + deconstruction GB/s vs HBM/MFMA roofs",
@@ -517,8 +563,7 @@ def main():
                    "route": cfg["route"]},
         "roofline": gemm_roofline(w, cfg, rt),
         "roofline_deconstruct": dec_roofline(w, cfg, rt, scan_ms, dec_ms),
-        "roofline_reconstruct": {"bound": "hbm", "achieved": round(rt["rec_gbs"], 1), "peak": HBM_PEAK_GBS,
-                                 "unit": "GB/s", "frac": round(rt["rec_gbs"] / HBM_PEAK_GBS, 4)},
+        "roofline_reconstruct": rec_roofline(w, rt),
         "stage_ms": {"scan": round(scan_ms, 4), "deconstruct": round(dec_ms, 4), "residue_gemm": round(gemm_ms, 4),
                      "reconstruct": round(rec_ms, 4)},
         "emulation_roof_tflops": round(rt["roof"], 2),

@@ -1,6 +1,7 @@
 """bench.py's command line on a machine without a GPU: more than one GPU is
-refused with a message, the per-set constants describe the kernels, and the
-roofline names the kernel the library launches for each workload."""
+refused with a message, the per-set constants describe the kernels, the
+roofline names the kernel the library launches for each workload, and a stage
+that does not run is priced as none."""
 import os
 import subprocess
 import sys
@@ -76,3 +77,44 @@ def test_gemm_kernel_names(monkeypatch):
     for name in ("square", "ragged", "reach", "tiny"):
         assert bench.gemm_kernel_name(W[name], s12) == "residue_gemm_kernel<int16>", name
         assert bench.gemm_kernel_name(W[name], a15) == "residue_gemm_bytes_kernel<int8>", name
+
+
+def test_one_launch_rule_is_the_library_s():
+    """bench.one_launch follows the library's rule (dispatch.hpp) on both
+    sides of its line; beyond it fused(w) the storage-mode rule, and joint(w)
+    the joint launches'."""
+    import itertools
+    sys.path.insert(0, ROOT)
+    sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+    import bench
+    import workloads
+    from routes import route, rules
+    sizes = (1, 31, 64, 300, 512, 1023, 1024, 2049, 6000, 40000)
+    seen = set()
+    for m, n, k in itertools.product(sizes, sizes, (1, 64, 65, 300, 640, 768, 1000, 4096, 4097)):
+        w = workloads.Workload("x", m, n, k, 1.0, 1)
+        want = route(m, n, k)
+        seen.add(want)
+        assert bench.one_launch(w) == (want == "one"), (m, n, k)
+        assert want == "one" or bench.fused(w) == (want == "fused"), (m, n, k)
+        if want == "staged":
+            assert bench.joint(w) == bool(rules().rule_both_at_once(m, n, k, -(-k // 128) * 128, 1 << 40)), (m, n, k)
+    assert seen == {"one", "fused", "staged"}
+
+
+def test_stages_that_do_not_run_are_not_priced():
+    """The tiny workload runs as one kernel: its event gaps, zero or not, are
+    no scan, deconstruction or reconstruction rates."""
+    sys.path.insert(0, ROOT)
+    import bench
+    import workloads
+    w, cfg = workloads.WORKLOADS["tiny"], bench.DGEMM["s12"]
+    for stages in ([0.0, 0.0, 0.007, 0.0], [0.002, 0.002, 0.007, 0.002]):
+        rt = bench.rates(w, cfg, 0.01, stages)
+        for r in (bench.dec_roofline(w, cfg, rt, *stages[:2]), bench.rec_roofline(w, rt)):
+            assert r["achieved"] is None and r["frac"] is None and "one kernel" in r["note"]
+        r = bench.gemm_roofline(w, cfg, rt)
+        assert r["kernel"] == "one_kernel" and r["achieved"] == round(2 * 15 * 64 ** 3 / 0.007e-3 / 1e12, 2)
+    w = workloads.WORKLOADS["reach"]
+    rt = bench.rates(w, cfg, 0.05, [0.007, 0.02, 0.02, 0.006])
+    assert bench.dec_roofline(w, cfg, rt, 0.007, 0.02)["achieved"] > 0 and bench.rec_roofline(w, rt)["achieved"] > 0
