@@ -1,9 +1,10 @@
 """ozaki25_dgemm_ex with a caller workspace enqueues kernels only (no
 allocation, no memset), so a HIP graph can capture it: every replay of the
 captured graph, with eager work and synchronisations between replays, gives
-the eager result bit for bit (both modulus sets; the split-k path included,
-and at 1800 x 1500 x 256 the published set's residue GEMM in its form with
-one block per CU walking 576 tiles)."""
+the eager result bit for bit (both modulus sets; one kernel at 64^3, the split-k
+path, storage mode F at 5000 x 100 x 300, separate scans at 3 x 5 x 600000, and at
+1800 x 1500 x 256 the residue GEMM in its form with one block per CU walking
+720 tiles)."""
 import numpy as np
 import pytest
 
@@ -20,7 +21,8 @@ def gpu():
 
 
 @pytest.mark.parametrize("dset", [oz.S12, oz.A15])
-@pytest.mark.parametrize("m,n,k", [(64, 64, 64), (300, 129, 700), (256, 256, 4096), (1800, 1500, 256)])
+@pytest.mark.parametrize("m,n,k", [(64, 64, 64), (300, 129, 700), (256, 256, 4096), (1800, 1500, 256), (5000, 100, 300),
+                                   (3, 5, 600000)])
 def test_graph_replays_match_eager(dset, m, n, k):
     import torch
     log(f"graph capture set={dset} m={m} n={n} k={k}")

@@ -1,14 +1,14 @@
 """Emulated DGEMM at shapes where the residue GEMM (compact output, whole
 k) runs one block per compute unit and each block walks several output
 tiles in turn, loading the next tile's first K stage while it stores the
-current one: for the published set 12 moduli x (1800/256 -> 8) x
-(1500/256 -> 6) = 576 tiles, for the all-byte set 15 x 8 x 6 = 720, and more
-below, against 256 CUs.  Ragged and exact tile edges, C = AB
-and C -= AB, both quantisers (Eq. (scale)), the accurate mode (Sec. 2,
-Eq. (alpha)) and k from 2 to 16 K stages of 128 (the form serves short k
-only).  The final C on a seeded sample of
-rows and columns (both ends included) is compared bit for bit with the
-oracle's."""
+current one: 15 moduli x (1800/256 -> 8) x (1500/256 -> 6) = 720 tiles, and
+more below, against 256 CUs.  ozaki25_dgemm* run the byte moduli's products
+for either set; the published set's own FP8 products run from stored planes
+(12 moduli, 576 tiles).  Ragged and exact tile edges, C = AB and C -= AB, both
+quantisers (Eq. (scale)), the accurate mode (Sec. 2, Eq. (alpha)) and k from 2
+to 16 K stages of 128 (the form serves an even count of at most 16; 3 stages
+take a block per tile).  The final C on a seeded sample of rows and columns
+(both ends included) is compared bit for bit with the oracle's."""
 import numpy as np
 import pytest
 
@@ -75,3 +75,25 @@ def test_stored_planes_tall_narrow(set):
     rows = sample_indices(m, 128, 8202)
     want = oracle.dgemm(A, B, rows=rows, set=set, want_planes=False).C
     assert_bits_equal(C.cpu().numpy()[rows], want, "C (sampled rows)")
+
+
+@pytest.mark.parametrize("set", SETS)
+@pytest.mark.parametrize("m, n, k, sub", [(1800, 1500, 256, True), (1800, 1500, 384, False), (2048, 2048, 512, False),
+                                          (1800, 1800, 2048, True)])
+def test_stored_planes_wide(set, m, n, k, sub):
+    """Storage mode P more than 128 columns wide (256 x 256 tiles), more than
+    two tiles per CU of each set's own products."""
+    import torch
+    assert (12 if set == oz.S12 else 15) * -(-m // 256) * -(-n // 256) >= 512
+    log(f"[multitile] mode P set={set} m={m} n={n} k={k}")
+    A = workloads.random_matrix(m, k, 1.0, 8300)
+    B = workloads.random_matrix(k, n, 1.0, 8301)
+    C0 = workloads.random_matrix(m, n, 1.0, 8302) if sub else None
+    planesA, expsA = oz.ozaki25_deconstruct(0, to_dev(A), set=set)
+    planesB, expsB = oz.ozaki25_deconstruct(1, to_dev(B), set=set)
+    C = to_dev(C0) if sub else torch.full((m, n), 7.0, dtype=torch.float64, device="cuda")
+    oz.ozaki25_dgemm_planes(k, planesA, expsA, planesB, expsB, C, subtract=sub, set=set)
+    torch.cuda.synchronize()
+    rows, cols = sample_indices(m, 64, 8303), sample_indices(n, 64, 8304)
+    want = oracle.dgemm(A, B, C_in=C0, rows=rows, cols=cols, set=set, want_planes=False).C
+    assert_bits_equal(C.cpu().numpy()[np.ix_(rows, cols)], want, "C (sampled)")

@@ -431,8 +431,10 @@ def test_dgemm_stage_events():
 
 @pytest.mark.parametrize("m,n,k,seed", [(40, 300, 8576, 81), (24, 40, 70000, 82), (256, 256, 1024, 83)])
 def test_dgemm_split_k_matches_oracle(m, n, k, seed):
-    """Few output tiles: the fused path splits the k range across blocks
-    (uneven stage ranges) and sums the partial products mod m."""
+    """Few output tiles: the k range is split across blocks (uneven stage
+    ranges) and the partial products summed mod m -- the byte moduli's, which
+    ozaki25_dgemm runs for this set; the FP8 products' split is held to the
+    oracle through stored planes."""
     log(f"dgemm split-k m={m} n={n} k={k}")
     A = workloads.random_matrix(m, k, 1.0, seed)
     B = workloads.random_matrix(k, n, 1.0, seed + 1)
@@ -444,7 +446,8 @@ def test_dgemm_split_k_matches_oracle(m, n, k, seed):
 @pytest.mark.parametrize("m,n,k,seed", [(300, 128, 700, 84), (300, 129, 700, 85), (513, 96, 2000, 86),
                                         (260, 1, 129, 87)])
 def test_dgemm_narrow_tiles_match_oracle(m, n, k, seed):
-    """At most 128 columns use the 512 x 128 tile (n = 129 the 256 x 256 one)."""
+    """At most 128 columns use the 512 x 128 tile (n = 129 the 256 x 256 one),
+    here in ozaki25_residue_gemm; C by ozaki25_dgemm's own route."""
     log(f"dgemm narrow m={m} n={n} k={k}")
     A = workloads.random_matrix(m, k, 1.0, seed)
     B = workloads.random_matrix(k, n, 1.0, seed + 1)

@@ -1,17 +1,19 @@
 """Seeded random shapes through the emulated DGEMM, bit for bit against the
-oracle (any NaN matching any NaN): ragged m, n and k on both sides of the
-tall/skinny threshold (storage mode F for A at most 128 columns and at least
-1024 rows, the materialised planes otherwise), both modulus sets, both
+oracle (any NaN matching any NaN): ragged m, n and k, both modulus sets, both
 quantisers (Eq. (scale)), C = AB and C -= AB, the fixed-t scales and the
 accurate mode (Sec. 2, Eq. (alpha)), and a spread of exponent ranges, each
-drawn per case from one seeded generator."""
+drawn per case from one seeded generator.  The first cases are small (with
+the fixed-t scales they run as one kernel); the others are drawn for each
+route of the fixed-t scales: one kernel over many rounds of tiles, materialised
+planes, and storage mode F with three and with five moduli per block."""
 import numpy as np
 import pytest
 
 import oracle
 import paper_2609_09095_amd as oz
 import workloads
-from gpu_util import assert_bits_equal, log, require_gpu, to_dev
+from gpu_util import assert_bits_equal, log, require_gpu, sample_indices, to_dev
+from routes import route, rules
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +59,42 @@ def test_random_shape(i):
     want = oracle.dgemm(A, B, C_in=C0, set=c["set"], accurate=c["accurate"], want_planes=False,
                         quant=oracle.TZ if c["tz"] else oracle.RN).C
     assert_bits_equal(_run(A, B, C0, c), want, f"C (case {i})")
+
+
+ROUTES = ["one", "staged", "fused3", "fused5"]
+
+
+def _routed_case(name, i):
+    rng = np.random.default_rng(7500 + 100 * ROUTES.index(name) + i)
+
+    def log_uniform(lo, hi):
+        return int(round(np.exp(rng.uniform(np.log(lo), np.log(hi)))))
+
+    while True:
+        if name == "one":
+            m, n, k = log_uniform(300, 20000), log_uniform(20, 2000), log_uniform(1, 500)
+            found = route(m, n, k) == "one" and -(-m // 32) * -(-n // 32) > 256
+        elif name == "staged":
+            m, n, k = log_uniform(1, 3000), log_uniform(1, 3000), log_uniform(1, 3000)
+            found = route(m, n, k) == "staged" and m * n <= 3000000
+        else:
+            m, n, k = log_uniform(1024, 15000), log_uniform(1, 128), log_uniform(8, 3000)
+            found = route(m, n, k) == "fused" and rules().rule_fused_moduli(m) == int(name[5])
+        if found:
+            break
+    return dict(m=m, n=n, k=k, set=i % 2, tz=bool(rng.integers(0, 2)), sub=bool(rng.integers(0, 2)), accurate=False,
+                s=float(rng.choice([0.5, 1.0, 2.0, 4.0])), seed=7900 + i)
+
+
+@pytest.mark.parametrize("i", range(8))
+@pytest.mark.parametrize("name", ROUTES)
+def test_random_shape_of_each_route(name, i):
+    c = _routed_case(name, i)
+    log(f"sweep {name} case {i}: {c}")
+    A = workloads.random_matrix(c["m"], c["k"], c["s"], c["seed"])
+    B = workloads.random_matrix(c["k"], c["n"], c["s"], c["seed"] + 1)
+    C0 = workloads.random_matrix(c["m"], c["n"], 1.0, c["seed"] + 2) if c["sub"] else None
+    rows, cols = sample_indices(c["m"], 100, c["seed"]), sample_indices(c["n"], 200, c["seed"])
+    want = oracle.dgemm(A, B, C_in=C0, rows=rows, cols=cols, set=c["set"], want_planes=False,
+                        quant=oracle.TZ if c["tz"] else oracle.RN).C
+    assert_bits_equal(_run(A, B, C0, c)[np.ix_(rows, cols)], want, f"C ({name} case {i}, sampled)")

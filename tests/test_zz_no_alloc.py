@@ -5,8 +5,9 @@ ozaki25_dgemm_ex with a caller workspace, bit for bit, through the C ABI.
 Two calls in a row share the array, the second with a smaller input, so
 anything the first call left behind that the second depended on would
 show; one product splits its k range (per-split partials in the array).
-The published and the all-byte set, C = AB and C -= AB; the first product
-is also held to the oracle."""
+The published and the all-byte set, C = AB and C -= AB; the second product
+is also held to the oracle.  Both reach the array (one-kernel products leave it
+alone), and one that does not runs between two that do."""
 import numpy as np
 import pytest
 
@@ -14,6 +15,7 @@ import oracle
 import paper_2609_09095_amd as oz
 import workloads
 from gpu_util import assert_bits_equal, log, require_gpu, to_dev
+from routes import route
 
 pytestmark = pytest.mark.gpu
 
@@ -48,8 +50,9 @@ def _noalloc(A, B, C0, subtract, set):
 @pytest.mark.parametrize("set", [oz.S12, oz.A15])
 @pytest.mark.parametrize("subtract", [False, True])
 def test_noalloc_matches_dgemm_ex_twice(set, subtract):
-    shapes = [(1000, 1024, 1000), (130, 257, 300)]
+    shapes = [(1000, 1024, 1000), (130, 257, 1100)]
     for call, (m, n, k) in enumerate(shapes):
+        assert route(m, n, k) == "staged"
         log(f"noalloc set={set} subtract={subtract} call {call}: m={m} n={n} k={k}")
         A = workloads.random_matrix(m, k, 1.0, 300 + call)
         B = workloads.random_matrix(k, n, 1.0, 310 + call)
@@ -63,8 +66,10 @@ def test_noalloc_matches_dgemm_ex_twice(set, subtract):
 
 def test_noalloc_split_k_then_smaller():
     """256 x 256 x 2048 splits the k range of its few tiles (partials in the
-    array), then a smaller product without split."""
-    for call, (m, n, k) in enumerate([(256, 256, 2048), (64, 64, 64)]):
+    array), then a product that runs as one kernel and does without the array,
+    then one without split."""
+    for call, (m, n, k) in enumerate([(256, 256, 2048), (64, 64, 64), (1000, 1024, 200)]):
+        assert route(m, n, k) == ("one" if call == 1 else "staged")
         log(f"noalloc split-k sequence call {call}: m={m} n={n} k={k}")
         A = workloads.random_matrix(m, k, 0.5, 400 + call)
         B = workloads.random_matrix(k, n, 0.5, 410 + call)
@@ -77,7 +82,8 @@ def test_noalloc_tall_skinny_then_smaller(set):
     """Tall and skinny products (storage mode F for A: B's planes and the
     products in the array, A converted inside the product kernel), the
     second one smaller."""
-    for call, (m, n, k) in enumerate([(2048, 100, 700), (1024, 64, 130)]):
+    for call, (m, n, k) in enumerate([(5200, 100, 700), (2100, 128, 300)]):
+        assert route(m, n, k) == "fused"
         log(f"noalloc tall/skinny set={set} call {call}: m={m} n={n} k={k}")
         A = workloads.random_matrix(m, k, 1.0, 500 + call)
         B = workloads.random_matrix(k, n, 1.0, 510 + call)
