@@ -104,8 +104,8 @@ size_t workspace_total(int64_t m, int64_t n, int64_t k, ozaki25_moduli_set set) 
 // (2^117.8 against 2^111.8) with 15 int8 products and 15 plane bytes per
 // element where its limb planes take 36 FP8 products and 30 bytes: 8192^3
 // 14.89 -> 7.61 ms, 32768^2 x 1024 update 39.9 -> 25.5 ms, 262144 x 128 x
-// 4096 10.3 -> 7.1 ms, 512^3 61 -> 43 us.  The stage API and stored planes keep the published moduli's own
-// planes.
+// 4096 10.3 -> 7.1 ms, 512^3 61 -> 43 us.  The stage API and stored planes
+// keep the published moduli's own planes.
 constexpr ozaki25_moduli_set kInner = OZAKI25_MODULI_A15;
 constexpr bool byte_moduli_cover_published() {
   u128 ms = 1, ma = 1;
@@ -265,7 +265,7 @@ hipError_t accurate_exponents(ozaki25_moduli_set set, int64_t m, int64_t n, int6
 }
 
 // The accurate mode's shifts are at most 58: the deconstruction runs at that
-// t (the residue route with one correction).
+// t (the residue route that first reduces modulo a group of moduli).
 constexpr int kAccurateT = oz::kMaxScaleBits;
 
 // The allocation-free entry point's workspace: one static array per GPU
@@ -647,7 +647,7 @@ ozaki25_status ozaki25_dgemm_planes(int64_t m, int64_t n, int64_t k, const uint8
     int16_t* cres = (int16_t*)ws;
     e = oz::launch_residue_gemm_i16(m, n, kp, pa, pb, cres, (int16_t*)part, splits, s);
     if (e == hipSuccess)
-      e = oz::launch_reconstruct_i16(m, n, cres, expsA, expsB, C, ldc, sub, oz::NativeOperands{}, s);
+      e = oz::launch_reconstruct_i16(m, n, cres, expsA, expsB, C, ldc, sub, s);
   }
   if (owned) {
     const hipError_t f = hipFreeAsync(ws, s);

@@ -116,13 +116,15 @@ struct NativeOperands {
   int64_t k = 0;
 };
 
-// Alg. 3: Garner, Horner, lift, single rounding (C = or C -= ).
+// Alg. 3: Garner, Horner, lift, single rounding (C = or C -= ).  Only the byte
+// moduli's compact residues, which ozaki25_dgemm* run on, take operands for
+// the native re-issue; the others write NaN on flagged rows and columns.
 hipError_t launch_reconstruct_i32(int64_t m, int64_t n, const int32_t* cres, const int32_t* ea,
                                   const int32_t* eb, double* C, int64_t ldc, int subtract,
                                   hipStream_t stream);
 hipError_t launch_reconstruct_i16(int64_t m, int64_t n, const int16_t* cres, const int32_t* ea,
                                   const int32_t* eb, double* C, int64_t ldc, int subtract,
-                                  const NativeOperands& nat, hipStream_t stream);
+                                  hipStream_t stream);
 // the same for the fifteen residues of the all-byte set
 hipError_t launch_reconstruct_bytes_i32(int64_t m, int64_t n, const int32_t* cres,
                                         const int32_t* ea, const int32_t* eb, double* C,

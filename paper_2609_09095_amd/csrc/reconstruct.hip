@@ -138,13 +138,12 @@ __device__ __forceinline__ int load_residue(const RT* rowbase, int n, int col) {
 }
 
 // rowq: residues of this output row for modulus 0 (row-uniform); the
-// modulus-q row sits mn elements further per q.
-// fill: the value of an output on a row or column flagged non-finite (NaN,
-// or +0 when the native re-issue supplies those outputs)
+// modulus-q row sits mn elements further per q.  NaN on a row or column flagged
+// non-finite.
 template <typename RT>
 __device__ __forceinline__ double reconstruct_one(const RT* rowq, int64_t mn, int n, int col, int sa,
-                                                  int sb, double fill) {
-  if (sa == INT32_MIN || sb == INT32_MIN) return fill;
+                                                  int sb) {
+  if (sa == INT32_MIN || sb == INT32_MIN) return __builtin_nan("");
   int c[kR], v[kR];
   uint32_t packed[kR / 2];
 #pragma unroll
@@ -161,8 +160,8 @@ __device__ __forceinline__ double reconstruct_one(const RT* rowq, int64_t mn, in
 // ---- all-byte set (Sec. 5.1, candidate A): garner_bytes.hpp
 template <typename RT>
 __device__ __forceinline__ double reconstruct_one_a(const RT* rowq, int64_t mn, int n, int col,
-                                                    int sa, int sb, double fill) {
-  if (sa == INT32_MIN || sb == INT32_MIN) return fill;
+                                                    int sa, int sb) {
+  if (sa == INT32_MIN || sb == INT32_MIN) return __builtin_nan("");
   int c[kRA];
 #pragma unroll
   for (int q = 0; q < kRA; ++q) c[q] = load_residue(rowq + q * mn, n, col);
@@ -176,14 +175,14 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(int64_t m, int64_t n,
                                                           const int32_t* __restrict__ ea,
                                                           const int32_t* __restrict__ eb,
                                                           double* __restrict__ C, int64_t ldc,
-                                                          int subtract, double fill) {
+                                                          int subtract) {
   const int64_t col = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (col >= n) return;
   const int64_t mn = m * n;
   const int sb = eb[col];
   for (int64_t row = blockIdx.y; row < m; row += gridDim.y) {
-    const double r = BYTES ? reconstruct_one_a(cres + row * n, mn, (int)n, (int)col, ea[row], sb, fill)
-                           : reconstruct_one(cres + row * n, mn, (int)n, (int)col, ea[row], sb, fill);
+    const double r = BYTES ? reconstruct_one_a(cres + row * n, mn, (int)n, (int)col, ea[row], sb)
+                           : reconstruct_one(cres + row * n, mn, (int)n, (int)col, ea[row], sb);
     // C streams through once: non-temporal load and store (with the
     // residues' nt loads, the 32768^2 update 8.14 -> 7.74 ms; the all-byte
     // set and 8192^3 unchanged)
@@ -204,11 +203,13 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(int64_t m, int64_t n,
 // With the CRT sum's shorter arithmetic, strips of columns against runs:
 // 32768^2 C -= AB 7.6 -> 5.9 ms (5.6 TB/s), 8192^2 476 -> 413 us, 4096^2 115 ->
 // 94 us, 100000 x 100 114 -> 65 us, 262144 x 8 131 -> 20 us; with Garner's
-// digits runs gained nothing on square outputs.
+// digits runs gained nothing on square outputs.  Small and wide outputs from
+// stored planes keep the strips (reconstruct_strips in dispatch.hpp).
 constexpr int kRun = 1024, kSlab = kRun + 256, kPerThread = kRun / 256;
 using lds_ptr_r = __attribute__((address_space(3))) void*;
 
-// NATIVE: flagged outputs are re-issued here; else they get `fill`.
+// NATIVE: flagged outputs are re-issued here; else they get `fill` (NaN, or +0
+// where the native re-issue's own launch supplies them).
 template <bool ALIGNED, bool NATIVE>
 __global__ __launch_bounds__(256) void reconstruct_runs_kernel(int64_t mn, int n, int64_t ldc,
                                                                const int8_t* __restrict__ cres,
@@ -397,7 +398,7 @@ hipError_t launch_rec(int64_t m, int64_t n, const RT* cres, const int32_t* ea, c
   }
   if (strips) {
     hipLaunchKernelGGL((reconstruct_kernel<BYTES, RT>), grid_for(m, n), dim3(256), 0, stream, m, n, cres, ea, eb, C,
-                       ldc, subtract, fill);
+                       ldc, subtract);
   } else if constexpr (RUNS) {
     if (inside)
       launch_runs<true>(m, n, cres, ea, eb, C, ldc, subtract, fill, nat, stream);
@@ -419,8 +420,8 @@ hipError_t launch_reconstruct_i32(int64_t m, int64_t n, const int32_t* cres, con
 
 hipError_t launch_reconstruct_i16(int64_t m, int64_t n, const int16_t* cres, const int32_t* ea,
                                   const int32_t* eb, double* C, int64_t ldc, int subtract,
-                                  const NativeOperands& nat, hipStream_t stream) {
-  return launch_rec<false, int16_t>(m, n, cres, ea, eb, C, ldc, subtract, nat, stream);
+                                  hipStream_t stream) {
+  return launch_rec<false, int16_t>(m, n, cres, ea, eb, C, ldc, subtract, NativeOperands{}, stream);
 }
 
 hipError_t launch_reconstruct_bytes_i32(int64_t m, int64_t n, const int32_t* cres,
