@@ -991,8 +991,9 @@ __global__ __launch_bounds__(256) void bound_totals_kernel(int64_t m, int64_t n,
 // that separates it from a half integer for odd m; for even m (1024, 256)
 // the tie +m/2 maps to -m/2.  Grid: x over m n, y over the moduli.
 // V: values per thread, loaded as one piece (the host takes V > 1 where every
-// slice starts on such a piece); the loads of eight splits in flight.
-template <bool BYTES, typename OT, int V>
+// slice starts on such a piece); the loads of U splits in flight (the host
+// takes no more than about the splits there are: the rest repeat one).
+template <bool BYTES, typename OT, int V, int U>
 __global__ __launch_bounds__(256) void reduce_splits_kernel(int64_t mn, int splits,
                                                             const OT* __restrict__ part,
                                                             OT* __restrict__ out) {
@@ -1004,13 +1005,13 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(int64_t mn, int spli
   const int64_t stride = (int64_t)(BYTES ? kRA : kR) * mn;
   const int64_t at = (int64_t)q * mn + i;
   int sum[V] = {};
-  for (int sp = 0; sp < splits; sp += 8) {
-    piece p[8];
+  for (int sp = 0; sp < splits; sp += U) {
+    piece p[U];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < U; ++u)
       p[u] = *reinterpret_cast<const piece*>(part + (sp + u < splits ? sp + u : sp) * stride + at);
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int j = 0; j < V; ++j) sum[j] += sp + u < splits ? (int)p[u][j] : 0;
   }
@@ -1223,10 +1224,18 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const
     constexpr int V = 8 / (int)sizeof(OT);
     const int64_t per = mn % V == 0 && ((uintptr_t)part % 8) == 0 && ((uintptr_t)cres % 8) == 0 ? 256 * V : 256;
     const dim3 rgrid((unsigned)((mn + per - 1) / per), (unsigned)(BYTES ? kRA : kR));
-    if (per > 256)
-      hipLaunchKernelGGL((reduce_splits_kernel<BYTES, OT, V>), rgrid, dim3(256), 0, stream, mn, splits, part, cres);
-    else
-      hipLaunchKernelGGL((reduce_splits_kernel<BYTES, OT, 1>), rgrid, dim3(256), 0, stream, mn, splits, part, cres);
+#define OZ_REDUCE(V, U)                                                                                         \
+  hipLaunchKernelGGL((reduce_splits_kernel<BYTES, OT, V, U>), rgrid, dim3(256), 0, stream, mn, splits, part, cres)
+    if (per > 256) {
+      if (splits <= 2) OZ_REDUCE(V, 2);
+      else if (splits <= 4) OZ_REDUCE(V, 4);
+      else OZ_REDUCE(V, 8);
+    } else {
+      if (splits <= 2) OZ_REDUCE(1, 2);
+      else if (splits <= 4) OZ_REDUCE(1, 4);
+      else OZ_REDUCE(1, 8);
+    }
+#undef OZ_REDUCE
   }
   return hipGetLastError();
 }
