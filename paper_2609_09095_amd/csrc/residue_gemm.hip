@@ -48,6 +48,7 @@
 // 20-25 B/clk per CU, which bounds a stage (halving the stream cuts the time
 // by a quarter, halving the LDS fragment reads by 2 %), and the MFMA clock
 // itself drops with the switching activity of dense data.
+#include "dispatch.hpp"
 #include "kernels.hpp"
 #include "moduli.hpp"
 #include "residues.hpp"
@@ -1201,10 +1202,7 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t kp, const int8_t* pa, const
     }
   }
   if constexpr (BYTES) {
-    // few tiles per modulus: one range of the order per XCD (1537 x 2049 x
-    // 1031, 63 tiles, 143 -> 136 us for the call; 1024^3, 16 tiles, 50.0 ->
-    // 47.9; no change at 64 tiles of long k, and 4096^3, 256 tiles, 1 % slower)
-    const int ranges = blocks * splits / kRA <= 128;
+    const int ranges = xcd_ranges(blocks / kRA, nstage, splits);
     if (shape == 3)
       hipLaunchKernelGGL((residue_gemm_bytes_kernel<OT, 3>), grid, dim3(1024), 0, stream, m, n, kp, pa,
                          pb, dst, splits, group, ranges);

@@ -9,6 +9,7 @@ int rule_one_kernel(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb) {
 int rule_fused_a(int64_t m, int64_t n) { return oz::fused_a(m, n); }
 int rule_fused_moduli(int64_t m) { return oz::fused_moduli(m); }
 int rule_reconstruct_strips(int64_t m, int64_t n) { return oz::reconstruct_strips(m, n); }
+int rule_xcd_ranges(int64_t tiles, int64_t stages, int64_t splits) { return oz::xcd_ranges(tiles, stages, splits); }
 int rule_both_at_once(int64_t m, int64_t n, int64_t k, int64_t kp, int64_t room) {
   return oz::both_at_once(m, n, k, kp, room);
 }

@@ -28,6 +28,7 @@ def rules():
         i64 = ctypes.c_int64
         for name, args, res in (("rule_one_kernel", 5, ctypes.c_int), ("rule_fused_a", 2, ctypes.c_int),
                                 ("rule_fused_moduli", 1, ctypes.c_int), ("rule_reconstruct_strips", 2, ctypes.c_int),
+                                ("rule_xcd_ranges", 3, ctypes.c_int),
                                 ("rule_both_at_once", 5, ctypes.c_int), ("rule_scan_both_slabs", 2, i64),
                                 ("rule_scan_both_blocks", 3, i64)):
             f = getattr(L, name)

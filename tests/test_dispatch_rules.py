@@ -54,3 +54,14 @@ def test_tall_product_fills_its_rounds():
         g = L.rule_fused_moduli(m)
         assert cost[g] == min(cost.values()), m
     assert [L.rule_fused_moduli(m) for m in (1024, 6144, 6145, 10241, 12288, 12289, 262144)] == [3, 3, 5, 3, 3, 5, 5]
+
+
+def test_xcd_ranges_on_the_measured_side():
+    """The block placement of the int8 product, at products measured both
+    ways (tiles, stages of 128 k, splits): in ranges where that was faster,
+    dealt in turn where it was not."""
+    rule = rules().rule_xcd_ranges
+    for c in ((16, 8, 1), (30, 5, 1), (36, 32, 1), (16, 313, 1), (30, 94, 1), (9, 64, 3), (25, 24, 2), (6, 128, 5)):
+        assert rule(*c), c
+    for c in ((16, 3, 1), (4, 8, 2), (64, 128, 1), (4, 16, 4), (12, 313, 4), (6, 313, 5), (24, 128, 2), (256, 64, 1)):
+        assert not rule(*c), c
