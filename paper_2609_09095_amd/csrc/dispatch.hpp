@@ -101,14 +101,16 @@ constexpr bool both_at_once(int64_t m, int64_t n, int64_t k, int64_t kp, int64_t
 //  - 1024^3 (16, 1) 30.3 / 29.6 us, 1283 x 1025 x 640 (30, 1) 41.9 / 40.0, 1500 x
 //    1500 x 4096 (36, 1) 179 / 171, 1024 x 1024 x 40000 (16, 1) 600 / 554, 1283 x
 //    1025 x 12000 (30, 1) 331 / 301, 760 x 760 x 8192 (9, 3) 108 / 95, 1100 x 1100 x
-//    3000 (25, 2) 103 / 99;
+//    3000 (25, 2) 103 / 99, 500 x 1000 x 54000 (8, 2) 428 / 415, 760 x 500 x 30000
+//    (6, 5) 220 / 213;
 //  - 1024 x 1024 x 384 (16, 1) 22.5 / 25.7, 500 x 500 x 1024 (4, 2) 23.4 / 25.8, 2048
 //    x 2048 x 16384 (64, 1) 912 / 930, 500 x 500 x 2000 (4, 4) 27.7 / 30.1, 783 x 708
 //    x 40000 (12, 4) 432 / 467, 700 x 300 x 40000 (6, 5) 226 / 248, 1391 x 983 x
 //    16384 (24, 2) 390 / 401.
 constexpr bool xcd_ranges(int64_t tiles, int64_t stages, int64_t splits) {
   if (tiles * splits > 128 || splits % 4 == 0 || stages / splits < (splits > 1 || tiles <= 20 ? 8 : 3)) return false;
-  return splits == 1 ? tiles <= 32 || stages <= 64 : stages <= (splits == 2 ? 64 : 128);
+  if (splits == 1) return tiles <= 32 || stages <= 64;
+  return tiles <= 10 ? splits < 4 || stages <= 240 : stages <= 64;
 }
 
 // Whether the reconstruction from stored byte planes (no native re-issue)

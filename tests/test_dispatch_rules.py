@@ -61,7 +61,7 @@ def test_xcd_ranges_on_the_measured_side():
     ways (tiles, stages of 128 k, splits): in ranges where that was faster,
     dealt in turn where it was not."""
     rule = rules().rule_xcd_ranges
-    for c in ((16, 8, 1), (30, 5, 1), (36, 32, 1), (16, 313, 1), (30, 94, 1), (9, 64, 3), (25, 24, 2), (6, 128, 5)):
+    for c in ((16, 8, 1), (30, 5, 1), (36, 32, 1), (16, 313, 1), (30, 94, 1), (9, 64, 3), (25, 24, 2), (6, 235, 5), (8, 422, 2)):
         assert rule(*c), c
     for c in ((16, 3, 1), (4, 8, 2), (64, 128, 1), (4, 16, 4), (12, 313, 4), (6, 313, 5), (24, 128, 2), (256, 64, 1)):
         assert not rule(*c), c
