@@ -486,9 +486,9 @@ hipError_t launch_deconstruct_bytes_both(int quant, int64_t m, int64_t n, int64_
   const int mode = t <= 51 ? 1 : (t == 52 ? 2 : 3);  // as in launch_deconstruct
   // streaming plane stores, but for long k and planes that the last-level
   // cache holds with room plain ones, which the products then find there
-  // (2048^3, 120 MiB, 202 -> 192 us a call, 256 x 256 x 8192 56.7 -> 53.8, 700 x 900
-  // x 3000 79.7 -> 76.6; at short k no better, 3000 x 2500 x 700 1 % slower, and
-  // 2000 x 4000 x 4000, 343 MiB, likewise)
+  // (2048^3, 120 MiB, 198 -> 188 us a call, 900 x 700 x 4096 98.8 -> 93.1, 700 x
+  // 900 x 3000 78.4 -> 73.9; within 2 % either way at 256 x 256 and 512 x 512; no
+  // better at short k, nor at 2000 x 4000 x 4000, 343 MiB)
   const bool nt = kp < 2048 || kRA * (m + n) * kp > (int64_t)128 << 20;
 #define OZ_BOTH(MODE, TZ, NT)                                                                                     \
   hipLaunchKernelGGL((deconstruct_bytes_both_kernel<MODE, TZ, NT>), dim3((unsigned)blocks), dim3(256), 0, stream, \

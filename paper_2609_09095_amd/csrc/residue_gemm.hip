@@ -728,8 +728,8 @@ __device__ __forceinline__ int cmod_i32(int x, int m, double minv) {
 // instructions (the quotient in the low word of the FMA onto 1.5 2^52, then
 // x - q m modulo 2^24) where the int32 residue takes five -- in the epilogue
 // all wavefronts wait on them.  qinv: RN(1/m), 0 for m = 256, whose residue
-// byte is x's own.  32768^2 x 1024 update 23.2 -> 22.5 ms a call, 20000 x 3000 x
-// 256 835 -> 801 us, 8192^3 unchanged.
+// byte is x's own.  32768^2 x 1024 update 23.5 -> 22.9 ms a call, 20000 x 3000 x
+// 256 784 -> 758 us, 8192^3 7.44 -> 7.40 ms.
 __constant__ double kQinvA[kRA] = {
     0.0,                 1.0 / kModulusA[1],  1.0 / kModulusA[2],  1.0 / kModulusA[3],
     1.0 / kModulusA[4],  1.0 / kModulusA[5],  1.0 / kModulusA[6],  1.0 / kModulusA[7],

@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256) void scan_cols_kernel(int64_t vecs, int64_t k,
 // Both operands' scans in one launch: blocks below ablocks take a row of A
 // each, or four rows of at most kShortRow elements, a wavefront per row, as a
 // block would spend such a row on starting and joining its wavefronts
-// (262144 rows of 256: 254 -> 161 us; 100000 of 300: 103 -> 58); sigma goes
+// (262144 rows of 256: 241 -> 148 us; 100000 of 300: 88 -> 55); sigma goes
 // to ea.  The others take a slab of 64 columns x rows_per_block rows of B,
 // whose column keys go to part[slab][n] -- plain stores, combined by the
 // deconstruction on load, where atomics would need cleared keys.  Sixteen
