@@ -200,7 +200,7 @@ __global__ __launch_bounds__(1024) void one_kernel(int m, int n, int k, int tile
     const int sa = sig[0][row], sb = sig[1][col];
     double r;
     if (sa == INT32_MIN || sb == INT32_MIN) {
-      r = native_dot(A + (int64_t)(row0 + row) * lda, B + col0 + col, ldb, k);
+      r = native_dot(A + (int64_t)(row0 + row) * lda, B + col0, (uint32_t)col, ldb, k);
     } else {
       int c[kRA];
 #pragma unroll

@@ -29,7 +29,6 @@
 //    integer and rounded once.
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
 #include <utility>
 
 #include "dispatch.hpp"
@@ -248,30 +247,6 @@ __global__ __launch_bounds__(256) void reconstruct_runs_kernel(int64_t mn, int n
     col -= dr * n;
   };
   [[maybe_unused]] unsigned flagged = 0;  // bit j: output tid + 256 j awaits its re-issue
-  // N = kPerThread: bit j's output is dot j, with an unflagged one repeating the
-  // first flagged; N = 1: that one
-  [[maybe_unused]] auto reissue = [&]<int N>(std::integral_constant<int, N>) __attribute__((always_inline)) {
-    const double *a[N], *b[N];
-    double s[N];
-    const int first = __builtin_ctz(flagged);
-    auto output = [&](int j) { return N > 1 && (flagged >> j & 1) ? j : first; };
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      int dr, col;
-      place(threadIdx.x + 256 * output(j), dr, col);
-      a[j] = nat.A + (row0 + dr) * nat.lda;
-      b[j] = nat.B + col;
-    }
-    native_dots(a, b, nat.ldb, nat.k, s);
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      if (N > 1 && !(flagged >> j & 1)) continue;
-      int dr, col;
-      place(threadIdx.x + 256 * output(j), dr, col);
-      double* out = C + (row0 + dr) * ldc + col;
-      *out = subtract ? *out - s[j] : s[j];
-    }
-  };
 #pragma unroll
   for (int j = 0; j < kPerThread; ++j) {
     const int o = threadIdx.x + 256 * j;
@@ -296,15 +271,45 @@ __global__ __launch_bounds__(256) void reconstruct_runs_kernel(int64_t mn, int n
   }
   if constexpr (NATIVE) {
     if (!flagged) return;
-    // the thread's flagged outputs together: a flagged row of 1024 columns is
-    // four of every thread, and one after another they took 1.02 ms at 1024^3
-    // (0.36 together).  Where no thread of the wavefront has more than one (a
-    // flagged column, short rows), that one alone: the others' loads would
-    // cost 20 to 100 %.
-    if (__any(flagged & (flagged - 1)))
-      reissue(std::integral_constant<int, kPerThread>{});
-    else
-      reissue(std::integral_constant<int, 1>{});
+    const auto row_of = [&](int j) __attribute__((always_inline)) {
+      int dr, col;
+      place(threadIdx.x + 256 * j, dr, col);
+      return dr;
+    };
+    // a flagged row is up to four outputs of every thread: where all of the
+    // wavefront's lie on one row and some thread has several, together (1024
+    // columns at k = 4096 add 0.49 ms, one after another 0.77), an unflagged one
+    // repeating the thread's first
+    const int first = __builtin_ctz(flagged), dr0 = __builtin_amdgcn_readfirstlane(row_of(first));
+    bool one_row = true;
+#pragma unroll
+    for (int j = 0; j < kPerThread; ++j)
+      if (flagged >> j & 1) one_row = one_row && row_of(j) == dr0;
+    if (__any(flagged & (flagged - 1)) && __all(one_row)) {
+      uint32_t cols[kPerThread];
+      double s[kPerThread];
+#pragma unroll
+      for (int j = 0; j < kPerThread; ++j) {
+        int dr, col;
+        place(threadIdx.x + 256 * (flagged >> j & 1 ? j : first), dr, col);
+        cols[j] = (uint32_t)col;
+      }
+      native_dots<kPerThread, 4>(nat.A + (row0 + dr0) * nat.lda, nat.B, cols, nat.ldb, nat.k, s);
+#pragma unroll
+      for (int j = 0; j < kPerThread; ++j) {
+        if (!(flagged >> j & 1)) continue;
+        double* out = C + (row0 + dr0) * ldc + cols[j];
+        *out = subtract ? *out - s[j] : s[j];
+      }
+      return;
+    }
+    for (; flagged; flagged &= flagged - 1) {
+      int dr, col;
+      place(threadIdx.x + 256 * __builtin_ctz(flagged), dr, col);
+      const double d = native_dot(nat.A + (row0 + dr) * nat.lda, nat.B, (uint32_t)col, nat.ldb, nat.k);
+      double* out = C + (row0 + dr) * ldc + col;
+      *out = subtract ? *out - d : d;
+    }
   }
 }
 
@@ -334,7 +339,8 @@ __global__ __launch_bounds__(256) void native_reissue_kernel(int64_t m, int64_t 
       for (int i = 0; i < rows; ++i) {
         if (!rowflag[i] && !colflag) continue;
         const int64_t row = row0 + i;
-        const double d = native_dot(nat.A + row * nat.lda, nat.B + col, nat.ldb, nat.k);
+        const double d = native_dot(nat.A + row * nat.lda, nat.B + (int64_t)blockIdx.x * 256, threadIdx.x, nat.ldb,
+                                    nat.k);
         double* out = C + row * ldc + col;
         *out = subtract ? *out - d : d;
       }
