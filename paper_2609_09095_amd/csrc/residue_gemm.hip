@@ -965,6 +965,7 @@ __global__ __launch_bounds__(256) void bound_totals_kernel(int64_t m, int64_t n,
   int low = 127;
   for (int r = 0; r < 16; r += 4) {
     const int64_t i0 = g * 64 + wave * 16 + r;
+    if (i0 >= m) break;  // rows past m: 1 x 64 x 30000 81 -> 69 us a call
     int sum[4] = {};
     for (int sp = 0; sp < splits; ++sp)
 #pragma unroll

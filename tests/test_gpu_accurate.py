@@ -208,3 +208,29 @@ def test_accurate_square_8192():
     log(f"max |C - AB| on the sample (long double reference): accurate {float(err_acc):.3e}, "
         f"fast {float(err_fast):.3e}")
     assert err_acc <= err_fast
+
+
+def test_split_bound_totals_of_few_rows_cost_less():
+    """A split bound product's totals are summed per 64-row group: a single row
+    pays for its own partial sums, not for those of the rows past m (0.62 of
+    the call on 17 rows; 0.72 where every wavefront summed clamped rows)."""
+    import torch
+    n, k = 64, 30000
+    best = {}
+    for m in (1, 17):
+        A = to_dev(workloads.random_matrix(m, k, 1.0, 71))
+        B = to_dev(workloads.random_matrix(k, n, 1.0, 72))
+        ea, eb = (torch.empty(v, dtype=torch.int32, device="cuda") for v in (m, n))
+        ws = torch.empty(oz.ozaki25_accurate_exponents_workspace_size(m, n, k), dtype=torch.uint8, device="cuda")
+        times = []
+        for _ in range(9):
+            s, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            s.record()
+            for _ in range(20):
+                oz.ozaki25_accurate_exponents(A, B, ea, eb, workspace=ws)
+            e.record()
+            torch.cuda.synchronize()
+            times.append(s.elapsed_time(e) / 20)
+        best[m] = min(times)
+    log(f"accurate exponents: {best}")
+    assert best[1] < 0.67 * best[17], best
