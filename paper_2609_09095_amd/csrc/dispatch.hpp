@@ -115,15 +115,19 @@ constexpr bool xcd_ranges(int64_t tiles, int64_t stages, int64_t splits) {
 
 // Whether the reconstruction from stored byte planes (no native re-issue)
 // takes strips of 256 columns, a thread per output and row, rather than runs
-// of 1024 consecutive outputs: where runs are too few to fill the chip, and for
-// whole strips (every store then starts on a line) of up to 2^21 outputs.
+// of 1024 consecutive outputs: where runs are too few to fill the chip (below 64
+// columns from the third or fourth output that a run's thread would take, one
+// after another), and for whole strips (every store then starts on a line) of
+// up to 2^21 outputs.
 // Strips / runs: 64 x 1024 4.2 / 5.2 us, 256 x 1024 4.6 / 6.1, 128 x 4096 6.4 /
-// 7.0, 11 x 93106 8.9 / 10.2, 2048 x 1024 13.9 / 15.1, level at 4096 x 1024; the
+// 7.0, 11 x 93106 8.9 / 10.2, 2048 x 1024 13.9 / 15.1, level at 4096 x 1024;
+// whole calls at k = 1 128 x 40 11.4 / 12.3, 1021 x 32 12.1 / 12.9, 28 x 32 11.1 / 11.5; the
 // other way 4080 x 257 16.6 / 9.7, 16384 x 64 12.2 / 9.1, 1023 x 1025 11.3 /
 // 10.3, 262144 x 8 131 / 20.
 constexpr bool reconstruct_strips(int64_t m, int64_t n) {
   const int64_t mn = m * n;
-  return n >= 64 && (mn <= 1 << 18 || (mn <= 1 << 20 && n >= 4096) || (mn <= 1 << 21 && n % 256 == 0));
+  if (n < 64) return n >= 24 && mn > (n >= 40 ? 512 : 768) && mn <= 1 << 15;
+  return mn <= 1 << 18 || (mn <= 1 << 20 && n >= 4096) || (mn <= 1 << 21 && n % 256 == 0);
 }
 
 }  // namespace oz

@@ -20,9 +20,10 @@ def gpu():
     require_gpu()
 
 
-RUNS = [(257, 1023, 0), (301, 1028, 1), (259, 1025, 3), (2049, 129, 0), (5000, 53, 1), (3, 7, 0), (4, 63, 2),
+RUNS = [(32, 24, 0), (8, 63, 1), (1366, 24, 0), (257, 1023, 0), (301, 1028, 1), (259, 1025, 3), (2049, 129, 0), (5000, 53, 1), (3, 7, 0), (4, 63, 2),
         (1, 1048579, 0), (262147, 1, 2), (513, 513, 1), (2049, 1024, 0)]
-STRIPS = [(4, 64, 0), (300, 1024, 1), (1, 262147, 0), (255, 1028, 2), (9, 93106, 1), (2050, 512, 0), (2, 100, 3)]
+STRIPS = [(4, 64, 0), (33, 24, 1), (9, 57, 0), (1040, 31, 2), (520, 63, 0), (300, 1024, 1), (1, 262147, 0),
+          (255, 1028, 2), (9, 93106, 1), (2050, 512, 0), (2, 100, 3)]
 
 
 @pytest.mark.parametrize("m, n, pad, strips", [(*c, False) for c in RUNS] + [(*c, True) for c in STRIPS])
