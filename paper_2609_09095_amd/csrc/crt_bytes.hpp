@@ -12,12 +12,13 @@
 //    by less than 2^-40, so X = S - k M lies in [-M/2, M/2) unless the
 //    quotient is within 2^-40 of a half integer (declined).
 //  - R_j = S_j - k M_j exactly (|k M_j| < 2^51 units).
-//  - p + ep = R_2 + R_1 exactly (two-sum).  Where ep = 0, X 2^-40 = p + R_0
-//    and r = RN(p + R_0) is the rounding itself.  Otherwise |p| >= 2^53,
-//    t = RN(ep + R_0), |t| < 2^26, r = RN(p + t), res = p + t - r exactly
-//    (Fast2Sum), and X 2^-40 - r = res + d with |d| <= |t| 2^-53: r is RN of
-//    it when |res| + |d| < ulp(r)/2 (with a factor-2 margin) and r is no power
-//    of two.
+//  - p + ep = R_2 + R_1 and t + te = ep + R_0 exactly (two-sums), and
+//    r = RN(p + t).  Where te = 0 (ep = 0, or X has few significant bits, as
+//    the products of integers and of FP32 values do), X 2^-40 = p + t and r is
+//    the rounding itself, of ties and powers of two too.  Otherwise |p| >= 2^53,
+//    |t| < 2^26, res = p + t - r exactly (Fast2Sum), and X 2^-40 - r = res + d
+//    with |d| <= |t| 2^-53: r is RN of it when |res| + |d| < ulp(r)/2 (with a
+//    factor-2 margin) and r is no power of two.
 // Returns false where that does not go through, or the result is subnormal.
 #pragma once
 
@@ -94,11 +95,13 @@ __device__ __forceinline__ bool crt_bytes(const int (&c)[kRA], int e, double& ou
   const double t = ep + r0;
   const double r = p + t;
   const double res = t - (r - p);
+  const double tb = t - ep;
+  const double te = (ep - (t - tb)) + (r0 - tb);
   const uint64_t rb = __builtin_bit_cast(uint64_t, r);
   const int eb = (int)(rb >> 52) & 0x7FF;
   const double halfu = __builtin_bit_cast(double, (uint64_t)(eb - 53) << 52);
   const double bound = __builtin_fma(__builtin_fabs(t), 0x1p-51, __builtin_fabs(res));
-  const bool rounded = ep == 0.0 || (bound < halfu && (rb << 12) != 0);
+  const bool rounded = te == 0.0 || (bound < halfu && (rb << 12) != 0);
   out = __builtin_ldexp(r, e + 40);
   return inside && rounded && (eb + e + 40 >= 1 || eb == 0);
 }

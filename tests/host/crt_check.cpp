@@ -3,8 +3,8 @@
 // bit for bit.  Cases: random X of every magnitude; values at and next to
 // powers of two, FP64 midpoints and the limbs' boundaries; the ends of
 // [-M/2, M/2); normal, subnormal and overflow scales.  Also checked: random
-// values are claimed almost always, and zero gives +0.  Exit status 0 on
-// success.
+// values are claimed almost always, those of few significant bits always, and
+// zero gives +0.  Exit status 0 on success.
 #include <cstdio>
 #include <cstring>
 
@@ -85,10 +85,22 @@ int main() {
     check(-M / 2 + d, -100);
     check((M / 2 - 1 - d) - ((i128)rnd() << (rnd() % 50)), -100);
   }
+  // few significant bits (products of integers, of FP32 values, of powers of
+  // two): every one is claimed, ties and powers of two among them
+  long few_claimed = 0, few_all = 0;
+  for (int it = 0; it < 1000000; ++it) {
+    const int bits = 1 + (int)(rnd() % 57), sh = (int)(rnd() % (117 - bits));
+    i128 X = (i128)(rnd() >> (64 - bits) | 1ull << (bits - 1));
+    if (it % 4 == 0) X = (i128)1 << (bits - 1);
+    X <<= sh;
+    if (X >= M / 2) continue;
+    few_all += 2;
+    few_claimed += check(X, -100) + check(-X, -100);
+  }
   int z[kRA] = {};
   double f = 1.0;
   const bool zero = crt_bytes(z, 5, f) && f == 0.0 && !__builtin_signbit(f);
-  printf("claimed %ld declined %ld mismatches %ld; random claimed %ld of %ld; zero %d\n", claimed, declined, bad,
-         random_claimed, random_all, (int)zero);
-  return bad || !zero || random_claimed < random_all * 0.999;
+  printf("claimed %ld declined %ld mismatches %ld; random claimed %ld of %ld; few bits %ld of %ld; zero %d\n", claimed,
+         declined, bad, random_claimed, random_all, few_claimed, few_all, (int)zero);
+  return bad || !zero || random_claimed < random_all * 0.999 || few_claimed < few_all;
 }
