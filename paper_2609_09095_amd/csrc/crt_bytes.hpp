@@ -19,7 +19,11 @@
 //    |t| < 2^26, res = p + t - r exactly (Fast2Sum), and X 2^-40 - r = res + d
 //    with |d| <= |t| 2^-53: r is RN of it when |res| + |d| < ulp(r)/2 (with a
 //    factor-2 margin) and r is no power of two.
-// Returns false where that does not go through, or the result is subnormal.
+//  - a subnormal result is r rounded once more, by the scaling: the rounding of
+//    X 2^e unless r lies on a tie of the subnormal grid (the ties are FP64
+//    numbers: any other is at least a whole step from r on its side, X 2^-40 at
+//    most half of one), where the sign of X 2^-40 - r decides.
+// Returns false where that does not go through.
 #pragma once
 
 #include <cstdint>
@@ -103,7 +107,15 @@ __device__ __forceinline__ bool crt_bytes(const int (&c)[kRA], int e, double& ou
   const double bound = __builtin_fma(__builtin_fabs(t), 0x1p-51, __builtin_fabs(res));
   const bool rounded = te == 0.0 || (bound < halfu && (rb << 12) != 0);
   out = __builtin_ldexp(r, e + 40);
-  return inside && rounded && (eb + e + 40 >= 1 || eb == 0);
+  const bool proven = inside && rounded;
+  if (proven && (eb + e + 40 >= 1 || eb == 0)) [[likely]]
+    return true;
+  if (!proven) return false;
+  const double half = __builtin_ldexp(1.0, -1115 - e);  // of the subnormal grid's step
+  // res + te: X 2^-40 - r exactly (where |p| < |t|, p + t needs no rounding)
+  if (__builtin_fabs(r - __builtin_ldexp(out, -e - 40)) == half && res + te != 0.0)
+    out = __builtin_copysign(__builtin_ldexp(r + __builtin_copysign(half, res + te), e + 40), r);
+  return true;
 }
 
 }  // namespace oz

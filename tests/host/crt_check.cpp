@@ -3,8 +3,7 @@
 // bit for bit.  Cases: random X of every magnitude; values at and next to
 // powers of two, FP64 midpoints and the limbs' boundaries; the ends of
 // [-M/2, M/2); normal, subnormal and overflow scales.  Also checked: random
-// values are claimed almost always, those of few significant bits always, and
-// zero gives +0.  Exit status 0 on success.
+// values are claimed almost always, with a subnormal result too, those of few significant bits always, and zero gives +0.  Exit status 0 on success.
 #include <cstdio>
 #include <cstring>
 
@@ -57,13 +56,21 @@ int main() {
   M = 1;
   for (int j = 0; j < kRA; ++j) M *= kModulusA[j];
   const int scales[] = {0, -100, -1030, -1074, -1100, -1150, 900, 960, 1023, -60};
-  long random_claimed = 0, random_all = 0;
+  long random_claimed = 0, random_all = 0, sub_claimed = 0, sub_all = 0;
   for (int it = 0; it < 3000000; ++it) {
     i128 X = ((i128)rnd() << 64) | (i128)rnd();
     X >>= 10 + (int)(rnd() % 117);
     ++random_all;
     random_claimed += X >= -M / 2 && X < M / 2 ? check(X, -100) : 1;
     check(X, scales[it % 10]);
+    // a subnormal result, down to its last bits and zero
+    const i128 Y = X < 0 ? -X : X;
+    int top = 127;
+    while (top > 0 && !(Y >> top)) --top;
+    if (Y && Y < M / 2) {
+      ++sub_all;
+      sub_claimed += check(X, -1023 - top - (int)(rnd() % 56));
+    }
   }
   for (int b = 0; b <= 117; ++b)
     for (int l = -1; l <= b; ++l)
@@ -85,6 +92,13 @@ int main() {
     check(-M / 2 + d, -100);
     check((M / 2 - 1 - d) - ((i128)rnd() << (rnd() % 50)), -100);
   }
+  // next to and on the ties of shallow subnormals
+  for (int it = 0; it < 1000000; ++it) {
+    const int sh = 60 + (int)(rnd() % 4), drop = 1 + (int)(rnd() % 8);
+    i128 X = (((i128)((rnd() >> 11) | (1ull << 52)) >> drop) << (sh + drop)) + ((i128)1 << (sh + drop - 1)) + (int)(rnd() % 5) - 2;
+    if (it & 8) X -= (i128)(rnd() >> 40);
+    check(rnd() & 1 ? X : -X, -1074 - sh - drop);
+  }
   // few significant bits (products of integers, of FP32 values, of powers of
   // two): every one is claimed, ties and powers of two among them
   long few_claimed = 0, few_all = 0;
@@ -100,7 +114,8 @@ int main() {
   int z[kRA] = {};
   double f = 1.0;
   const bool zero = crt_bytes(z, 5, f) && f == 0.0 && !__builtin_signbit(f);
-  printf("claimed %ld declined %ld mismatches %ld; random claimed %ld of %ld; few bits %ld of %ld; zero %d\n", claimed,
-         declined, bad, random_claimed, random_all, few_claimed, few_all, (int)zero);
-  return bad || !zero || random_claimed < random_all * 0.999 || few_claimed < few_all;
+  printf("claimed %ld declined %ld mismatches %ld; random claimed %ld of %ld; few bits %ld of %ld; subnormal %ld of %ld; zero %d\n",
+         claimed, declined, bad, random_claimed, random_all, few_claimed, few_all, sub_claimed, sub_all, (int)zero);
+  return bad || !zero || random_claimed < random_all * 0.999 || few_claimed < few_all ||
+         sub_claimed < sub_all * 0.999;
 }

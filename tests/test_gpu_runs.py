@@ -50,3 +50,27 @@ def test_runs_and_strips_match_oracle(m, n, pad, strips):
         want = oracle.dgemm(A, B, C_in=c, set=1, want_planes=False, fallback=False).C
         assert_bits_equal(C.cpu().numpy(), want, "C")
         assert bool((full[:, n:] == 5.0).all())
+
+
+# results across the whole subnormal range, and exact ones with ties: one
+# launch, runs (re-issue inside and apart), storage mode F
+@pytest.mark.parametrize("scale", [2.0 ** -515, 2.0 ** -530, 1.0])
+@pytest.mark.parametrize("m, n, k", [(300, 200, 20), (700, 650, 300), (2100, 2050, 40), (1500, 100, 500)])
+def test_subnormal_and_exact_results_match_oracle(m, n, k, scale):
+    import torch
+    rng = np.random.default_rng(m + n)
+    rows = np.unique(rng.integers(0, m, 60))
+    A = workloads.random_matrix(m, k, 3.0, 750)
+    B = workloads.random_matrix(k, n, 3.0, 751)
+    if scale == 1.0:  # products of FP32 values: ties in the last bits
+        A, B = A.astype(np.float32).astype(np.float64), B.astype(np.float32).astype(np.float64)
+        A[:, 2:] = 0.0
+        A[1] = 0.0
+        A[1, 0] = 1.0
+    A, B = A * scale, B * scale
+    log(f"subnormal results m={m} n={n} k={k} scale={scale}")
+    C = torch.empty((m, n), dtype=torch.float64, device="cuda")
+    oz.ozaki25_dgemm_ex(to_dev(A), to_dev(B), C)
+    torch.cuda.synchronize()
+    want = oracle.dgemm(A, B, rows=rows, want_planes=False).C
+    assert_bits_equal(C.cpu().numpy()[rows], want, "C (sampled rows)")
