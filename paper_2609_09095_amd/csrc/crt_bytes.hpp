@@ -99,18 +99,21 @@ __device__ __forceinline__ bool crt_bytes(const int (&c)[kRA], int e, double& ou
   const double t = ep + r0;
   const double r = p + t;
   const double res = t - (r - p);
-  const double tb = t - ep;
-  const double te = (ep - (t - tb)) + (r0 - tb);
   const uint64_t rb = __builtin_bit_cast(uint64_t, r);
   const int eb = (int)(rb >> 52) & 0x7FF;
   const double halfu = __builtin_bit_cast(double, (uint64_t)(eb - 53) << 52);
   const double bound = __builtin_fma(__builtin_fabs(t), 0x1p-51, __builtin_fabs(res));
-  const bool rounded = te == 0.0 || (bound < halfu && (rb << 12) != 0);
+  const bool proven = ep == 0.0 || (bound < halfu && (rb << 12) != 0);
   out = __builtin_ldexp(r, e + 40);
-  const bool proven = inside && rounded;
-  if (proven && (eb + e + 40 >= 1 || eb == 0)) [[likely]]
+  const bool normal = eb + e + 40 >= 1 || eb == 0;
+  if (inside && proven && normal) [[likely]]
     return true;
-  if (!proven) return false;
+  // apart from the common path, whose chain it would lengthen (201 x 333 x 157
+  // 11.4 -> 11.5 us)
+  const double tb = t - ep;
+  const double te = (ep - (t - tb)) + (r0 - tb);
+  if (!inside || !(proven || te == 0.0)) return false;
+  if (normal) return true;
   const double half = __builtin_ldexp(1.0, -1115 - e);  // of the subnormal grid's step
   // res + te: X 2^-40 - r exactly (where |p| < |t|, p + t needs no rounding)
   if (__builtin_fabs(r - __builtin_ldexp(out, -e - 40)) == half && res + te != 0.0)

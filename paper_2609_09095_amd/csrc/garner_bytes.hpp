@@ -71,20 +71,23 @@ __device__ __forceinline__ int garner_digit_a(const int (&c)[kRA], uint32_t (&pa
   return v;
 }
 
-// RN(X 2^e) of the integer X in [-M/2, M/2) with centred residues c: the FP64
-// CRT sum (crt_bytes.hpp), or where that cannot prove its rounding Garner's
-// digits and 128-bit integers.
+// RN(X 2^e) of the integer X in [-M/2, M/2) with centred residues c, by
+// Garner's digits and 128-bit integers.
+__device__ __forceinline__ double garner_exact(const int (&c)[kRA], int e) {
+  int v[kRA];
+  uint32_t packed[4] = {0, 0, 0, 0};
+  [&]<int... J>(std::integer_sequence<int, J...>) {
+    ((v[J] = garner_digit_a<J>(c, packed)), ...);
+  }(std::make_integer_sequence<int, kRA>{});
+  // |xl| <= P/2, |xh| <= (Q - 1) / 2
+  return round_exact_a(half_value_a<0, kSplitA>(v), half_value_a<kSplitA, kRA>(v), e);
+}
+
+// The same by the FP64 CRT sum (crt_bytes.hpp), or as above where that cannot
+// prove its rounding.
 __device__ __forceinline__ double garner_bytes(const int (&c)[kRA], int e) {
   double out;
-  if (!crt_bytes(c, e, out)) {
-    int v[kRA];
-    uint32_t packed[4] = {0, 0, 0, 0};
-    [&]<int... J>(std::integer_sequence<int, J...>) {
-      ((v[J] = garner_digit_a<J>(c, packed)), ...);
-    }(std::make_integer_sequence<int, kRA>{});
-    // |xl| <= P/2, |xh| <= (Q - 1) / 2
-    out = round_exact_a(half_value_a<0, kSplitA>(v), half_value_a<kSplitA, kRA>(v), e);
-  }
+  if (!crt_bytes(c, e, out)) out = garner_exact(c, e);
   return out;
 }
 

@@ -246,7 +246,13 @@ __global__ __launch_bounds__(256) void reconstruct_runs_kernel(int64_t mn, int n
     dr = n >= kRun ? (col >= n ? 1 : 0) : (int)(((float)col + 0.5f) * rn);
     col -= dr * n;
   };
-  [[maybe_unused]] unsigned flagged = 0;  // bit j: output tid + 256 j awaits its re-issue
+  auto residues = [&](int o, int (&c)[kRA]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < kRA; ++q) c[q] = slab[q * kSlab + (ALIGNED ? 0 : (int)((q * mn + i0) & 3)) + o];
+  };
+  // bit j: output tid + 256 j awaits Garner's digits, or its re-issue
+  unsigned declined = 0;
+  [[maybe_unused]] unsigned flagged = 0;
 #pragma unroll
   for (int j = 0; j < kPerThread; ++j) {
     const int o = threadIdx.x + 256 * j;
@@ -259,15 +265,27 @@ __global__ __launch_bounds__(256) void reconstruct_runs_kernel(int64_t mn, int n
     double r = fill;
     if (sa != INT32_MIN && sb != INT32_MIN) {
       int c[kRA];
-#pragma unroll
-      for (int q = 0; q < kRA; ++q)
-        c[q] = slab[q * kSlab + (ALIGNED ? 0 : (int)((q * mn + i0) & 3)) + o];
-      r = garner_bytes(c, -sa - sb);
+      residues(o, c);
+      if (!crt_bytes(c, -sa - sb, r)) {
+        declined |= 1u << j;
+        continue;
+      }
     } else if constexpr (NATIVE) {
       flagged |= 1u << j;
       continue;
     }
     __builtin_nontemporal_store(subtract ? old - r : r, out);
+  }
+  // apart from the loop, whose code would hold Garner's path four times over
+  // (short launches wait for their instructions)
+  for (; declined; declined &= declined - 1) {
+    const int o = threadIdx.x + 256 * __builtin_ctz(declined);
+    int dr, col, c[kRA];
+    place(o, dr, col);
+    residues(o, c);
+    const double r = garner_exact(c, -ea[row0 + dr] - eb[col]);
+    double* out = C + (row0 + dr) * ldc + col;
+    *out = subtract ? *out - r : r;
   }
   if constexpr (NATIVE) {
     if (!flagged) return;
